@@ -358,7 +358,7 @@ struct Engine {
         }
         // coarse tail: every member's levels with edges up to the tail edge, in
         // one workgroup per member (all batched iterates start at zero)
-        const int a_t = std::getenv("MG_NO_TAIL") ? 0 : log2edge(tail_max_edge(dim, 4));
+        const int a_t = std::getenv("MG_NO_TAIL") ? 0 : log2edge(tail_max_edge(dim, 4, OP_LAP));
         if (a_t >= 1 && a_t <= kMaxTailLevels) {
             for (const Inst* I : members) {
                 TailDesc t{};

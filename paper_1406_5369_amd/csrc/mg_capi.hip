@@ -266,7 +266,7 @@ int validate(const mg_params* p) {
     if (p->nu1 < 0 || p->nu2 < 0 || p->nu1 > 16 || p->nu2 > 16) return MG_EINVAL;
     if (p->cycle < MG_CYCLE_V || p->cycle > MG_CYCLE_F || p->cg_iters < 0) return MG_EINVAL;
     if (p->coarse_n != 0 && (!valid_edge(p->dim, p->coarse_n) || p->coarse_n > p->n)) return MG_EINVAL;
-    if (p->coarse_n > tail_max_edge(p->dim, p->precision == MG_PREC_FP64 ? 8 : 4)) return MG_ENOTSUP;
+    if (p->coarse_n > cg_max_edge(p->dim, p->precision == MG_PREC_FP64 ? 8 : 4)) return MG_ENOTSUP;
     if (p->precision != MG_PREC_FP64 && p->precision != MG_PREC_FP32_IR && p->precision != MG_PREC_FP16_IR)
         return MG_ENOTSUP;
     if (p->precision == MG_PREC_FP16_IR && p->op != MG_OP_LAPLACE) return MG_ENOTSUP;
@@ -1447,7 +1447,7 @@ int mg_setup(const mg_params* p, void* stream, mg_ctx** out) {
         SETUP_CK(build_levels(c->L64, dim, c->n, 8, false, c->k64, s));
         SETUP_CK(build_faces(c->L64, s));
         SETUP_CK(build_groups(c->G64, c->L64, c->prob, ctl_done(c), s));
-        SETUP_CK(build_tail(c->tail64, c->G64, tail_first_level(dim, 8, c->n, false), s));
+        SETUP_CK(build_tail(c->tail64, c->G64, tail_first_level(dim, 8, c->prob.op(), c->n, false), s));
     } else {
         SETUP_CK(build_levels(c->L32, dim, c->n, ir_elem(c->p), true, nullptr, s));
         if (c->prob.var) {
@@ -1465,7 +1465,7 @@ int mg_setup(const mg_params* p, void* stream, mg_ctx** out) {
         }
         SETUP_CK(build_faces(c->L32, s));
         SETUP_CK(build_groups(c->G32, c->L32, c->prob, ctl_done(c), s));
-        SETUP_CK(build_tail(c->tail32, c->G32, tail_first_level(dim, ir_elem(c->p), c->n, true), s));
+        SETUP_CK(build_tail(c->tail32, c->G32, tail_first_level(dim, ir_elem(c->p), c->prob.op(), c->n, true), s));
         SETUP_CK(zalloc((void**)&c->u64_scratch, N * sizeof(double), s));
         c->h_ir = IRDesc{};
         c->h_ir.u[0] = nullptr;
@@ -1997,7 +1997,7 @@ int mg_level_coarsest_cg(int dim, int n, int dtype, const void* k, void* u, cons
     const int elem = dtype_elem(dtype);
     if (!valid_edge(dim, n) || !elem || !u || !f || iters < 0) return MG_EINVAL;
     if (elem == 2 && k) return MG_ENOTSUP;
-    if (n > tail_max_edge(dim, elem)) return MG_ENOTSUP;
+    if (n > cg_max_edge(dim, elem)) return MG_ENOTSUP;
     hipStream_t s = (hipStream_t)stream;
     GridDesc h{};
     h.u = u;

@@ -41,6 +41,10 @@ inline int max_tile_rows(int dim, int elem, bool var, int family, int wv = 4) {
 
 enum Smoother { SM_RBGS = 0, SM_JACOBI = 1 };
 
+// Operators of the node-based kernels: the Laplacian, nodal coefficients, a
+// constant stencil (GridDesc::sc).
+enum Op { OP_LAP = 0, OP_VAR = 1, OP_STENCIL = 2 };
+
 // Kernel flags for the smoothing sweep.
 enum SweepFlags {
     SWEEP_ZERO_GUESS = 1,  // the incoming iterate is identically zero: read nothing
@@ -72,6 +76,7 @@ struct GridDesc {
     double omega;     // smoother weight
     double* npart;    // SWEEP_NORM: per-workgroup partial sums of r^2 (as many as the launch has
                       // workgroups in x), or null
+    double sc[7];     // OP_STENCIL: centre, -x, +x, -y, +y[, -z, +z] (times c)
 };
 
 // FP64 refinement pass of one grid: u_out = u_in + e (inner nodes),
@@ -170,14 +175,17 @@ hipError_t launch_restrict(int dim, bool var, const GridDesc* d, int ninst, int 
                            hipStream_t s);
 template <typename T>
 hipError_t launch_prolong(int dim, const GridDesc* d, int ninst, int nf, int sel, hipStream_t s);
-// Largest tail edge for a dimension and word size (levels at or below it can
-// run in the single-workgroup tail kernel).
-int tail_max_edge(int dim, int elem);
+// Largest tail edge for a dimension, word size and operator (levels at or
+// below it can run in the single-workgroup tail kernel).
+int tail_max_edge(int dim, int elem, int op);
+// post_first: colour relaxed first in the post-smoothing sweeps (0 red, 1
+// black); kind: 0 V, 1 W, 2 F; zero: start from a zero iterate, else from u.
 template <typename T>
-// post_first: colour relaxed first in the post-smoothing sweeps (0 red, 1 black).
-hipError_t launch_tail(int dim, int sm, bool var, const TailDesc* d, int ninst, int nu1, int nu2, int post_first,
-                       hipStream_t s);
-// Conjugate gradients on a coarsest level of edge n (3 <= n <= tail_max_edge),
+hipError_t launch_tail(int dim, int sm, int op, const TailDesc* d, int ninst, int nu1, int nu2, int post_first,
+                       int kind, bool zero, hipStream_t s);
+// Largest edge of a coarsest level solved by conjugate gradients.
+int cg_max_edge(int dim, int elem);
+// Conjugate gradients on a coarsest level of edge n (3 <= n <= cg_max_edge),
 // 'iters' steps from u = 0, one workgroup per instance.
 template <typename T>
 hipError_t launch_cg(int dim, bool var, const GridDesc* d, int ninst, int n, int iters, hipStream_t s);

@@ -108,6 +108,36 @@ __device__ __forceinline__ T res_lap3(T uC, T uW, T uE, T uS, T uN, T uB, T uT, 
     return f - c * (T(6) * uC - s);
 }
 
+// 2D variable-coefficient residual from the four face coefficients (each
+// kface of the lower and the upper node of its face).
+template <typename T>
+__device__ __forceinline__ T res_var2f(T uC, T uW, T uE, T uS, T uN, T kxW, T kxC, T kyS, T kyC, T f, T c, T& dsum) {
+    dsum = (kxW + kxC) + (kyS + kyC);
+    const T t = (kxW * uW + kxC * uE) + (kyS * uS + kyC * uN);
+    return f - c * (dsum * uC - t);
+}
+
+// Residual of a constant operator: the Laplacian or a constant stencil s.
+template <int OP, typename T>
+__device__ __forceinline__ T res_const2(T uC, T uW, T uE, T uS, T uN, T f, T c, const T* s) {
+    if constexpr (OP == OP_STENCIL) {
+        const T t = (s[1] * uW + s[2] * uE) + (s[3] * uS + s[4] * uN);
+        return f - c * (s[0] * uC + t);
+    } else {
+        return res_lap2(uC, uW, uE, uS, uN, f, c);
+    }
+}
+template <int OP, typename T>
+__device__ __forceinline__ T res_const3(T uC, T uW, T uE, T uS, T uN, T uB, T uT, T f, T c, const T* s) {
+    if constexpr (OP == OP_STENCIL) {
+        T t = (s[1] * uW + s[2] * uE) + (s[3] * uS + s[4] * uN);
+        t = t + (s[5] * uB + s[6] * uT);
+        return f - c * (s[0] * uC + t);
+    } else {
+        return res_lap3(uC, uW, uE, uS, uN, uB, uT, f, c);
+    }
+}
+
 template <typename T>
 __device__ __forceinline__ T res_var2(T uC, T uW, T uE, T uS, T uN, T kC, T kW, T kE, T kS, T kN, T f, T c,
                                       T& dsum) {

@@ -75,6 +75,7 @@ struct Problem {
     bool var;
     bool sym = false;   // symmetric red-black: the post-smoothing sweeps relax black first
     int cycle = 0;      // 0 V, 1 W, 2 F (Algorithm 1 with one / two recursive calls; F: F then V)
+    int op() const { return var ? OP_VAR : OP_LAP; }
     int cg_iters = 0;   // conjugate-gradient steps on a coarsest level with n > 3 (0: 4 (n - 1))
 };
 
@@ -89,7 +90,7 @@ struct TailPlan {
 // First level of a hierarchy (edges n[0] > n[1] > ... > 3) that the tail kernel
 // takes, or -1: the largest level with an edge up to tail_max_edge, not the
 // top level unless its iterate starts at zero.  MG_NO_TAIL disables the tail.
-int tail_first_level(int dim, int elem, const std::vector<int>& n, bool zero_top);
+int tail_first_level(int dim, int elem, int op, const std::vector<int>& n, bool zero_top);
 
 // V-cycle over groups[0..L-1] (groups[l] holds every instance's level l);
 // zero_top: the iterate at level 0 is known to be zero.  Works in precision T.

@@ -100,10 +100,10 @@ struct Prof {
         if (e_ != hipSuccess) return e_;   \
     } while (0)
 
-int tail_first_level(int dim, int elem, const std::vector<int>& n, bool zero_top) {
+int tail_first_level(int dim, int elem, int op, const std::vector<int>& n, bool zero_top) {
     if (std::getenv("MG_NO_TAIL")) return -1;
     if (n.empty() || n.back() != 3) return -1;  // the tail ends in the exact 3-node solve
-    const int tmax = tail_max_edge(dim, elem);
+    const int tmax = tail_max_edge(dim, elem, op);
     for (int l = zero_top ? 0 : 1; l < (int)n.size(); ++l)
         if (n[(size_t)l] <= tmax && (int)n.size() - l <= kMaxTailLevels) return l;
     return -1;
@@ -153,13 +153,18 @@ inline int post_sel(const Problem& P, int cur) { return cur | (P.sym ? SEL_BLACK
 // Algorithm 1 on level l with gamma recursive calls: kind 0 V (one call), 1 W
 // (two), 2 F (an F-cycle then a V-cycle).  The zero guess precedes the first
 // call only; later calls continue from the coarse iterate the previous call
-// left.  Level by level (no coarse tail).
+// left.  Level by level down to the tail's finest level, whose whole recursion
+// is one launch.
 template <typename T>
 hipError_t cycle_rec(const Problem& P, const std::vector<Group>& G, int l, int kind, bool zero,
-                     const std::vector<Tiles>& tiles, hipStream_t s, Prof& prof, bool first_done = false) {
+                     const std::vector<Tiles>& tiles, hipStream_t s, Prof& prof, const TailPlan* tail,
+                     bool first_done = false) {
     const int L = (int)G.size();
     const int dim = P.dim;
     const Group& g = G[(size_t)l];
+    if (tail && l == tail->first && !first_done)
+        return launch_tail<T>(dim, P.smoother, P.op(), tail->d, tail->ninst, P.nu1, P.nu2, P.sym ? 1 : 0, kind, zero,
+                              s);
     if (l == L - 1) return coarse_solve<T>(P, g, s);
     int cur = first_done ? 1 : 0;
     int i0 = first_done ? 1 : 0;
@@ -180,13 +185,13 @@ hipError_t cycle_rec(const Problem& P, const std::vector<Group>& G, int l, int k
     if (P.nu1 == 0 && zero) MG_TRY(launch_zero_u<T>(dim, g.d, g.ninst, g.n, s));
     MG_TRY(launch_restrict<T>(dim, P.var, g.d, g.ninst, g.n, cur, tiles[(size_t)l].restr, s));
     if (kind == 0) {
-        MG_TRY(cycle_rec<T>(P, G, l + 1, 0, true, tiles, s, prof));
+        MG_TRY(cycle_rec<T>(P, G, l + 1, 0, true, tiles, s, prof, tail));
     } else if (kind == 1) {
-        MG_TRY(cycle_rec<T>(P, G, l + 1, 1, true, tiles, s, prof));
-        MG_TRY(cycle_rec<T>(P, G, l + 1, 1, false, tiles, s, prof));
+        MG_TRY(cycle_rec<T>(P, G, l + 1, 1, true, tiles, s, prof, tail));
+        MG_TRY(cycle_rec<T>(P, G, l + 1, 1, false, tiles, s, prof, tail));
     } else {
-        MG_TRY(cycle_rec<T>(P, G, l + 1, 2, true, tiles, s, prof));
-        MG_TRY(cycle_rec<T>(P, G, l + 1, 0, false, tiles, s, prof));
+        MG_TRY(cycle_rec<T>(P, G, l + 1, 2, true, tiles, s, prof, tail));
+        MG_TRY(cycle_rec<T>(P, G, l + 1, 0, false, tiles, s, prof, tail));
     }
     const bool fuse = P.nu2 > 0;
     if (!fuse) MG_TRY(launch_prolong<T>(dim, g.d, g.ninst, g.n, cur, s));
@@ -212,8 +217,9 @@ hipError_t vcycle(const Problem& P, const std::vector<Group>& G, bool zero_top, 
     Prof prof{prof_ev, prof_n, prof_cap, s};
     // a first sweep that already ran needs a level-0 pre-smoothing sweep to have been
     if (first_done && (L < 2 || P.nu1 < 1 || zero_top)) return hipErrorInvalidValue;
-    if (P.cycle != 0) return cycle_rec<T>(P, G, 0, P.cycle, zero_top, tiles, s, prof, first_done);
     const bool use_tail = tail && tail->first >= 0 && tail->first < L && tail->d;
+    if (P.cycle != 0)
+        return cycle_rec<T>(P, G, 0, P.cycle, zero_top, tiles, s, prof, use_tail ? tail : nullptr, first_done);
     // levels [0, stop) run level by level; the rest is the tail (or the coarsest solve)
     const int stop = use_tail ? tail->first : L - 1;
     if (first_done && stop == 0) return hipErrorInvalidValue;
@@ -258,7 +264,8 @@ hipError_t vcycle(const Problem& P, const std::vector<Group>& G, bool zero_top, 
     }
     if (use_tail) {
         // every level from 'stop' to the coarsest in one launch, from a zero guess
-        MG_TRY(launch_tail<T>(dim, P.smoother, P.var, tail->d, tail->ninst, P.nu1, P.nu2, P.sym ? 1 : 0, s));
+        MG_TRY(launch_tail<T>(dim, P.smoother, P.op(), tail->d, tail->ninst, P.nu1, P.nu2, P.sym ? 1 : 0, 0, true,
+                              s));
     } else {
         // coarsest grid from the zero guess
         MG_TRY(coarse_solve<T>(P, G[(size_t)L - 1], s));

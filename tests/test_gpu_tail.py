@@ -1,0 +1,51 @@
+"""The coarse tail at every finest level it takes (edges 3 .. 65 in 2D, 3 .. 17
+in 3D; smaller with FP64 coefficient fields): V-, W- and F-cycles, sweep counts
+down to zero, every smoother and precision.  The tail's arithmetic is the
+oracle's per point, so fields are compared bit for bit."""
+
+import numpy as np
+import pytest
+
+import inputs
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+RB, JAC, SYM = 0, 1, 2
+V, W, F = 0, 1, 2
+
+
+def gpu_solve(dim, n, f, k, precision, **kw):
+    import torch
+
+    import paper_1406_5369_amd as m
+
+    cycles = kw.pop("cycles")
+    dev = lambda a: None if a is None else torch.from_numpy(np.ascontiguousarray(a)).to("cuda")  # noqa: E731
+    u = dev(np.zeros_like(f))
+    with m.Solver(m.Params(dim=dim, n=n, precision=precision, k=dev(k),
+                           op=m.OP_LAPLACE if k is None else m.OP_VARCOEF_NODAL, **kw)) as s:
+        _, cyc, hist = s.solve(u, dev(f), tol=0.0, max_cycles=cycles)
+        torch.cuda.synchronize()
+        return u.cpu().numpy(), cyc, np.array(hist)
+
+
+@pytest.mark.parametrize("dim,n", [(2, 5), (2, 9), (2, 17), (2, 33), (2, 65), (2, 129), (3, 5), (3, 9), (3, 17),
+                                   (3, 33)])
+@pytest.mark.parametrize("precision", [0, 1, 2])
+@pytest.mark.parametrize("smoother,cycle,nu1,nu2", [(RB, V, 2, 2), (SYM, W, 2, 2), (JAC, W, 1, 2), (RB, F, 1, 1),
+                                                    (RB, W, 0, 2), (SYM, F, 3, 0), (JAC, V, 0, 3)])
+@pytest.mark.parametrize("varcoef", [False, True])
+def test_tail_matches_oracle(dim, n, precision, smoother, cycle, nu1, nu2, varcoef):
+    if varcoef and precision == 2:
+        pytest.skip("binary16 is Laplacian only")
+    f = inputs.uniform_rhs(dim, n, 5)
+    k = inputs.varcoef_k(n, 6, dim=dim) if varcoef else None
+    ref = {0: oracle.solve, 1: oracle.solve_ir_f32, 2: oracle.solve_ir_f16}[precision]
+    ue, he, _ = ref(np.zeros_like(f), f, tol=0.0, max_cycles=3, smoother=smoother, omega=0.8 if smoother == JAC else 1.0,
+                    nu1=nu1, nu2=nu2, k=k, cycle=cycle)
+    u, cyc, h = gpu_solve(dim, n, f, k, precision, smoother=smoother, cycle=cycle, nu1=nu1, nu2=nu2, cycles=3)
+    assert cyc == len(he) - 1
+    # two sums of N squares in different orders differ by at most (N - 1) 2^-53 relative each
+    np.testing.assert_allclose(h, he, rtol=max(1e-12, 2.0 * f.size * 2.0**-53))
+    assert np.array_equal(u, ue)
