@@ -58,7 +58,7 @@ enum mg_operator {
                                  level's h (re-discretisation; consistent for a second-order operator,
                                  entries summing to zero, e.g. anisotropic diffusion); smoothing
                                  u + omega h^2 / s0 (f - A u).  MG_PREC_FP64 and coarse_n 0 or 3 only
-                                 (MG_ENOTSUP otherwise); plain one-node-per-thread kernels, level by level */
+                                 (MG_ENOTSUP otherwise) */
     MG_OP_VARCOEF_NODAL = 2   /* -div(k grad u): nodal k, face k = 2 k_p k_q / (k_p + k_q) */
 };
 enum mg_bc {

@@ -163,6 +163,17 @@ hipError_t build_faces(Levels& L, hipStream_t s) {
     return hipSuccess;
 }
 
+// Operator constants of a level of edge n.
+void set_operator(GridDesc& d, const Problem& P, int n) {
+    d.c = level_c(n);
+    d.wd = level_wd(P.dim, n, P.omega);
+    d.omega = P.omega;
+    if (P.stencil) {
+        d.wd = st_const(P.dim, n, P.sc, P.omega).wd;
+        for (int q = 0; q < 7; ++q) d.sc[q] = P.sc[q];
+    }
+}
+
 // One descriptor per level for a single-instance hierarchy.
 hipError_t build_groups(std::vector<Group>& G, const Levels& L, const Problem& P, const int* done, hipStream_t s) {
     G.assign((size_t)L.nlev, Group{});
@@ -181,9 +192,7 @@ hipError_t build_groups(std::vector<Group>& G, const Levels& L, const Problem& P
         d.done = done;
         d.n = g.n;
         d.inst = 0;
-        d.c = level_c(g.n);
-        d.wd = level_wd(P.dim, g.n, P.omega);
-        d.omega = P.omega;
+        set_operator(d, P, g.n);
         g.h.assign(1, d);
         hipError_t e = hipMalloc((void**)&g.d, sizeof(GridDesc));
         if (e != hipSuccess) return e;
@@ -295,11 +304,6 @@ void destroy(mg_ctx* c) {
     ffree(c->cc_work);
     ffree(c->cc_mean);
     delete c->cd;
-    for (size_t l = 0; l < c->stn.size(); ++l) {
-        if (l > 0) ffree(c->stu[l]);
-        ffree(c->stt[l]);
-        if (l > 0) ffree(c->stf[l]);
-    }
     ffree(c->d_ir);
     ffree(c->d_scl);
     ffree(c->d_pmax);
@@ -359,6 +363,7 @@ void prof_end(mg_ctx* c, int step, int kind, hipStream_t s) {
 }
 
 hipError_t enqueue_norm(mg_ctx* c, hipStream_t s, int step = 0) {
+    if (c->st) return st_norm(c->p.dim, c->d_top, c->p.n, c->d_partial, c->d_norm, s);
     const bool var = c->prob.var;
     const int nparts = norm_tiles(c->p.dim, c->p.n, c->top.norm);
     const bool timed = prof_begin(c, step, s);
@@ -376,7 +381,7 @@ hipError_t enqueue_nrm_sweep(mg_ctx* c, hipStream_t s, int step = 0) {
     const TileCfg cfg = c->tl64[0].smooth_nrm;
     const int nparts = smooth_tiles(c->p.dim, c->prob.smoother, c->p.n, cfg);
     const bool timed = prof_begin(c, step, s);
-    hipError_t e = launch_smooth<double>(c->p.dim, c->prob.smoother, c->prob.var, c->G64[0].d, 1, c->p.n, 0,
+    hipError_t e = launch_smooth<double>(c->p.dim, c->prob.smoother, c->prob.op(), c->G64[0].d, 1, c->p.n, 0,
                                          SWEEP_NORM, cfg, s);
     if (timed) prof_end(c, step, 1, s);
     if (e != hipSuccess) return e;
@@ -623,134 +628,6 @@ int cc_solve(mg_ctx* c, double* u, const double* f, double tol, int max_cycles, 
         CK(cc_cycle_top(c, u, c->ccfh));
         CK(cc_remove_mean(dim, n, u, c->cc_work, c->cc_mean, s));
         CK(cc_norm(dim, u, c->ccfh, L0, c->d_partial, c->d_norm, s));
-        CK(launch_stop_test(c->d_norm, c->d_norm0, ctl_done(c), ctl_steps(c), ctl_status(c), c->d_hist, c->hist_cap,
-                            tol, max_cycles, 1, s));
-        CK(hipMemcpyAsync(ctl, c->d_ctrl, 3 * sizeof(int), hipMemcpyDeviceToHost, s));
-        CK(hipStreamSynchronize(s));
-        ++steps;
-    }
-    steps = ctl[1];
-    const int status = ctl[2];
-    if (res_hist) {
-        CK(hipMemcpyAsync(c->h_pin, c->d_hist, sizeof(double) * (size_t)(steps + 1), hipMemcpyDeviceToHost, s));
-        CK(hipStreamSynchronize(s));
-        std::memcpy(res_hist, c->h_pin, sizeof(double) * (size_t)(steps + 1));
-    }
-    if (cycles_done) *cycles_done = steps;
-    if (status == 0) return MG_OK;
-    if (status == -5) return MG_EDIVERGED;
-    return MG_ENOTCONV;
-}
-
-// ---------------------------------------------------------------------------
-// Constant stencil: Algorithm 1 level by level (V, W or F), plain kernels,
-// levels n, (n-1)/2+1, ..., 3; the iterate of level l is in 'cur' (the other
-// buffer of the level is the Jacobi partner).
-// ---------------------------------------------------------------------------
-hipError_t st_smooth_level(mg_ctx* c, double*& cur, double*& other, const double* f, const STConst& L, bool post) {
-    const int dim = c->p.dim;
-    hipStream_t s = c->stream;
-    if (c->p.smoother == MG_SMOOTH_WJACOBI) {
-        hipError_t e = st_relax(dim, true, cur, other, f, L, 0, s);
-        std::swap(cur, other);
-        return e;
-    }
-    const int first = (post && c->p.smoother == MG_SMOOTH_RBGS_SYM) ? 1 : 0;
-    hipError_t e = st_relax(dim, false, cur, cur, f, L, first, s);
-    if (e != hipSuccess) return e;
-    return st_relax(dim, false, cur, cur, f, L, 1 - first, s);
-}
-
-hipError_t st_cycle(mg_ctx* c, int l, int kind, double*& cur, double*& other, const double* f) {
-    const int dim = c->p.dim, n = c->stn[(size_t)l];
-    hipStream_t s = c->stream;
-    const STConst L = st_const(dim, n, c->st_coef, c->p.omega);
-    if (l + 1 == (int)c->stn.size()) return st_coarsest(dim, cur, f, L, s);  // n = 3: one unknown
-    hipError_t e = hipSuccess;
-    for (int i = 0; i < c->p.nu1 && e == hipSuccess; ++i) e = st_smooth_level(c, cur, other, f, L, false);
-    if (e != hipSuccess) return e;
-    double* fc = c->stf[(size_t)l + 1];
-    if ((e = st_restrict(dim, cur, f, fc, L, s)) != hipSuccess) return e;
-    double* ucur = c->stu[(size_t)l + 1];
-    double* uoth = c->stt[(size_t)l + 1];
-    const int nc = c->stn[(size_t)l + 1];
-    if ((e = cc_fill(ucur, npts(dim, nc), 0.0, s)) != hipSuccess) return e;  // zero guess
-    if (kind == MG_CYCLE_V) {
-        e = st_cycle(c, l + 1, MG_CYCLE_V, ucur, uoth, fc);
-    } else if (kind == MG_CYCLE_W) {
-        e = st_cycle(c, l + 1, MG_CYCLE_W, ucur, uoth, fc);
-        if (e == hipSuccess) e = st_cycle(c, l + 1, MG_CYCLE_W, ucur, uoth, fc);
-    } else {
-        e = st_cycle(c, l + 1, MG_CYCLE_F, ucur, uoth, fc);
-        if (e == hipSuccess) e = st_cycle(c, l + 1, MG_CYCLE_V, ucur, uoth, fc);
-    }
-    if (e != hipSuccess) return e;
-    c->stu[(size_t)l + 1] = ucur;
-    c->stt[(size_t)l + 1] = uoth;
-    e = st_prolong(dim, cur, ucur, n, s);
-    for (int i = 0; i < c->p.nu2 && e == hipSuccess; ++i) e = st_smooth_level(c, cur, other, f, L, true);
-    return e;
-}
-
-hipError_t st_cycle_top(mg_ctx* c, double* u, const double* f) {
-    double* cur = u;
-    double* other = c->stt[0];
-    hipError_t e = st_cycle(c, 0, c->p.cycle, cur, other, f);
-    if (e == hipSuccess && cur != u)
-        e = hipMemcpyAsync(u, cur, npts(c->p.dim, c->p.n) * sizeof(double), hipMemcpyDeviceToDevice, c->stream);
-    return e;
-}
-
-int st_setup(mg_ctx* c) {
-    const int dim = c->p.dim;
-    hipStream_t s = c->stream;
-    c->st = true;
-    for (int q = 0; q < 2 * dim + 1; ++q) c->st_coef[q] = c->p.stencil[q];
-    c->p.stencil = nullptr;  // the context keeps its own copy
-    for (int m = c->p.n; m >= 3; m = (m - 1) / 2 + 1) {
-        c->stn.push_back(m);
-        if (m == 3) break;
-    }
-    const size_t L = c->stn.size();
-    c->stu.assign(L, nullptr);
-    c->stt.assign(L, nullptr);
-    c->stf.assign(L, nullptr);
-    for (size_t l = 0; l < L; ++l) {
-        const size_t bytes = npts(dim, c->stn[l]) * sizeof(double);
-        if (l > 0) CK(zalloc((void**)&c->stu[l], bytes, s));
-        CK(zalloc((void**)&c->stt[l], bytes, s));
-        if (l > 0) CK(zalloc((void**)&c->stf[l], bytes, s));
-    }
-    c->nlev = (int)L;
-    c->pstride = st_norm_parts(dim, c->p.n);
-    CK(hipMalloc((void**)&c->d_partial, sizeof(double) * (size_t)c->pstride));
-    CK(hipMalloc((void**)&c->d_norm, sizeof(double)));
-    CK(hipMalloc((void**)&c->d_norm0, sizeof(double)));
-    CK(hipMalloc((void**)&c->d_ctrl, 3 * sizeof(int)));
-    CK(launch_fill_int(c->d_ctrl, 0, 3, s));
-    int r = ensure_hist(c, 64);
-    if (r != MG_OK) return r;
-    CK(hipStreamSynchronize(s));
-    return MG_OK;
-}
-
-int st_solve(mg_ctx* c, double* u, const double* f, double tol, int max_cycles, int* cycles_done, double* res_hist) {
-    const int dim = c->p.dim, n = c->p.n;
-    hipStream_t s = c->stream;
-    const STConst L0 = st_const(dim, n, c->st_coef, c->p.omega);
-    int r = ensure_hist(c, max_cycles + 1);
-    if (r != MG_OK) return r;
-    CK(launch_fill_int(ctl_done(c), 0, 1, s));
-    CK(st_norm(dim, u, f, L0, c->d_partial, c->d_norm, s));
-    CK(launch_solve_init(c->d_norm, c->d_norm0, ctl_done(c), ctl_steps(c), ctl_status(c), c->d_hist, c->hist_cap, 1,
-                         s));
-    int* ctl = (int*)c->h_pin;
-    CK(hipMemcpyAsync(ctl, c->d_ctrl, 3 * sizeof(int), hipMemcpyDeviceToHost, s));
-    CK(hipStreamSynchronize(s));
-    int steps = 0;
-    while (!ctl[0] && steps < max_cycles) {
-        CK(st_cycle_top(c, u, f));
-        CK(st_norm(dim, u, f, L0, c->d_partial, c->d_norm, s));
         CK(launch_stop_test(c->d_norm, c->d_norm0, ctl_done(c), ctl_steps(c), ctl_status(c), c->d_hist, c->hist_cap,
                             tol, max_cycles, 1, s));
         CK(hipMemcpyAsync(ctl, c->d_ctrl, 3 * sizeof(int), hipMemcpyDeviceToHost, s));
@@ -1380,16 +1257,6 @@ int mg_setup(const mg_params* p, void* stream, mg_ctx** out) {
     c->p = *p;
     if (c->p.omega <= 0.0) c->p.omega = p->smoother == MG_SMOOTH_WJACOBI ? 0.8 : 1.0;
     c->stream = (hipStream_t)stream;
-    if (p->op == MG_OP_CONST_STENCIL) {
-        (void)hipGetDevice(&c->device);
-        const int r = st_setup(c);
-        if (r != MG_OK) {
-            destroy(c);
-            return r;
-        }
-        *out = c;
-        return MG_OK;
-    }
     if (p->bc == MG_BC_NEUMANN_CC) {
         (void)hipGetDevice(&c->device);
         const int r = cc_setup(c);
@@ -1405,6 +1272,11 @@ int mg_setup(const mg_params* p, void* stream, mg_ctx** out) {
     const int dim = p->dim;
     c->prob = Problem{dim, p->smoother == MG_SMOOTH_WJACOBI ? SM_JACOBI : SM_RBGS, p->nu1, p->nu2, c->p.omega,
                       p->op == MG_OP_VARCOEF_NODAL};
+    if (p->op == MG_OP_CONST_STENCIL) {
+        c->st = c->prob.stencil = true;
+        for (int q = 0; q < 2 * dim + 1; ++q) c->prob.sc[q] = p->stencil[q];
+        c->p.stencil = nullptr;  // the context keeps its own copy
+    }
     c->prob.sym = p->smoother == MG_SMOOTH_RBGS_SYM;
     c->prob.cycle = p->cycle;
     c->prob.cg_iters = p->cg_iters;
@@ -1425,7 +1297,9 @@ int mg_setup(const mg_params* p, void* stream, mg_ctx** out) {
         else c->top.norm.by = std::min(c->top.norm.by, 4 * c->top.norm.wv);
     }
     const char* at = std::getenv("MG_AUTOTUNE");
-    c->autotune = !(at && at[0] == '0');
+    // a constant stencil keeps the heuristic geometry: tuning its levels takes 40 .. 1000 ms at setup (against
+    // 1 ms) and gains 5 % of a solve at 129^3 and 257^3, 19 % at 4097^2
+    c->autotune = !(at && at[0] == '0') && !c->st;
     hipStream_t s = c->stream;
     const size_t N = npts(dim, p->n);
     hipError_t e = hipSuccess;
@@ -1490,9 +1364,7 @@ int mg_setup(const mg_params* p, void* stream, mg_ctx** out) {
     c->h_top.k = c->k64;
     c->h_top.n = p->n;
     c->h_top.inst = 0;
-    c->h_top.c = level_c(p->n);
-    c->h_top.wd = level_wd(dim, p->n, c->p.omega);
-    c->h_top.omega = c->p.omega;
+    set_operator(c->h_top, c->prob, p->n);
     SETUP_CK(hipMalloc((void**)&c->d_top, sizeof(GridDesc)));
     SETUP_CK(hipMemcpyAsync(c->d_top, &c->h_top, sizeof(GridDesc), hipMemcpyHostToDevice, s));
     // FP64: each cycle's residual norm from the next cycle's first pre-smoothing sweep
@@ -1512,7 +1384,7 @@ int mg_setup(const mg_params* p, void* stream, mg_ctx** out) {
     if (c->autotune) SETUP_CK(autotune(c));
     if (c->nrm_fused && smooth_tiles(dim, c->prob.smoother, p->n, c->tl64[0].smooth_nrm) > c->spart_cap)
         c->nrm_fused = false;
-    c->pstride = std::max(1, norm_tiles(dim, p->n, c->top.norm));
+    c->pstride = c->st ? st_norm_parts(dim, p->n) : std::max(1, norm_tiles(dim, p->n, c->top.norm));
     SETUP_CK(hipMalloc((void**)&c->d_partial, sizeof(double) * (size_t)c->pstride));
     if (is_h16(c->p)) {
         SETUP_CK(hipMalloc((void**)&c->d_pmax, sizeof(double) * (size_t)c->pstride));
@@ -1521,7 +1393,7 @@ int mg_setup(const mg_params* p, void* stream, mg_ctx** out) {
     }
     SETUP_CK(hipMalloc((void**)&c->d_norm, sizeof(double)));
     SETUP_CK(hipMalloc((void**)&c->d_norm0, sizeof(double)));
-    c->prof_ev.resize(512);
+    if (!c->st) c->prof_ev.resize(512);
     for (auto& ev : c->prof_ev) SETUP_CK(hipEventCreate(&ev));
     int r = ensure_hist(c, 64);
     if (r != MG_OK) {
@@ -1548,7 +1420,7 @@ int mg_tile_config(const mg_ctx* c, int level, int family, int* by, int* zchunk,
                    int* order, int* pairs) {
     if (!c || is_batch_handle(c) || !by || !zchunk || level < 0 || level >= c->nlev || family < 0 || family > 8)
         return MG_EINVAL;
-    if (c->cc || c->st || c->cd) return MG_ENOTSUP;  // plain kernels, no tiles
+    if (c->cc || c->st || c->cd) return MG_ENOTSUP;  // no tuned tiles
     const std::vector<Tiles>& tl = c->p.precision == MG_PREC_FP64 ? c->tl64 : c->tl32;
     const Tiles& tv = tl[(size_t)level];
     const TileCfg t = family == 0   ? tv.smooth
@@ -1587,11 +1459,6 @@ int mg_vcycle(mg_ctx* c, double* u, const double* f) {
         CK(cc_cycle_top(c, u, f));
         return MG_OK;
     }
-    if (c->st) {
-        if (!u || !f) return MG_EINVAL;
-        CK(st_cycle_top(c, u, f));
-        return MG_OK;
-    }
     int r = bind(c, u, f);
     if (r != MG_OK) return r;
     CK(launch_fill_int(ctl_done(c), 0, 1, c->stream));
@@ -1620,15 +1487,6 @@ int mg_residual_norm(mg_ctx* c, const double* u, const double* f, double* out) {
         *out = c->h_pin[0];
         return MG_OK;
     }
-    if (c->st) {
-        if (!u || !f) return MG_EINVAL;
-        CK(st_norm(c->p.dim, u, f, st_const(c->p.dim, c->p.n, c->st_coef, c->p.omega), c->d_partial, c->d_norm,
-                   c->stream));
-        CK(hipMemcpyAsync(c->h_pin, c->d_norm, sizeof(double), hipMemcpyDeviceToHost, c->stream));
-        CK(hipStreamSynchronize(c->stream));
-        *out = c->h_pin[0];
-        return MG_OK;
-    }
     int r = bind(c, u, f);
     if (r != MG_OK) return r;
     CK(enqueue_norm(c, c->stream));
@@ -1645,10 +1503,6 @@ int mg_solve(mg_ctx* c, double* u, const double* f, double tol, int max_cycles, 
     if (c->cc) {
         if (!u || !f) return MG_EINVAL;
         return cc_solve(c, u, f, tol, max_cycles, cycles_done, res_hist);
-    }
-    if (c->st) {
-        if (!u || !f) return MG_EINVAL;
-        return st_solve(c, u, f, tol, max_cycles, cycles_done, res_hist);
     }
     int r = bind(c, u, f);
     if (r != MG_OK) return r;
@@ -1728,7 +1582,7 @@ int mg_solve(mg_ctx* c, double* u, const double* f, double tol, int max_cycles, 
 int mg_prof_enable(mg_ctx* c, int on) {
     if (!c) return MG_EINVAL;
     if (is_batch_handle(c)) return MG_EINVAL;
-    c->prof_on = on != 0;
+    c->prof_on = on != 0 && !c->st;
     c->prof_n = 0;
     c->prof_step.clear();
     c->prof_kind.clear();

@@ -136,14 +136,14 @@ int norm_tiles(int dim, int n, TileCfg cfg);
 // Kernel launchers.  'ninst' grids with equal n are processed by one launch
 // (blockIdx.y selects the descriptor).  'T' is double or float.
 template <typename T>
-hipError_t launch_smooth(int dim, int sm, bool var, const GridDesc* d, int ninst, int n, int sel, int flags,
+hipError_t launch_smooth(int dim, int sm, int op, const GridDesc* d, int ninst, int n, int sel, int flags,
                          TileCfg cfg, hipStream_t s);
 // Per-dimension sweep launchers behind launch_smooth (grid already sized).
 template <typename T>
-hipError_t launch_smooth2d(int sm, bool var, const GridDesc* d, int sel, int flags, TileCfg cfg, dim3 grid,
+hipError_t launch_smooth2d(int sm, int op, const GridDesc* d, int sel, int flags, TileCfg cfg, dim3 grid,
                            hipStream_t s);
 template <typename T>
-hipError_t launch_smooth3d(int sm, bool var, const GridDesc* d, int sel, int flags, TileCfg cfg, dim3 grid,
+hipError_t launch_smooth3d(int sm, int op, const GridDesc* d, int sel, int flags, TileCfg cfg, dim3 grid,
                            hipStream_t s);
 // 3D Laplacian, FP32 or binary16 storage: the first two red-first RBGS
 // pre-smoothing sweeps from a zero iterate in one launch, the second sweep's
@@ -171,7 +171,7 @@ int smooth2d_pro2_tiles(int n, int ychunk);
 template <typename T>
 hipError_t launch_smooth_restrict3d(const GridDesc* d, int ninst, int nf, int sel, TileCfg cfg, hipStream_t s);
 template <typename T>
-hipError_t launch_restrict(int dim, bool var, const GridDesc* d, int ninst, int nf, int sel, TileCfg cfg,
+hipError_t launch_restrict(int dim, int op, const GridDesc* d, int ninst, int nf, int sel, TileCfg cfg,
                            hipStream_t s);
 template <typename T>
 hipError_t launch_prolong(int dim, const GridDesc* d, int ninst, int nf, int sel, hipStream_t s);
@@ -190,7 +190,7 @@ int cg_max_edge(int dim, int elem);
 template <typename T>
 hipError_t launch_cg(int dim, bool var, const GridDesc* d, int ninst, int n, int iters, hipStream_t s);
 template <typename T>
-hipError_t launch_coarsest(int dim, bool var, const GridDesc* d, int ninst, hipStream_t s);
+hipError_t launch_coarsest(int dim, int op, const GridDesc* d, int ninst, hipStream_t s);
 template <typename T>
 hipError_t launch_copy_t_to_u(int dim, const GridDesc* d, int ninst, int n, hipStream_t s);
 template <typename T>

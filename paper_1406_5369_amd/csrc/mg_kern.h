@@ -166,29 +166,31 @@ __device__ __forceinline__ T res_var3(T uC, T uW, T uE, T uS, T uN, T uB, T uT, 
 }
 
 // 2D stencil evaluation on an LDS box A (and coefficient box K), centre (ly, lx).
-template <typename T, bool VAR>
-__device__ __forceinline__ T lds_res2(const T (*A)[BX], const T (*K)[BX], int ly, int lx, T f, T c, T& dsum) {
-    if constexpr (VAR) {
+template <typename T, int OP>
+__device__ __forceinline__ T lds_res2(const T (*A)[BX], const T (*K)[BX], int ly, int lx, T f, T c, T& dsum,
+                                      const T* s = nullptr) {
+    if constexpr (OP == OP_VAR) {
         return res_var2(A[ly][lx], A[ly][lx - 1], A[ly][lx + 1], A[ly - 1][lx], A[ly + 1][lx], K[ly][lx],
                         K[ly][lx - 1], K[ly][lx + 1], K[ly - 1][lx], K[ly + 1][lx], f, c, dsum);
     } else {
         dsum = T(0);
-        return res_lap2(A[ly][lx], A[ly][lx - 1], A[ly][lx + 1], A[ly - 1][lx], A[ly + 1][lx], f, c);
+        return res_const2<OP>(A[ly][lx], A[ly][lx - 1], A[ly][lx + 1], A[ly - 1][lx], A[ly + 1][lx], f, c, s);
     }
 }
 
 // 3D: planes Ab (below, z-1), Ac (centre), Aa (above, z+1).
-template <typename T, bool VAR>
+template <typename T, int OP>
 __device__ __forceinline__ T lds_res3(const T (*Ab)[BX], const T (*Ac)[BX], const T (*Aa)[BX], const T (*Kb)[BX],
-                                      const T (*Kc)[BX], const T (*Ka)[BX], int ly, int lx, T f, T c, T& dsum) {
-    if constexpr (VAR) {
+                                      const T (*Kc)[BX], const T (*Ka)[BX], int ly, int lx, T f, T c, T& dsum,
+                                      const T* s = nullptr) {
+    if constexpr (OP == OP_VAR) {
         return res_var3(Ac[ly][lx], Ac[ly][lx - 1], Ac[ly][lx + 1], Ac[ly - 1][lx], Ac[ly + 1][lx], Ab[ly][lx],
                         Aa[ly][lx], Kc[ly][lx], Kc[ly][lx - 1], Kc[ly][lx + 1], Kc[ly - 1][lx], Kc[ly + 1][lx],
                         Kb[ly][lx], Ka[ly][lx], f, c, dsum);
     } else {
         dsum = T(0);
-        return res_lap3(Ac[ly][lx], Ac[ly][lx - 1], Ac[ly][lx + 1], Ac[ly - 1][lx], Ac[ly + 1][lx], Ab[ly][lx],
-                        Aa[ly][lx], f, c);
+        return res_const3<OP>(Ac[ly][lx], Ac[ly][lx - 1], Ac[ly][lx + 1], Ac[ly - 1][lx], Ac[ly + 1][lx], Ab[ly][lx],
+                              Aa[ly][lx], f, c, s);
     }
 }
 
@@ -286,15 +288,22 @@ __device__ __forceinline__ double lane_next(double v) {
 }
 
 // 3D residual from explicit neighbour values.
-template <typename T, bool VAR>
+template <typename T, int OP>
 __device__ __forceinline__ T res3(T uC, T uW, T uE, T uS, T uN, T uB, T uT, T kC, T kW, T kE, T kS, T kN, T kB, T kT,
-                                  T f, T c, T& dsum) {
-    if constexpr (VAR) {
+                                  T f, T c, T& dsum, const T* s = nullptr) {
+    if constexpr (OP == OP_VAR) {
         return res_var3(uC, uW, uE, uS, uN, uB, uT, kC, kW, kE, kS, kN, kB, kT, f, c, dsum);
     } else {
         dsum = T(0);
-        return res_lap3(uC, uW, uE, uS, uN, uB, uT, f, c);
+        return res_const3<OP>(uC, uW, uE, uS, uN, uB, uT, f, c, s);
     }
+}
+
+// Coefficients of a constant stencil (nothing else reads them).
+template <int OP, typename T>
+__device__ __forceinline__ void load_stencil(const GridDesc& d, T (&s)[7]) {
+#pragma unroll
+    for (int q = 0; q < 7; ++q) s[q] = OP == OP_STENCIL ? (T)d.sc[q] : T(0);
 }
 
 inline int cdiv(int a, int b) { return (a + b - 1) / b; }

@@ -44,7 +44,7 @@ __global__ __launch_bounds__(NT) void k_norm2d(const GridDesc* __restrict__ desc
         const int ly = w + 4 * m, gy = y0 - 1 + ly;
         if (lane >= 1 && lane <= BX - 2 && ly >= 1 && ly <= BY - 2 && gx <= n - 2 && gy <= n - 2) {
             double ds;
-            const double r = lds_res2<double, VAR>(U, K, ly, lane, fr[m], c, ds);
+            const double r = lds_res2<double, VAR ? OP_VAR : OP_LAP>(U, K, ly, lane, fr[m], c, ds);
             acc += r * r;
         }
     }
@@ -184,7 +184,7 @@ struct Resid3D {
                         kN = K[S1][ly + 1][lane];
                     }
                     double ds;
-                    const double r = res3<double, VAR>(uc, uw, ue, U[S1][ly - 1][lane], U[S1][ly + 1][lane],
+                    const double r = res3<double, VAR ? OP_VAR : OP_LAP>(uc, uw, ue, U[S1][ly - 1][lane], U[S1][ly + 1][lane],
                                                        uo[S2][m], uo[S0][m], kc, kw, ke, kS, kN, kb, ka, fr[S1][m],
                                                        c, ds);
                     if constexpr (IR) st_off(r32 + (size_t)zz * pl + rowoff(m), xb4, (float)r);
@@ -872,7 +872,7 @@ __global__ __launch_bounds__(NT) void k_ir2d(const IRDesc* __restrict__ descs, i
         if (lane >= 1 && lane <= BX - 2 && ly >= 1 && ly <= BY - 2 && gx <= n - 2 && gy <= n - 2) {
             const size_t p = (size_t)gy * n + gx;
             double ds;
-            const double r = lds_res2<double, VAR>(U, K, ly, lane, fr[m], c, ds);
+            const double r = lds_res2<double, VAR ? OP_VAR : OP_LAP>(U, K, ly, lane, fr[m], c, ds);
             if (!(flags & IR_NO_UPDATE)) uout[p] = U[ly][lane];
             r32[p] = (float)r;
             acc += r * r;

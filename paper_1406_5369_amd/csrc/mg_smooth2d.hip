@@ -8,8 +8,9 @@ namespace {
 // 2D smoothing sweep (one LDS tile per workgroup, no marching)
 // ---------------------------------------------------------------------------
 
-template <typename ST, int SM, bool VAR, int BY, int FL>
+template <typename ST, int SM, int OP, int BY, int FL>
 __global__ __launch_bounds__(NT) void k_smooth2d(const GridDesc* __restrict__ descs, int sel) {
+    constexpr bool VAR = OP == OP_VAR;
     using T = arith_t<ST>;  // arithmetic type; ST is the storage type of u, f and the coarse correction
     static_assert(!VAR || sizeof(ST) == sizeof(T), "coefficient fields are stored in the arithmetic type");
     constexpr int flags = FL;
@@ -31,6 +32,8 @@ __global__ __launch_bounds__(NT) void k_smooth2d(const GridDesc* __restrict__ de
     const MG_GLOBAL ST* __restrict__ ec = gp((const ST*)d.uc);
     const int nc = (n - 1) / 2 + 1;
     const T c = (T)d.c, wd = (T)d.wd, om = (T)d.omega;
+    T sc[7];
+    load_stencil<OP>(d, sc);
 
     __shared__ T U[BY][BX];
     __shared__ T R[SM == SM_RBGS ? BY : 1][BX];
@@ -96,7 +99,7 @@ __global__ __launch_bounds__(NT) void k_smooth2d(const GridDesc* __restrict__ de
                     // residual of both colours on the incoming values; summed over the output nodes
                     if (inn) {
                         T ds;
-                        const T r = lds_res2<T, VAR>(U, K, ly, lane, fr[m], c, ds);
+                        const T r = lds_res2<T, OP>(U, K, ly, lane, fr[m], c, ds, sc);
                         if (((gx + gy) & 1) == cfirst) v = stored<ST>(relax<T, VAR>(v, r, ds, c, wd, om));
                         if (lane >= 2 && lane <= BX - 3 && ly >= 2 && ly <= BY - 3 && gx <= n - 2 && gy <= n - 2)
                             nacc += r * r;
@@ -104,7 +107,7 @@ __global__ __launch_bounds__(NT) void k_smooth2d(const GridDesc* __restrict__ de
                 } else {
                     if (inn && ((gx + gy) & 1) == cfirst) {
                         T ds;
-                        const T r = lds_res2<T, VAR>(U, K, ly, lane, fr[m], c, ds);
+                        const T r = lds_res2<T, OP>(U, K, ly, lane, fr[m], c, ds, sc);
                         v = stored<ST>(relax<T, VAR>(v, r, ds, c, wd, om));
                     }
                 }
@@ -120,7 +123,7 @@ __global__ __launch_bounds__(NT) void k_smooth2d(const GridDesc* __restrict__ de
                 T v = R[ly][lane];
                 if (((gx + gy) & 1) != cfirst) {
                     T ds;
-                    const T r = lds_res2<T, VAR>(R, K, ly, lane, fr[m], c, ds);
+                    const T r = lds_res2<T, OP>(R, K, ly, lane, fr[m], c, ds, sc);
                     v = relax<T, VAR>(v, r, ds, c, wd, om);
                 }
                 uout[(size_t)gy * n + gx] = (ST)v;
@@ -132,7 +135,7 @@ __global__ __launch_bounds__(NT) void k_smooth2d(const GridDesc* __restrict__ de
             const int ly = w + 4 * m, gy = y0 - H + ly;
             if (lane1 && ly >= 1 && ly <= BY - 2 && gx <= n - 2 && gy <= n - 2) {
                 T ds;
-                const T r = lds_res2<T, VAR>(U, K, ly, lane, fr[m], c, ds);
+                const T r = lds_res2<T, OP>(U, K, ly, lane, fr[m], c, ds, sc);
                 if constexpr (NRM) nacc += r * r;
                 uout[(size_t)gy * n + gx] = (ST)relax<T, VAR>(U[ly][lane], r, ds, c, wd, om);
             }
@@ -487,40 +490,45 @@ template hipError_t launch_smooth2d_zg2<double>(const GridDesc*, int, int, int, 
 template hipError_t launch_smooth2d_zg2<float>(const GridDesc*, int, int, int, TileCfg, hipStream_t);
 template hipError_t launch_smooth2d_zg2<half_t>(const GridDesc*, int, int, int, TileCfg, hipStream_t);
 
-template <typename T, int SMV, bool VARV, int FL>
+template <typename T, int SMV, int OPV, int FL>
 hipError_t launch_smooth2d_fl(const GridDesc* d, int sel, TileCfg cfg, dim3 grid, hipStream_t s) {
-    MG_BY_SWITCH(cfg.by, (k_smooth2d<T, SMV, VARV, BY, FL><<<grid, NT, 0, s>>>(d, sweep_arg(sel, cfg))))
+    MG_BY_SWITCH(cfg.by, (k_smooth2d<T, SMV, OPV, BY, FL><<<grid, NT, 0, s>>>(d, sweep_arg(sel, cfg))))
     return hipSuccess;
 }
 
 template <typename T>
-hipError_t launch_smooth2d(int sm, bool var, const GridDesc* d, int sel, int flags, TileCfg cfg, dim3 grid,
+hipError_t launch_smooth2d(int sm, int op, const GridDesc* d, int sel, int flags, TileCfg cfg, dim3 grid,
                            hipStream_t s) {
-#define MG_FL(SMV, VARV)                                                                                   \
+#define MG_FL(SMV, OPV)                                                                                   \
     switch (flags) {                                                                                       \
-        case 0: return launch_smooth2d_fl<T, SMV, VARV, 0>(d, sel, cfg, grid, s);                           \
-        case SWEEP_ZERO_GUESS: return launch_smooth2d_fl<T, SMV, VARV, SWEEP_ZERO_GUESS>(d, sel, cfg, grid, s); \
-        case SWEEP_PROLONG: return launch_smooth2d_fl<T, SMV, VARV, SWEEP_PROLONG>(d, sel, cfg, grid, s);   \
+        case 0: return launch_smooth2d_fl<T, SMV, OPV, 0>(d, sel, cfg, grid, s);                           \
+        case SWEEP_ZERO_GUESS: return launch_smooth2d_fl<T, SMV, OPV, SWEEP_ZERO_GUESS>(d, sel, cfg, grid, s); \
+        case SWEEP_PROLONG: return launch_smooth2d_fl<T, SMV, OPV, SWEEP_PROLONG>(d, sel, cfg, grid, s);   \
         case SWEEP_NORM:                                                                                   \
-            if constexpr (sizeof(T) == 8) return launch_smooth2d_fl<T, SMV, VARV, SWEEP_NORM>(d, sel, cfg, grid, s); \
+            if constexpr (sizeof(T) == 8) return launch_smooth2d_fl<T, SMV, OPV, SWEEP_NORM>(d, sel, cfg, grid, s); \
             return hipErrorInvalidValue;                                                                   \
         default: return hipErrorInvalidValue;                                                              \
     }
-    if constexpr (sizeof(T) == 2) {  // binary16 storage: Laplacian only
-        if (var) return hipErrorInvalidValue;
-        if (sm == SM_RBGS) MG_FL(SM_RBGS, false) else MG_FL(SM_JACOBI, false)
-    } else {
-        if (sm == SM_RBGS) {
-            if (var) MG_FL(SM_RBGS, true) else MG_FL(SM_RBGS, false)
-        } else {
-            if (var) MG_FL(SM_JACOBI, true) else MG_FL(SM_JACOBI, false)
+    // binary16 storage: Laplacian only; a constant stencil: FP64 only
+    if (op == OP_LAP) {
+        if (sm == SM_RBGS) MG_FL(SM_RBGS, OP_LAP) else MG_FL(SM_JACOBI, OP_LAP)
+    }
+    if constexpr (sizeof(T) >= 4) {
+        if (op == OP_VAR) {
+            if (sm == SM_RBGS) MG_FL(SM_RBGS, OP_VAR) else MG_FL(SM_JACOBI, OP_VAR)
         }
     }
+    if constexpr (sizeof(T) == 8) {
+        if (op == OP_STENCIL) {
+            if (sm == SM_RBGS) MG_FL(SM_RBGS, OP_STENCIL) else MG_FL(SM_JACOBI, OP_STENCIL)
+        }
+    }
+    return hipErrorInvalidValue;
 #undef MG_FL
 }
 
-template hipError_t launch_smooth2d<double>(int, bool, const GridDesc*, int, int, TileCfg, dim3, hipStream_t);
-template hipError_t launch_smooth2d<float>(int, bool, const GridDesc*, int, int, TileCfg, dim3, hipStream_t);
-template hipError_t launch_smooth2d<half_t>(int, bool, const GridDesc*, int, int, TileCfg, dim3, hipStream_t);
+template hipError_t launch_smooth2d<double>(int, int, const GridDesc*, int, int, TileCfg, dim3, hipStream_t);
+template hipError_t launch_smooth2d<float>(int, int, const GridDesc*, int, int, TileCfg, dim3, hipStream_t);
+template hipError_t launch_smooth2d<half_t>(int, int, const GridDesc*, int, int, TileCfg, dim3, hipStream_t);
 
 }  // namespace mg

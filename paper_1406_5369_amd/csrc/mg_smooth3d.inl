@@ -37,8 +37,9 @@ namespace {
 // its x-then-y partial sum; the odd-x partner value comes from the next lane.
 // ---------------------------------------------------------------------------
 
-template <typename ST, int SM, bool VAR, int BY, int PD, int FL, int WV>
+template <typename ST, int SM, int OP, int BY, int PD, int FL, int WV>
 struct Smooth3D {
+    static constexpr bool VAR = OP == OP_VAR;
     using T = arith_t<ST>;  // arithmetic type; ST is the storage type of u, f and the coarse correction
     static_assert(!VAR || sizeof(ST) == sizeof(T), "coefficient fields are stored in the arithmetic type");
     static constexpr int flags = FL;
@@ -59,6 +60,7 @@ struct Smooth3D {
     const MG_GLOBAL T* __restrict__ fxa;  // face coefficients: +x at fxa, +y at fxa + n^3, +z at fxa + 2 n^3
     int n, x0, y0, z0, z1, kstart, kend;
     T c, wd, om;
+    T sc[7];  // constant stencil
     int lane, w, gx;
     int cfirst;  // colour relaxed in the first half-sweep (0 red, 1 black)
     bool colg, coli, lane1;
@@ -224,7 +226,7 @@ struct Smooth3D {
                              fzc[QC][m], fv, c, ds);
         } else {
             ds = T(0);
-            return res_lap3(uc, uw, ue, uS, uN, ub, ua, fv, c);
+            return res_const3<OP>(uc, uw, ue, uS, uN, ub, ua, fv, c, sc);
         }
     }
     template <int QC, int QB>
@@ -373,11 +375,12 @@ struct Smooth3D {
     }
 };
 
-template <typename ST, int SM, bool VAR, int BY, int PD, int FL, int WV>
+template <typename ST, int SM, int OP, int BY, int PD, int FL, int WV>
 __global__ __launch_bounds__(64 * WV) void k_smooth3d(const GridDesc* __restrict__ descs, int sel, int zchunk) {
     const GridDesc d = descs[blockIdx.y];
     if (d.done && *gp(d.done)) return;
-    using S = Smooth3D<ST, SM, VAR, BY, PD, FL, WV>;
+    constexpr bool VAR = OP == OP_VAR;
+    using S = Smooth3D<ST, SM, OP, BY, PD, FL, WV>;
     using T = arith_t<ST>;
     __shared__ T U[3][BY][BX];
     __shared__ T R[SM == SM_RBGS ? 3 : 1][BY][BX];
@@ -406,6 +409,7 @@ __global__ __launch_bounds__(64 * WV) void k_smooth3d(const GridDesc* __restrict
     s.c = (T)d.c;
     s.wd = (T)d.wd;
     s.om = (T)d.omega;
+    load_stencil<OP>(d, s.sc);
     s.lane = threadIdx.x & 63;
     s.w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     s.cfirst = (sel & SEL_BLACK_FIRST) ? 1 : 0;
@@ -425,27 +429,28 @@ __global__ __launch_bounds__(64 * WV) void k_smooth3d(const GridDesc* __restrict
 
 }  // namespace
 
-template <typename T, int SMV, bool VARV, int FL, int BY, int WV>
+template <typename T, int SMV, int OPV, int FL, int BY, int WV>
 hipError_t launch_smooth3d_g(const GridDesc* d, int sel, TileCfg cfg, dim3 grid, hipStream_t s) {
     const int arg = sweep_arg(sel, cfg);
-    if (cfg.pd == 2) k_smooth3d<T, SMV, VARV, BY, 2, FL, WV><<<grid, 64 * WV, 0, s>>>(d, arg, cfg.zchunk);
-    else k_smooth3d<T, SMV, VARV, BY, 1, FL, WV><<<grid, 64 * WV, 0, s>>>(d, arg, cfg.zchunk);
+    if (cfg.pd == 2) k_smooth3d<T, SMV, OPV, BY, 2, FL, WV><<<grid, 64 * WV, 0, s>>>(d, arg, cfg.zchunk);
+    else k_smooth3d<T, SMV, OPV, BY, 1, FL, WV><<<grid, 64 * WV, 0, s>>>(d, arg, cfg.zchunk);
     return hipSuccess;
 }
 
-template <typename T, int SMV, bool VARV, int FL, int BY>
+template <typename T, int SMV, int OPV, int FL, int BY>
 hipError_t launch_smooth3d_rc(const GridDesc* d, int sel, TileCfg cfg, dim3 grid, hipStream_t s) {
     const int arg = sweep_arg(sel, cfg);
-    if (cfg.pd == 2) k_smooth3d_rc<T, SMV, VARV, BY, 2, FL><<<grid, 64, 0, s>>>(d, arg, cfg.zchunk);
-    else k_smooth3d_rc<T, SMV, VARV, BY, 1, FL><<<grid, 64, 0, s>>>(d, arg, cfg.zchunk);
+    if (cfg.pd == 2) k_smooth3d_rc<T, SMV, OPV, BY, 2, FL><<<grid, 64, 0, s>>>(d, arg, cfg.zchunk);
+    else k_smooth3d_rc<T, SMV, OPV, BY, 1, FL><<<grid, 64, 0, s>>>(d, arg, cfg.zchunk);
     return hipSuccess;
 }
 
 // Tile geometries (rows x wavefronts): 8x4, 16x4, 32x4 (FP32 Laplacian only:
 // eight rows per thread), 16x8 and 32x8; 8x1 and 12x1 in registers.
 
-template <typename T, int SMV, bool VARV, int FL>
+template <typename T, int SMV, int OPV, int FL>
 hipError_t launch_smooth3d_fl(const GridDesc* d, int sel, TileCfg cfg, dim3 grid, hipStream_t s) {
+    constexpr bool VARV = OPV == OP_VAR;
     constexpr bool wide = sizeof(arith_t<T>) == 4 && !VARV;
     constexpr bool fp64var = sizeof(arith_t<T>) == 8 && VARV;  // two rows per thread at most
     if (cfg.wv == 1) {  // one wavefront per tile, rows in registers: 8 rows, or 12 in FP32 without coefficients
@@ -453,9 +458,9 @@ hipError_t launch_smooth3d_fl(const GridDesc* d, int sel, TileCfg cfg, dim3 grid
             return hipErrorInvalidValue;
         } else {
             switch (cfg.by) {
-                case 8: return launch_smooth3d_rc<T, SMV, VARV, FL, 8>(d, sel, cfg, grid, s);
+                case 8: return launch_smooth3d_rc<T, SMV, OPV, FL, 8>(d, sel, cfg, grid, s);
                 case 12:
-                    if constexpr (wide) return launch_smooth3d_rc<T, SMV, VARV, FL, 12>(d, sel, cfg, grid, s);
+                    if constexpr (wide) return launch_smooth3d_rc<T, SMV, OPV, FL, 12>(d, sel, cfg, grid, s);
                     return hipErrorInvalidValue;
                 default: return hipErrorInvalidValue;
             }
@@ -463,21 +468,21 @@ hipError_t launch_smooth3d_fl(const GridDesc* d, int sel, TileCfg cfg, dim3 grid
     }
     if (cfg.wv == 4) {
         switch (cfg.by) {
-            case 8: return launch_smooth3d_g<T, SMV, VARV, FL, 8, 4>(d, sel, cfg, grid, s);
+            case 8: return launch_smooth3d_g<T, SMV, OPV, FL, 8, 4>(d, sel, cfg, grid, s);
             case 16:
-                if constexpr (!fp64var) return launch_smooth3d_g<T, SMV, VARV, FL, 16, 4>(d, sel, cfg, grid, s);
+                if constexpr (!fp64var) return launch_smooth3d_g<T, SMV, OPV, FL, 16, 4>(d, sel, cfg, grid, s);
                 return hipErrorInvalidValue;
             case 32:
-                if constexpr (wide) return launch_smooth3d_g<T, SMV, VARV, FL, 32, 4>(d, sel, cfg, grid, s);
+                if constexpr (wide) return launch_smooth3d_g<T, SMV, OPV, FL, 32, 4>(d, sel, cfg, grid, s);
                 return hipErrorInvalidValue;
             default: return hipErrorInvalidValue;
         }
     }
     if (cfg.wv == 8) {
         switch (cfg.by) {
-            case 16: return launch_smooth3d_g<T, SMV, VARV, FL, 16, 8>(d, sel, cfg, grid, s);
+            case 16: return launch_smooth3d_g<T, SMV, OPV, FL, 16, 8>(d, sel, cfg, grid, s);
             case 32:
-                if constexpr (!fp64var) return launch_smooth3d_g<T, SMV, VARV, FL, 32, 8>(d, sel, cfg, grid, s);
+                if constexpr (!fp64var) return launch_smooth3d_g<T, SMV, OPV, FL, 32, 8>(d, sel, cfg, grid, s);
                 return hipErrorInvalidValue;
             default: return hipErrorInvalidValue;
         }
@@ -486,32 +491,37 @@ hipError_t launch_smooth3d_fl(const GridDesc* d, int sel, TileCfg cfg, dim3 grid
 }
 
 template <typename T>
-hipError_t launch_smooth3d(int sm, bool var, const GridDesc* d, int sel, int flags, TileCfg cfg, dim3 grid,
+hipError_t launch_smooth3d(int sm, int op, const GridDesc* d, int sel, int flags, TileCfg cfg, dim3 grid,
                            hipStream_t s) {
-#define MG_FL(SMV, VARV)                                                                                   \
+#define MG_FL(SMV, OPV)                                                                                   \
     switch (flags) {                                                                                       \
-        case 0: return launch_smooth3d_fl<T, SMV, VARV, 0>(d, sel, cfg, grid, s);                           \
-        case SWEEP_ZERO_GUESS: return launch_smooth3d_fl<T, SMV, VARV, SWEEP_ZERO_GUESS>(d, sel, cfg, grid, s); \
-        case SWEEP_PROLONG: return launch_smooth3d_fl<T, SMV, VARV, SWEEP_PROLONG>(d, sel, cfg, grid, s);       \
+        case 0: return launch_smooth3d_fl<T, SMV, OPV, 0>(d, sel, cfg, grid, s);                           \
+        case SWEEP_ZERO_GUESS: return launch_smooth3d_fl<T, SMV, OPV, SWEEP_ZERO_GUESS>(d, sel, cfg, grid, s); \
+        case SWEEP_PROLONG: return launch_smooth3d_fl<T, SMV, OPV, SWEEP_PROLONG>(d, sel, cfg, grid, s);       \
         case SWEEP_NORM:                                                                                   \
-            if constexpr (sizeof(T) == 8) return launch_smooth3d_fl<T, SMV, VARV, SWEEP_NORM>(d, sel, cfg, grid, s); \
+            if constexpr (sizeof(T) == 8) return launch_smooth3d_fl<T, SMV, OPV, SWEEP_NORM>(d, sel, cfg, grid, s); \
             return hipErrorInvalidValue;                                                                   \
         default: return hipErrorInvalidValue;                                                              \
     }
-    if constexpr (sizeof(T) == 2) {  // binary16 storage: Laplacian only
-        if (var) return hipErrorInvalidValue;
-        if (sm == SM_RBGS) MG_FL(SM_RBGS, false) else MG_FL(SM_JACOBI, false)
-    } else {
-        if (sm == SM_RBGS) {
-            if (var) MG_FL(SM_RBGS, true) else MG_FL(SM_RBGS, false)
-        } else {
-            if (var) MG_FL(SM_JACOBI, true) else MG_FL(SM_JACOBI, false)
+    // binary16 storage: Laplacian only; a constant stencil: FP64 only
+    if (op == OP_LAP) {
+        if (sm == SM_RBGS) MG_FL(SM_RBGS, OP_LAP) else MG_FL(SM_JACOBI, OP_LAP)
+    }
+    if constexpr (sizeof(T) >= 4) {
+        if (op == OP_VAR) {
+            if (sm == SM_RBGS) MG_FL(SM_RBGS, OP_VAR) else MG_FL(SM_JACOBI, OP_VAR)
         }
     }
+    if constexpr (sizeof(T) == 8) {
+        if (op == OP_STENCIL) {
+            if (sm == SM_RBGS) MG_FL(SM_RBGS, OP_STENCIL) else MG_FL(SM_JACOBI, OP_STENCIL)
+        }
+    }
+    return hipErrorInvalidValue;
 #undef MG_FL
 }
 
-template hipError_t launch_smooth3d<MG_T>(int, bool, const GridDesc*, int, int, TileCfg, dim3, hipStream_t);
+template hipError_t launch_smooth3d<MG_T>(int, int, const GridDesc*, int, int, TileCfg, dim3, hipStream_t);
 
 template <typename T>
 hipError_t launch_smooth3d_zg2(const GridDesc* d, int ninst, int n, int sel, TileCfg cfg, hipStream_t s) {

@@ -17,8 +17,9 @@ namespace {
 // black nodes keep their old values in the red half-sweep.
 // ---------------------------------------------------------------------------
 
-template <typename ST, int SM, bool VAR, int BY, int PD, int FL>
+template <typename ST, int SM, int OP, int BY, int PD, int FL>
 struct SweepRC {
+    static constexpr bool VAR = OP == OP_VAR;
     using T = arith_t<ST>;  // arithmetic type; ST is the storage type of u, f and the coarse correction
     static_assert(!VAR || sizeof(ST) == sizeof(T), "coefficient fields are stored in the arithmetic type");
     static constexpr int flags = FL;
@@ -33,6 +34,7 @@ struct SweepRC {
     const MG_GLOBAL ST* __restrict__ ec;
     int n, nc, x0, y0, z0, z1, kstart, kend;
     T c, wd, om;
+    T sc[7];  // constant stencil
     int lane, gx;
     int cfirst;  // colour relaxed in the first half-sweep (0 red, 1 black)
     bool coli, lane1, lanet;
@@ -144,7 +146,7 @@ struct SweepRC {
             ka = KU[m];
         }
         T ds;
-        const T r = res3<T, VAR>(uc, uw, ue, A[m - 1], A[m + 1], Bv[m], Av[m], kc, kw, ke, kS, kN, kb, ka, fv, c, ds);
+        const T r = res3<T, OP>(uc, uw, ue, A[m - 1], A[m + 1], Bv[m], Av[m], kc, kw, ke, kS, kN, kb, ka, fv, c, ds, sc);
         return relax<T, VAR>(uc, r, ds, c, wd, om);
     }
 
@@ -234,11 +236,11 @@ struct SweepRC {
     }
 };
 
-template <typename ST, int SM, bool VAR, int BY, int PD, int FL>
+template <typename ST, int SM, int OP, int BY, int PD, int FL>
 __global__ __launch_bounds__(64) void k_smooth3d_rc(const GridDesc* __restrict__ descs, int sel, int zchunk) {
     const GridDesc d = descs[blockIdx.y];
     if (d.done && *gp(d.done)) return;
-    using S = SweepRC<ST, SM, VAR, BY, PD, FL>;
+    using S = SweepRC<ST, SM, OP, BY, PD, FL>;
     using T = arith_t<ST>;
     S s;
     const int n = d.n;
@@ -261,6 +263,7 @@ __global__ __launch_bounds__(64) void k_smooth3d_rc(const GridDesc* __restrict__
     s.c = (T)d.c;
     s.wd = (T)d.wd;
     s.om = (T)d.omega;
+    load_stencil<OP>(d, s.sc);
     s.lane = threadIdx.x;
     s.cfirst = (sel & SEL_BLACK_FIRST) ? 1 : 0;
     s.gx = s.x0 - S::H + s.lane;

@@ -75,7 +75,9 @@ struct Problem {
     bool var;
     bool sym = false;   // symmetric red-black: the post-smoothing sweeps relax black first
     int cycle = 0;      // 0 V, 1 W, 2 F (Algorithm 1 with one / two recursive calls; F: F then V)
-    int op() const { return var ? OP_VAR : OP_LAP; }
+    bool stencil = false;  // a constant stencil (FP64), coefficients sc
+    double sc[7] = {0, 0, 0, 0, 0, 0, 0};
+    int op() const { return stencil ? OP_STENCIL : (var ? OP_VAR : OP_LAP); }
     int cg_iters = 0;   // conjugate-gradient steps on a coarsest level with n > 3 (0: 4 (n - 1))
 };
 
@@ -185,13 +187,7 @@ struct mg_ctx {
     // complex diffusion (mg_cdiff_setup): its level hierarchy
     struct CDState* cd = nullptr;
 
-    // constant stencil (op MG_OP_CONST_STENCIL): the stencil and levels n, ...,
-    // 3 with their iterate (level 0: the caller's), Jacobi partner and
-    // right-hand side (level 0: the caller's)
-    bool st = false;
-    double st_coef[7] = {0, 0, 0, 0, 0, 0, 0};
-    std::vector<int> stn;
-    std::vector<double*> stu, stt, stf;
+    bool st = false;  // constant stencil (op MG_OP_CONST_STENCIL): heuristic launch geometry
 
     // measurement
     // measurement hooks: event pairs of the current solve, tagged with their

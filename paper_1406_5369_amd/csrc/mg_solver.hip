@@ -58,19 +58,19 @@ Tiles default_tiles(int dim, int elem_bytes, int n, int smoother) {
 }
 
 template <typename T>
-hipError_t launch_smooth(int dim, int sm, bool var, const GridDesc* d, int ninst, int n, int sel, int flags,
+hipError_t launch_smooth(int dim, int sm, int op, const GridDesc* d, int ninst, int n, int sel, int flags,
                          TileCfg cfg, hipStream_t s) {
     if (n < 5 || ninst <= 0) return hipErrorInvalidValue;
     if ((flags & SWEEP_NORM) && ninst != 1) return hipErrorInvalidValue;  // one partial row
     const dim3 grid(smooth_tiles(dim, sm, n, cfg), ninst);
-    const hipError_t e = dim == 2 ? launch_smooth2d<T>(sm, var, d, sel, flags, cfg, grid, s)
-                                  : launch_smooth3d<T>(sm, var, d, sel, flags, cfg, grid, s);
+    const hipError_t e = dim == 2 ? launch_smooth2d<T>(sm, op, d, sel, flags, cfg, grid, s)
+                                  : launch_smooth3d<T>(sm, op, d, sel, flags, cfg, grid, s);
     if (e != hipSuccess) return e;
     return hipGetLastError();
 }
-template hipError_t launch_smooth<double>(int, int, bool, const GridDesc*, int, int, int, int, TileCfg, hipStream_t);
-template hipError_t launch_smooth<float>(int, int, bool, const GridDesc*, int, int, int, int, TileCfg, hipStream_t);
-template hipError_t launch_smooth<half_t>(int, int, bool, const GridDesc*, int, int, int, int, TileCfg, hipStream_t);
+template hipError_t launch_smooth<double>(int, int, int, const GridDesc*, int, int, int, int, TileCfg, hipStream_t);
+template hipError_t launch_smooth<float>(int, int, int, const GridDesc*, int, int, int, int, TileCfg, hipStream_t);
+template hipError_t launch_smooth<half_t>(int, int, int, const GridDesc*, int, int, int, int, TileCfg, hipStream_t);
 
 namespace {
 
@@ -113,7 +113,7 @@ int tail_first_level(int dim, int elem, int op, const std::vector<int>& n, bool 
 // gradients (n > 3), from a zero iterate.
 template <typename T>
 hipError_t coarse_solve(const Problem& P, const Group& g, hipStream_t s) {
-    if (g.n == 3) return launch_coarsest<T>(P.dim, P.var, g.d, g.ninst, s);
+    if (g.n == 3) return launch_coarsest<T>(P.dim, P.op(), g.d, g.ninst, s);
     return launch_cg<T>(P.dim, P.var, g.d, g.ninst, g.n, P.cg_iters > 0 ? P.cg_iters : 4 * (g.n - 1), s);
 }
 
@@ -121,7 +121,7 @@ hipError_t coarse_solve(const Problem& P, const Group& g, hipStream_t s) {
 // red-black levels in FP32 or binary16 storage whose tiles chose it.
 template <typename T>
 bool fused_restrict_ok(const Problem& P, int dim, const Tiles& t) {
-    return sizeof(T) <= 4 && dim == 3 && !P.var && P.smoother == SM_RBGS && t.fused.zchunk > 0 &&
+    return sizeof(T) <= 4 && dim == 3 && P.op() == OP_LAP && P.smoother == SM_RBGS && t.fused.zchunk > 0 &&
            std::getenv("MG_NO_FUSED_RESTRICT") == nullptr;
 }
 
@@ -129,7 +129,7 @@ bool fused_restrict_ok(const Problem& P, int dim, const Tiles& t) {
 // Laplacian red-black levels in FP32 or binary16 storage whose tiles chose it.
 template <typename T>
 bool smooth2_ok(const Problem& P, int dim, const Tiles& t, bool zero) {
-    return zero && sizeof(T) <= 4 && (dim == 2 || dim == 3) && !P.var && P.smoother == SM_RBGS && P.nu1 >= 2 &&
+    return zero && sizeof(T) <= 4 && (dim == 2 || dim == 3) && P.op() == OP_LAP && P.smoother == SM_RBGS && P.nu1 >= 2 &&
            t.smooth_zg2.zchunk > 0 && std::getenv("MG_NO_FUSED_SMOOTH2") == nullptr;
 }
 // 'sel' names the output buffer (1: u, 0: t; the input is the zero iterate).
@@ -143,7 +143,7 @@ hipError_t launch_smooth2(int dim, const Group& g, const Tiles& t, int sel, hipS
 // tiles chose it.
 template <typename T>
 bool post2_ok(const Problem& P, int dim, const Tiles& t) {
-    return sizeof(T) <= 4 && dim == 2 && !P.var && P.smoother == SM_RBGS && P.nu2 >= 2 &&
+    return sizeof(T) <= 4 && dim == 2 && P.op() == OP_LAP && P.smoother == SM_RBGS && P.nu2 >= 2 &&
            t.smooth_pro2.zchunk > 0 && std::getenv("MG_NO_FUSED_POST2") == nullptr;
 }
 
@@ -177,13 +177,13 @@ hipError_t cycle_rec(const Problem& P, const std::vector<Group>& G, int l, int k
         const int flags = (i == 0 && zero) ? SWEEP_ZERO_GUESS : 0;
         const bool timed = l == 0 && flags == 0;
         if (timed) prof.begin();
-        MG_TRY(launch_smooth<T>(dim, P.smoother, P.var, g.d, g.ninst, g.n, cur, flags, tiles[(size_t)l].sweep(flags),
+        MG_TRY(launch_smooth<T>(dim, P.smoother, P.op(), g.d, g.ninst, g.n, cur, flags, tiles[(size_t)l].sweep(flags),
                                 s));
         if (timed) prof.end();
         cur ^= 1;
     }
     if (P.nu1 == 0 && zero) MG_TRY(launch_zero_u<T>(dim, g.d, g.ninst, g.n, s));
-    MG_TRY(launch_restrict<T>(dim, P.var, g.d, g.ninst, g.n, cur, tiles[(size_t)l].restr, s));
+    MG_TRY(launch_restrict<T>(dim, P.op(), g.d, g.ninst, g.n, cur, tiles[(size_t)l].restr, s));
     if (kind == 0) {
         MG_TRY(cycle_rec<T>(P, G, l + 1, 0, true, tiles, s, prof, tail));
     } else if (kind == 1) {
@@ -199,7 +199,7 @@ hipError_t cycle_rec(const Problem& P, const std::vector<Group>& G, int l, int k
         const int flags = (i == 0 && fuse) ? SWEEP_PROLONG : 0;
         const bool timed = l == 0 && flags == 0;
         if (timed) prof.begin();
-        MG_TRY(launch_smooth<T>(dim, P.smoother, P.var, g.d, g.ninst, g.n, post_sel(P, cur), flags,
+        MG_TRY(launch_smooth<T>(dim, P.smoother, P.op(), g.d, g.ninst, g.n, post_sel(P, cur), flags,
                                 tiles[(size_t)l].sweep(flags), s));
         if (timed) prof.end();
         cur ^= 1;
@@ -253,13 +253,13 @@ hipError_t vcycle(const Problem& P, const std::vector<Group>& G, bool zero_top, 
             }
             const bool timed = l == 0 && flags == 0;  // plain finest-level sweeps only
             if (timed) prof.begin();
-            MG_TRY(launch_smooth<T>(dim, P.smoother, P.var, g.d, g.ninst, g.n, cur, flags,
+            MG_TRY(launch_smooth<T>(dim, P.smoother, P.op(), g.d, g.ninst, g.n, cur, flags,
                                     tiles[(size_t)l].sweep(flags), s));
             if (timed) prof.end();
             cur ^= 1;
         }
         if (P.nu1 == 0 && zero) MG_TRY(launch_zero_u<T>(dim, g.d, g.ninst, g.n, s));
-        if (!fuse) MG_TRY(launch_restrict<T>(dim, P.var, g.d, g.ninst, g.n, cur, tiles[(size_t)l].restr, s));
+        if (!fuse) MG_TRY(launch_restrict<T>(dim, P.op(), g.d, g.ninst, g.n, cur, tiles[(size_t)l].restr, s));
         sel[(size_t)l] = cur;
     }
     if (use_tail) {
@@ -287,7 +287,7 @@ hipError_t vcycle(const Problem& P, const std::vector<Group>& G, bool zero_top, 
             const int flags = (i == 0 && fuse) ? SWEEP_PROLONG : 0;
             const bool timed = l == 0 && flags == 0;
             if (timed) prof.begin();
-            MG_TRY(launch_smooth<T>(dim, P.smoother, P.var, g.d, g.ninst, g.n, post_sel(P, cur), flags,
+            MG_TRY(launch_smooth<T>(dim, P.smoother, P.op(), g.d, g.ninst, g.n, post_sel(P, cur), flags,
                                     tiles[(size_t)l].sweep(flags), s));
             if (timed) prof.end();
             cur ^= 1;

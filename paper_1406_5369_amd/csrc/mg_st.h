@@ -21,13 +21,11 @@ hipError_t st_relax(int dim, bool jacobi, const double* uin, double* uout, const
                     int colour, hipStream_t s);
 // fc (inner coarse nodes) = full weighting of the residual f - A u
 hipError_t st_restrict(int dim, const double* u, const double* f, double* fc, const STConst& L, hipStream_t s);
-// u (inner nodes, n per axis) += bi-/trilinear interpolation of ec
-hipError_t st_prolong(int dim, double* u, const double* ec, int n, hipStream_t s);
 // n = 3: the single unknown u = f / (c s0)
 hipError_t st_coarsest(int dim, double* u, const double* f, const STConst& L, hipStream_t s);
-// norm[0] = ||f - A u||_2 over inner nodes (part: st_norm_parts doubles)
+// norm[0] = ||f - A u||_2 over inner nodes of the grid (device descriptor) of
+// edge n (part: st_norm_parts doubles)
 int st_norm_parts(int dim, int n);
-hipError_t st_norm(int dim, const double* u, const double* f, const STConst& L, double* part, double* norm,
-                   hipStream_t s);
+hipError_t st_norm(int dim, const GridDesc* d, int n, double* part, double* norm, hipStream_t s);
 
 }  // namespace mg

@@ -6,9 +6,9 @@
 // relaxation u + wd r with wd = omega h^2 / s0, full-weighting restriction of
 // the residual and bi-/trilinear interpolation in the expression order of
 // the Laplacian path, the exact solve of the single unknown of the 3-node
-// grid.  FP64, plain one-node-per-thread kernels (neighbours through the
-// caches): a second operator beside the tuned Laplacian path, not its
-// throughput form.
+// grid.  FP64.  Solves run the Laplacian path's kernels (OP_STENCIL); here
+// are the single-level operations and the norm pass of solves without a
+// pre-smoothing sweep, one node per thread.
 #include <algorithm>
 #include <cstring>
 
@@ -97,35 +97,6 @@ __global__ __launch_bounds__(NT) void k_st_restrict(const double* __restrict__ u
     gp(fc_)[q] = v;
 }
 
-// u += P ec at inner fine nodes: coincident value, or the mean of 2 / 4 / 8
-// coarse neighbours along the odd axes (taken in x, y, z order)
-template <int DIM>
-__global__ __launch_bounds__(NT) void k_st_prolong(double* __restrict__ u_, const double* __restrict__ ec_, int nf) {
-    MG_GLOBAL double* __restrict__ u = gp(u_);
-    const MG_GLOBAL double* __restrict__ e = gp(ec_);
-    const size_t N = DIM == 2 ? (size_t)nf * nf : (size_t)nf * nf * nf;
-    const size_t p = (size_t)blockIdx.x * NT + threadIdx.x;
-    if (p >= N) return;
-    int i, j, k;
-    st_ijk<DIM>(p, nf, i, j, k);
-    if (!st_inner<DIM>(nf, i, j, k)) return;
-    const int nc = (nf - 1) / 2 + 1;
-    const size_t q = ((size_t)(k / 2) * nc + (size_t)(j / 2)) * nc + (size_t)(i / 2);
-    size_t s[3];
-    int m = 0;
-    if (i & 1) s[m++] = 1;
-    if (j & 1) s[m++] = (size_t)nc;
-    if (DIM == 3 && (k & 1)) s[m++] = (size_t)nc * nc;
-    double v;
-    if (m == 0) v = e[q];
-    else if (m == 1) v = 0.5 * (e[q] + e[q + s[0]]);
-    else if (m == 2) v = 0.25 * ((e[q] + e[q + s[0]]) + (e[q + s[1]] + e[q + s[0] + s[1]]));
-    else
-        v = 0.125 * (((e[q] + e[q + s[0]]) + (e[q + s[1]] + e[q + s[0] + s[1]])) +
-                     ((e[q + s[2]] + e[q + s[0] + s[2]]) + (e[q + s[1] + s[2]] + e[q + s[0] + s[1] + s[2]])));
-    u[p] = u[p] + v;
-}
-
 template <int DIM>
 __global__ void k_st_coarsest(double* __restrict__ u_, const double* __restrict__ f_, STConst L) {
     if (threadIdx.x != 0 || blockIdx.x != 0) return;
@@ -135,10 +106,15 @@ __global__ void k_st_coarsest(double* __restrict__ u_, const double* __restrict_
 
 // per-block partial sums of r^2 over inner nodes
 template <int DIM>
-__global__ __launch_bounds__(NT) void k_st_norm(const double* __restrict__ u_, const double* __restrict__ f_,
-                                                STConst L, double* __restrict__ part) {
+__global__ __launch_bounds__(NT) void k_st_norm(const GridDesc* __restrict__ desc, double* __restrict__ part) {
     __shared__ double red4[4];
-    const int n = L.n;
+    const GridDesc& d = *desc;
+    STConst L;
+    L.n = d.n;
+    L.c = d.c;
+#pragma unroll
+    for (int q = 0; q < 7; ++q) L.s[q] = d.sc[q];
+    const int n = d.n;
     const size_t N = DIM == 2 ? (size_t)n * n : (size_t)n * n * n;
     const size_t p = (size_t)blockIdx.x * NT + threadIdx.x;
     double acc = 0.0;
@@ -146,7 +122,7 @@ __global__ __launch_bounds__(NT) void k_st_norm(const double* __restrict__ u_, c
         int i, j, k;
         st_ijk<DIM>(p, n, i, j, k);
         if (st_inner<DIM>(n, i, j, k)) {
-            const double r = st_res<DIM>(gp(u_), gp(f_), L, p);
+            const double r = st_res<DIM>(gp((const double*)d.u), gp((const double*)d.f), L, p);
             acc = r * r;
         }
     }
@@ -190,13 +166,6 @@ hipError_t st_restrict(int dim, const double* u, const double* f, double* fc, co
     return hipGetLastError();
 }
 
-hipError_t st_prolong(int dim, double* u, const double* ec, int n, hipStream_t s) {
-    const unsigned b = nblk(nodes(dim, n));
-    if (dim == 2) k_st_prolong<2><<<b, NT, 0, s>>>(u, ec, n);
-    else k_st_prolong<3><<<b, NT, 0, s>>>(u, ec, n);
-    return hipGetLastError();
-}
-
 hipError_t st_coarsest(int dim, double* u, const double* f, const STConst& L, hipStream_t s) {
     if (dim == 2) k_st_coarsest<2><<<1, 64, 0, s>>>(u, f, L);
     else k_st_coarsest<3><<<1, 64, 0, s>>>(u, f, L);
@@ -205,11 +174,10 @@ hipError_t st_coarsest(int dim, double* u, const double* f, const STConst& L, hi
 
 int st_norm_parts(int dim, int n) { return (int)nblk(nodes(dim, n)); }
 
-hipError_t st_norm(int dim, const double* u, const double* f, const STConst& L, double* part, double* norm,
-                   hipStream_t s) {
-    const int np = st_norm_parts(dim, L.n);
-    if (dim == 2) k_st_norm<2><<<np, NT, 0, s>>>(u, f, L, part);
-    else k_st_norm<3><<<np, NT, 0, s>>>(u, f, L, part);
+hipError_t st_norm(int dim, const GridDesc* d, int n, double* part, double* norm, hipStream_t s) {
+    const int np = st_norm_parts(dim, n);
+    if (dim == 2) k_st_norm<2><<<np, NT, 0, s>>>(d, part);
+    else k_st_norm<3><<<np, NT, 0, s>>>(d, part);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_norm_finalize(part, np, np, 0, 1, norm, s);

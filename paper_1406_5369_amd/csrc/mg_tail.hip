@@ -623,10 +623,16 @@ hipError_t launch_tail(int dim, int sm, int op, const TailDesc* d, int ninst, in
         if (dim == 2) MG_TAIL(2, OP_LAP, 6);
         else MG_TAIL(3, OP_LAP, 4);
     }
-    if constexpr (sizeof(T) >= 4) {  // binary16 storage: Laplacian only
+    if constexpr (sizeof(T) >= 4) {  // binary16 storage: Laplacian only; a constant stencil: FP64 only
         if (op == OP_VAR) {
             if (dim == 2) MG_TAIL(2, OP_VAR, (F ? 6 : 5));
             else MG_TAIL(3, OP_VAR, (F ? 4 : 3));
+        }
+    }
+    if constexpr (sizeof(T) == 8) {
+        if (op == OP_STENCIL) {
+            if (dim == 2) MG_TAIL(2, OP_STENCIL, 6);
+            else MG_TAIL(3, OP_STENCIL, 4);
         }
     }
 #undef MG_TAIL

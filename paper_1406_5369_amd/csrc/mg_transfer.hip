@@ -35,8 +35,9 @@ __device__ __forceinline__ T fw3(const T (*Rb)[BX], const T (*Rc)[BX], const T (
     return ((T(0.125) * Rc[ly][lx] + T(0.0625) * faces) + T(0.03125) * edges) + T(0.015625) * corners;
 }
 
-template <typename ST, bool VAR, int BY>
+template <typename ST, int OP, int BY>
 __global__ __launch_bounds__(NT) void k_restrict2d(const GridDesc* __restrict__ descs, int sel) {
+    constexpr bool VAR = OP == OP_VAR;
     using T = arith_t<ST>;
     const GridDesc d = descs[blockIdx.y];
     if (d.done && *gp(d.done)) return;
@@ -51,6 +52,8 @@ __global__ __launch_bounds__(NT) void k_restrict2d(const GridDesc* __restrict__ 
     const MG_GLOBAL T* __restrict__ kf = gp((const T*)d.k);
     MG_GLOBAL ST* __restrict__ fc = gp((ST*)d.fc);
     const T c = (T)d.c;
+    T sc[7];
+    load_stencil<OP>(d, sc);
     __shared__ T U[BY][BX];
     __shared__ T Rr[BY][BX];
     __shared__ T K[VAR ? BY : 1][BX];
@@ -75,7 +78,7 @@ __global__ __launch_bounds__(NT) void k_restrict2d(const GridDesc* __restrict__ 
         if (lres && ly >= 1 && ly <= 2 * CY + 1) {
             const bool inn = gx >= 1 && gx <= nf - 2 && gy >= 1 && gy <= nf - 2;
             T ds;
-            Rr[ly][lane] = inn ? lds_res2<T, VAR>(U, K, ly, lane, fr[m], c, ds) : T(0);
+            Rr[ly][lane] = inn ? lds_res2<T, OP>(U, K, ly, lane, fr[m], c, ds, sc) : T(0);
         }
     }
     __syncthreads();
@@ -88,8 +91,9 @@ __global__ __launch_bounds__(NT) void k_restrict2d(const GridDesc* __restrict__ 
 // 3D: marching over fine planes; step m publishes u plane m, computes the
 // residual of plane m-1 and, once planes 2K-1..2K+1 are in the residual ring,
 // the coarse plane K.
-template <typename ST, bool VAR, int BY>
+template <typename ST, int OP, int BY>
 __global__ __launch_bounds__(NT) void k_restrict3d(const GridDesc* __restrict__ descs, int sel, int zchunk) {
+    constexpr bool VAR = OP == OP_VAR;
     using T = arith_t<ST>;
     const GridDesc d = descs[blockIdx.y];
     if (d.done && *gp(d.done)) return;
@@ -105,6 +109,8 @@ __global__ __launch_bounds__(NT) void k_restrict3d(const GridDesc* __restrict__ 
     const MG_GLOBAL T* __restrict__ kf = gp((const T*)d.k);
     MG_GLOBAL ST* __restrict__ fc = gp((ST*)d.fc);
     const T c = (T)d.c;
+    T sc[7];
+    load_stencil<OP>(d, sc);
     __shared__ T U[3][BY][BX];
     __shared__ T Rr[3][BY][BX];
     __shared__ T K[VAR ? 3 : 1][BY][BX];
@@ -163,7 +169,8 @@ __global__ __launch_bounds__(NT) void k_restrict3d(const GridDesc* __restrict__ 
                     const bool inn = zin && coli && gy >= 1 && gy <= nf - 2;
                     T ds;
                     Rr[s1][ly][lane] =
-                        inn ? lds_res3<T, VAR>(U[s2], U[s1], U[s0], K[s2], K[s1], K[s0], ly, lane, fprev[m], c, ds)
+                        inn ? lds_res3<T, OP>(U[s2], U[s1], U[s0], K[s2], K[s1], K[s0], ly, lane, fprev[m], c, ds,
+                                              sc)
                             : T(0);
                 }
             }
@@ -372,7 +379,7 @@ __global__ __launch_bounds__(NT) void k_prolong(const GridDesc* __restrict__ des
 }
 
 // n = 3: one unknown, u = f / diag (diag = c*2d, or c*dsum).
-template <typename ST, int DIM, bool VAR>
+template <typename ST, int DIM, int OP>
 __global__ void k_coarsest(const GridDesc* __restrict__ descs) {
     using T = arith_t<ST>;
     const GridDesc d = descs[blockIdx.x];
@@ -382,7 +389,7 @@ __global__ void k_coarsest(const GridDesc* __restrict__ descs) {
     const MG_GLOBAL ST* f = gp((const ST*)d.f);
     const T c = (T)d.c;
     T diag;
-    if constexpr (VAR) {
+    if constexpr (OP == OP_VAR) {
         const MG_GLOBAL T* k = gp((const T*)d.k);
         const T kC = k[p];
         const int sy = 3, sz = 9;
@@ -396,6 +403,8 @@ __global__ void k_coarsest(const GridDesc* __restrict__ descs) {
             dsum = ((kxW + kxC) + (kyS + kyC)) + (kzB + kzC);
         }
         diag = c * dsum;
+    } else if constexpr (OP == OP_STENCIL) {
+        diag = c * (T)d.sc[0];
     } else {
         diag = c * (DIM == 2 ? T(4) : T(6));
     }
@@ -477,33 +486,38 @@ int norm_tiles(int dim, int n, TileCfg cfg) {
     return cdiv(m, TX) * cdiv(m, TY) * nzchunks(m, cfg.zchunk);
 }
 
+namespace {
+template <typename T, int OPV>
+hipError_t launch_restrict_op(int dim, const GridDesc* d, int sel, TileCfg cfg, dim3 grid, hipStream_t s) {
+    if (dim == 2) {
+        MG_BY_SWITCH(cfg.by, (k_restrict2d<T, OPV, BY><<<grid, NT, 0, s>>>(d, sel)))
+    } else {
+        MG_BY_SWITCH(cfg.by, (k_restrict3d<T, OPV, BY><<<grid, NT, 0, s>>>(d, sel, cfg.zchunk)))
+    }
+    return hipGetLastError();
+}
+template <typename T, int OPV>
+hipError_t launch_coarsest_op(int dim, const GridDesc* d, int ninst, hipStream_t s) {
+    if (dim == 2) k_coarsest<T, 2, OPV><<<ninst, 64, 0, s>>>(d);
+    else k_coarsest<T, 3, OPV><<<ninst, 64, 0, s>>>(d);
+    return hipGetLastError();
+}
+}  // namespace
+
+// binary16 storage: Laplacian only; a constant stencil: FP64 only
 template <typename T>
-hipError_t launch_restrict(int dim, bool var, const GridDesc* d, int ninst, int nf, int sel, TileCfg cfg,
+hipError_t launch_restrict(int dim, int op, const GridDesc* d, int ninst, int nf, int sel, TileCfg cfg,
                            hipStream_t s) {
     if (nf < 5 || ninst <= 0) return hipErrorInvalidValue;
     const dim3 grid(restrict_tiles(dim, nf, cfg), ninst);
-    if constexpr (sizeof(T) == 2) {  // binary16 storage: Laplacian only
-        if (dim == 2) {
-            MG_BY_SWITCH(cfg.by, (k_restrict2d<T, false, BY><<<grid, NT, 0, s>>>(d, sel)))
-        } else {
-            MG_BY_SWITCH(cfg.by, (k_restrict3d<T, false, BY><<<grid, NT, 0, s>>>(d, sel, cfg.zchunk)))
-        }
-        return var ? hipErrorInvalidValue : hipGetLastError();
+    if (op == OP_LAP) return launch_restrict_op<T, OP_LAP>(dim, d, sel, cfg, grid, s);
+    if constexpr (sizeof(T) >= 4) {
+        if (op == OP_VAR) return launch_restrict_op<T, OP_VAR>(dim, d, sel, cfg, grid, s);
     }
-    if (dim == 2) {
-        if (var) {
-            MG_BY_SWITCH(cfg.by, (k_restrict2d<T, true, BY><<<grid, NT, 0, s>>>(d, sel)))
-        } else {
-            MG_BY_SWITCH(cfg.by, (k_restrict2d<T, false, BY><<<grid, NT, 0, s>>>(d, sel)))
-        }
-    } else {
-        if (var) {
-            MG_BY_SWITCH(cfg.by, (k_restrict3d<T, true, BY><<<grid, NT, 0, s>>>(d, sel, cfg.zchunk)))
-        } else {
-            MG_BY_SWITCH(cfg.by, (k_restrict3d<T, false, BY><<<grid, NT, 0, s>>>(d, sel, cfg.zchunk)))
-        }
+    if constexpr (sizeof(T) == 8) {
+        if (op == OP_STENCIL) return launch_restrict_op<T, OP_STENCIL>(dim, d, sel, cfg, grid, s);
     }
-    return hipGetLastError();
+    return hipErrorInvalidValue;
 }
 
 template <typename T>
@@ -517,21 +531,15 @@ hipError_t launch_prolong(int dim, const GridDesc* d, int ninst, int nf, int sel
 }
 
 template <typename T>
-hipError_t launch_coarsest(int dim, bool var, const GridDesc* d, int ninst, hipStream_t s) {
-    if constexpr (sizeof(T) == 2) {  // binary16 storage: Laplacian only
-        if (var) return hipErrorInvalidValue;
-        if (dim == 2) k_coarsest<T, 2, false><<<ninst, 64, 0, s>>>(d);
-        else k_coarsest<T, 3, false><<<ninst, 64, 0, s>>>(d);
-        return hipGetLastError();
+hipError_t launch_coarsest(int dim, int op, const GridDesc* d, int ninst, hipStream_t s) {
+    if (op == OP_LAP) return launch_coarsest_op<T, OP_LAP>(dim, d, ninst, s);
+    if constexpr (sizeof(T) >= 4) {
+        if (op == OP_VAR) return launch_coarsest_op<T, OP_VAR>(dim, d, ninst, s);
     }
-    if (dim == 2) {
-        if (var) k_coarsest<T, 2, true><<<ninst, 64, 0, s>>>(d);
-        else k_coarsest<T, 2, false><<<ninst, 64, 0, s>>>(d);
-    } else {
-        if (var) k_coarsest<T, 3, true><<<ninst, 64, 0, s>>>(d);
-        else k_coarsest<T, 3, false><<<ninst, 64, 0, s>>>(d);
+    if constexpr (sizeof(T) == 8) {
+        if (op == OP_STENCIL) return launch_coarsest_op<T, OP_STENCIL>(dim, d, ninst, s);
     }
-    return hipGetLastError();
+    return hipErrorInvalidValue;
 }
 
 template <typename T>
@@ -560,9 +568,9 @@ hipError_t launch_copy_bytes(void* dst, const void* src, size_t bytes, hipStream
 }
 
 #define MG_INST(T)                                                                                              \
-    template hipError_t launch_restrict<T>(int, bool, const GridDesc*, int, int, int, TileCfg, hipStream_t);    \
+    template hipError_t launch_restrict<T>(int, int, const GridDesc*, int, int, int, TileCfg, hipStream_t);    \
     template hipError_t launch_prolong<T>(int, const GridDesc*, int, int, int, hipStream_t);                    \
-    template hipError_t launch_coarsest<T>(int, bool, const GridDesc*, int, hipStream_t);                       \
+    template hipError_t launch_coarsest<T>(int, int, const GridDesc*, int, hipStream_t);                       \
     template hipError_t launch_copy_t_to_u<T>(int, const GridDesc*, int, int, hipStream_t);                     \
     template hipError_t launch_zero_u<T>(int, const GridDesc*, int, int, hipStream_t);                       \
     template hipError_t launch_smooth_restrict3d<T>(const GridDesc*, int, int, int, TileCfg, hipStream_t);
