@@ -264,7 +264,7 @@ struct Engine {
         max_a = log2edge(max_n);
         tiles.resize((size_t)max_a + 1);
         for (int a = 1; a <= max_a; ++a) {
-            tiles[(size_t)a] = default_tiles(dim, 4, (1 << a) + 1, P.smoother);
+            tiles[(size_t)a] = default_tiles(dim, 4, (1 << a) + 1, P.smoother, P.op());
             // 2D refinement pass (batches are Laplacian): two nodes per lane,
             // each wavefront marching 32 rows (longer chunks leave the smaller
             // grids of a batch too few workgroups)

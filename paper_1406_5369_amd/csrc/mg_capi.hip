@@ -874,7 +874,7 @@ std::vector<TileCfg> smooth2_candidates(int dim, int n) {
     std::vector<TileCfg> cands;
     const int m = n - 2;
     for (int by : dim == 2 ? std::vector<int>{1} : std::vector<int>{12, 16})
-        for (int zc = dim == 2 ? 16 : 8; zc <= (dim == 2 ? 256 : 128) && zc <= std::max(dim == 2 ? 16 : 8, m); zc *= 2)
+        for (int zc = dim == 2 ? 4 : 2; zc <= (dim == 2 ? 256 : 128) && zc <= std::max(dim == 2 ? 4 : 2, m); zc *= 2)
             for (int order : {0, 1}) {
                 TileCfg t{dim == 2 ? 12 : by, zc};
                 t.order = order;
@@ -1287,8 +1287,8 @@ int mg_setup(const mg_params* p, void* stream, mg_ctx** out) {
     }
     c->nlev = (int)c->n.size();
     for (int l = 0; l < c->nlev; ++l) {
-        c->tl64.push_back(default_tiles(dim, 8, c->n[(size_t)l], c->prob.smoother));
-        c->tl32.push_back(default_tiles(dim, 4, c->n[(size_t)l], c->prob.smoother));
+        c->tl64.push_back(default_tiles(dim, 8, c->n[(size_t)l], c->prob.smoother, c->prob.op()));
+        c->tl32.push_back(default_tiles(dim, ir_elem(c->p), c->n[(size_t)l], c->prob.smoother, c->prob.op()));
     }
     c->top = c->tl64[0];
     if (is_h16(c->p)) {  // the binary16 refinement pass has two nodes per lane
@@ -1613,8 +1613,10 @@ int mg_copy_kernel(void* dst, const void* src, size_t bytes, void* stream) {
 // Single-level operations
 // ---------------------------------------------------------------------------
 
-static TileCfg pick_cfg(int dim, int elem, int n, int smoother, int by, int zchunk, int kind) {
-    Tiles t = default_tiles(dim, elem, n, smoother);
+// 'own': the caller names the rows or the wavefronts of the tile; the rest is
+// then that of an LDS tile.
+static TileCfg pick_cfg(int dim, int elem, int n, int smoother, int op, int by, int zchunk, int kind, bool own) {
+    Tiles t = own ? lds_tiles(dim, n, smoother) : default_tiles(dim, elem, n, smoother, op);
     TileCfg c = kind == 0 ? t.smooth : (kind == 1 ? t.restr : t.norm);
     if (by) c.by = by;
     if (zchunk) c.zchunk = zchunk;
@@ -1660,7 +1662,7 @@ int mg_level_smooth(int dim, int n, int dtype, int smoother, double omega, const
     if (elem == 2 && k) return MG_ENOTSUP;
     const int sel = smoother == 2 ? SEL_BLACK_FIRST : 0;
     if (smoother == 2) smoother = SM_RBGS;
-    TileCfg cfg = pick_cfg(dim, elem, n, smoother, by, zchunk, 0);
+    TileCfg cfg = pick_cfg(dim, elem, n, smoother, k ? OP_VAR : OP_LAP, by, zchunk, 0, by != 0 || waves != 0);
     if (prefetch) cfg.pd = prefetch;
     if (waves) cfg.wv = waves;
     if (order != 0 && order != 1) return MG_EINVAL;
@@ -1789,7 +1791,7 @@ int mg_level_residual_restrict(int dim, int n, int dtype, const void* k, const v
     if (!valid_edge(dim, n) || n < 5 || !elem) return MG_EINVAL;
     if (!u || !f || !fc) return MG_EINVAL;
     if (elem == 2 && k) return MG_ENOTSUP;
-    const TileCfg cfg = pick_cfg(dim, elem, n, 0, by, zchunk, 1);
+    const TileCfg cfg = pick_cfg(dim, elem, n, 0, OP_LAP, by, zchunk, 1, true);
     if (!valid_cfg(cfg, dim, elem, k != nullptr, 1)) return MG_EINVAL;
     hipStream_t s = (hipStream_t)stream;
     GridDesc h{};
@@ -1874,7 +1876,7 @@ int mg_level_ir_update(int dim, int n, const double* k, const double* u_in, cons
                        int pairs, void* stream) {
     if (!valid_edge(dim, n) || n < 5) return MG_EINVAL;
     if (!u_in || !e || !f || !u_out || !r || !norm_out || u_in == u_out) return MG_EINVAL;
-    TileCfg cfg = pick_cfg(dim, 8, n, 0, by, zchunk, 2);
+    TileCfg cfg = pick_cfg(dim, 8, n, 0, OP_LAP, by, zchunk, 2, true);
     if (prefetch) cfg.pd = prefetch;
     if (waves) cfg.wv = waves;
     cfg.xp = pairs ? 2 : 1;
@@ -1915,7 +1917,7 @@ int mg_level_ir_update_f16(int dim, int n, const double* u_in, const void* e16, 
     if (!valid_edge(dim, n) || n < 5) return MG_EINVAL;
     if (!u_in || !f || !r16 || !norm_out || !max_out || (e16 && (!u_out || u_in == u_out))) return MG_EINVAL;
     if (e16 && !(e_scale > 0.0)) return MG_EINVAL;
-    TileCfg cfg = pick_cfg(dim, 8, n, 0, by, zchunk, 2);
+    TileCfg cfg = pick_cfg(dim, 8, n, 0, OP_LAP, by, zchunk, 2, true);
     if (prefetch) cfg.pd = prefetch;
     if (waves) cfg.wv = waves;
     cfg.xp = 2;
@@ -2203,7 +2205,7 @@ int mg_level_ir_update_noalloc(int dim, int n, const double* k, const double* u_
                                int waves, int pairs, void* stream) {
     if (!valid_edge(dim, n) || n < 5) return MG_EINVAL;
     if (!u_in || !e || !f || !u_out || !r || !norm_out || u_in == u_out) return MG_EINVAL;
-    TileCfg cfg = pick_cfg(dim, 8, n, 0, by, zchunk, 2);
+    TileCfg cfg = pick_cfg(dim, 8, n, 0, OP_LAP, by, zchunk, 2, true);
     if (prefetch) cfg.pd = prefetch;
     if (waves) cfg.wv = waves;
     cfg.xp = pairs ? 2 : 1;

@@ -2,7 +2,7 @@
 #pragma once
 #include "mg_kern.h"
 #include "mg_smooth3d_rc.inl"
-#include "mg_smooth3d_rc2.inl"
+#include "mg_smooth3d_rb.inl"
 
 namespace mg {
 namespace {
@@ -437,11 +437,19 @@ hipError_t launch_smooth3d_g(const GridDesc* d, int sel, TileCfg cfg, dim3 grid,
     return hipSuccess;
 }
 
+// One wavefront per tile: red-black sweeps of constant operators hold nodes by
+// colour, the others rows.
 template <typename T, int SMV, int OPV, int FL, int BY>
 hipError_t launch_smooth3d_rc(const GridDesc* d, int sel, TileCfg cfg, dim3 grid, hipStream_t s) {
     const int arg = sweep_arg(sel, cfg);
-    if (cfg.pd == 2) k_smooth3d_rc<T, SMV, OPV, BY, 2, FL><<<grid, 64, 0, s>>>(d, arg, cfg.zchunk);
-    else k_smooth3d_rc<T, SMV, OPV, BY, 1, FL><<<grid, 64, 0, s>>>(d, arg, cfg.zchunk);
+    if constexpr ((FL & SWEEP_NORM) != 0) {
+        return hipErrorInvalidValue;
+    } else if constexpr (SMV == SM_RBGS && OPV != OP_VAR) {
+        k_smooth3d_rb<T, OPV, BY, FL><<<grid, 64, 0, s>>>(d, arg, cfg.zchunk);
+    } else {
+        if (cfg.pd == 2) k_smooth3d_rc<T, SMV, OPV, BY, 2, FL><<<grid, 64, 0, s>>>(d, arg, cfg.zchunk);
+        else k_smooth3d_rc<T, SMV, OPV, BY, 1, FL><<<grid, 64, 0, s>>>(d, arg, cfg.zchunk);
+    }
     return hipSuccess;
 }
 
@@ -453,8 +461,8 @@ hipError_t launch_smooth3d_fl(const GridDesc* d, int sel, TileCfg cfg, dim3 grid
     constexpr bool VARV = OPV == OP_VAR;
     constexpr bool wide = sizeof(arith_t<T>) == 4 && !VARV;
     constexpr bool fp64var = sizeof(arith_t<T>) == 8 && VARV;  // two rows per thread at most
-    if (cfg.wv == 1) {  // one wavefront per tile, rows in registers: 8 rows, or 12 in FP32 without coefficients
-        if constexpr ((sizeof(arith_t<T>) == 8 && VARV) || (FL & SWEEP_NORM) != 0) {
+    if (cfg.wv == 1) {  // one wavefront per tile, rows in registers
+        if constexpr (sizeof(arith_t<T>) == 8 && VARV) {
             return hipErrorInvalidValue;
         } else {
             switch (cfg.by) {

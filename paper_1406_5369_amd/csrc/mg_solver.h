@@ -44,7 +44,9 @@ struct Tiles {
 // Heuristic launch geometry for one level (used when autotuning is off and
 // for levels too small to be worth timing): enough workgroups to cover the
 // chip (z-chunks in 3D) and the smallest tile height on small grids.
-Tiles default_tiles(int dim, int elem_bytes, int n, int smoother);
+Tiles default_tiles(int dim, int elem_bytes, int n, int smoother, int op);
+// The same with LDS tiles only (no one-wavefront sweeps).
+Tiles lds_tiles(int dim, int n, int smoother);
 // Autotune the FP32 sweeps and restriction of one absolute level of a batch:
 // 'count' instances of edge n, descriptors d (device).  Cached per process.
 hipError_t tune_group(int dim, int smoother, const GridDesc* d, int count, int n, Tiles& t, hipStream_t s);

@@ -28,7 +28,7 @@ int heuristic_zchunk(int dim, int n, int by, int halo, int target_blocks) {
     return std::max(2, (m + chunks - 1) / chunks);
 }
 
-Tiles default_tiles(int dim, int elem_bytes, int n, int smoother) {
+Tiles lds_tiles(int dim, int n, int smoother) {
     Tiles t;
     const int H = smoother == SM_RBGS ? 2 : 1;
     const int target = 2048;
@@ -53,7 +53,24 @@ Tiles default_tiles(int dim, int elem_bytes, int n, int smoother) {
         t.restr = {rb, std::max(1, (mc + chunks - 1) / chunks)};
     }
     t.norm = {by, heuristic_zchunk(3, n, by, 1, target)};
-    (void)elem_bytes;
+    return t;
+}
+
+Tiles default_tiles(int dim, int elem_bytes, int n, int smoother, int op) {
+    Tiles t = lds_tiles(dim, n, smoother);
+    if (dim == 3 && smoother == SM_RBGS && op != OP_VAR) {
+        // One wavefront per 64 x 8 tile, nodes held by colour: measured against
+        // the LDS tiles above, 33^3 4.5 / 6.5 us, 65^3 4.9 / 6.5 us, 129^3 9.0 /
+        // 17.2 us, 257^3 36.5 / 52.2 us (FP32 plain sweep; with the correction
+        // 11.5 / 25.6 us at 129^3; FP64 14.3 / 20.5 and 18.4 / 35.2 us there).
+        // Chunks: enough wavefronts on small grids, then few re-read planes
+        // (129^3 FP32: 10.7 / 9.0 / 9.3 / 11.5 us with 2 / 4 / 8 / 16 planes).
+        const int zc = std::min(32, std::max(2, n / (elem_bytes == 8 ? 16 : 32)));
+        t.smooth = t.smooth_zg = t.smooth_pro = {8, zc, 1, 1};
+        // The two sweeps from zero in one launch: 33^3 5.5 us against 3.9 + 4.5,
+        // 65^3 7.2 / 8.7, 129^3 13.4 / 15.9 us.
+        if (elem_bytes <= 4 && op == OP_LAP) t.smooth_zg2 = {12, zc};
+    }
     return t;
 }
 
