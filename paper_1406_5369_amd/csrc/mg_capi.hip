@@ -110,7 +110,7 @@ hipError_t build_levels(Levels& L, int dim, const std::vector<int>& n, int elem,
             L.own_u[l] = 1;
             L.own_f[l] = 1;
         }
-        if (n[l] > 3) {
+        if (n[l] > 3 || (n[l] & 1) == 0) {  // cell-centred grids sweep down to two cells
             hipError_t e = zalloc(&L.t[l], bytes, s);
             if (e != hipSuccess) return e;
         }
@@ -171,6 +171,11 @@ void set_operator(GridDesc& d, const Problem& P, int n) {
     if (P.stencil) {
         d.wd = st_const(P.dim, n, P.sc, P.omega).wd;
         for (int q = 0; q < 7; ++q) d.sc[q] = P.sc[q];
+    }
+    if (P.cc) {
+        const CCConst L = cc_const(P.dim, n, P.omega);
+        d.c = L.c;
+        for (int m = 0; m < 4; ++m) d.sc[m] = L.wd[m];
     }
 }
 
@@ -295,11 +300,6 @@ void destroy(mg_ctx* c) {
     ffree(c->tail32.d);
     free_levels(c->L64);
     free_levels(c->L32);
-    for (size_t l = 0; l < c->ccn.size(); ++l) {
-        if (l > 0) ffree(c->ccu[l]);
-        ffree(c->cct[l]);
-        if (l > 0) ffree(c->ccf[l]);
-    }
     ffree(c->ccfh);
     ffree(c->cc_work);
     ffree(c->cc_mean);
@@ -363,6 +363,7 @@ void prof_end(mg_ctx* c, int step, int kind, hipStream_t s) {
 }
 
 hipError_t enqueue_norm(mg_ctx* c, hipStream_t s, int step = 0) {
+    if (c->cc) return cc_norm(c->p.dim, c->d_top, c->p.n, c->d_partial, c->d_norm, s);
     if (c->st) return st_norm(c->p.dim, c->d_top, c->p.n, c->d_partial, c->d_norm, s);
     const bool var = c->prob.var;
     const int nparts = norm_tiles(c->p.dim, c->p.n, c->top.norm);
@@ -373,13 +374,22 @@ hipError_t enqueue_norm(mg_ctx* c, hipStream_t s, int step = 0) {
     return launch_norm_finalize(c->d_partial, c->pstride, nparts, 0, 1, c->d_norm, s);
 }
 
+// Cells: the mean of the bound iterate into cc_mean.  The next sweep subtracts
+// it; without the fused norm the iterate is projected here.
+hipError_t enqueue_mean(mg_ctx* c, hipStream_t s) {
+    const GridDesc* d = c->G64[0].d;
+    const hipError_t e = cc_mean(c->p.dim, c->p.n, nullptr, d, c->cc_work, c->cc_mean, s);
+    if (e != hipSuccess || c->nrm_fused) return e;
+    return cc_subtract(c->p.dim, c->p.n, nullptr, d, c->cc_mean, s);
+}
+
 // FP64 with the fused norm: the first pre-smoothing sweep of the next cycle
 // (reads the bound u, writes its ping-pong partner, leaving u as it is) and
 // the norm of u's residual that it sums, into d_norm.  With 'step' > 0 and
 // measurement on, the sweep is bracketed and tagged (step, kernel 1).
 hipError_t enqueue_nrm_sweep(mg_ctx* c, hipStream_t s, int step = 0) {
     const TileCfg cfg = c->tl64[0].smooth_nrm;
-    const int nparts = smooth_tiles(c->p.dim, c->prob.smoother, c->p.n, cfg);
+    const int nparts = smooth_tiles(c->p.dim, c->prob.smoother, c->p.n, cfg, c->prob.op());
     const bool timed = prof_begin(c, step, s);
     hipError_t e = launch_smooth<double>(c->p.dim, c->prob.smoother, c->prob.op(), c->G64[0].d, 1, c->p.n, 0,
                                          SWEEP_NORM, cfg, s);
@@ -432,6 +442,7 @@ hipError_t enqueue_steps(mg_ctx* c, int K, double tol, int max_cycles, hipStream
             e = vcycle<double>(c->prob, c->G64, false, c->tl64, s, pev, pn, pcap, &c->tail64, c->nrm_fused);
             for (int j = n0; prof && j < c->prof_n; j += 2) c->prof_step.push_back(step), c->prof_kind.push_back(0);
             if (e != hipSuccess) return e;
+            if (c->cc && (e = enqueue_mean(c, s)) != hipSuccess) return e;
             e = c->nrm_fused ? enqueue_nrm_sweep(c, s, step) : enqueue_norm(c, s, step);
         } else {
             e = is_h16(c->p) ? vcycle<half_t>(c->prob, c->G32, true, c->tl32, s, pev, pn, pcap, &c->tail32)
@@ -512,140 +523,6 @@ int next_chunk(const double* hist, int steps, double tol, int kmax) {
     return std::max(1, std::min(kmax, (int)std::ceil(need - 1e-9)));
 }
 
-
-// ---------------------------------------------------------------------------
-// Cell-centred Neumann grids: Algorithm 1 level by level (V, W or F), plain
-// kernels; the iterate of level l is in 'cur' (the other buffer of the level
-// is the Jacobi partner).  Returns the buffer that holds the result.
-// ---------------------------------------------------------------------------
-hipError_t cc_smooth_level(mg_ctx* c, int l, double*& cur, double*& other, const double* f, CCConst L) {
-    const int dim = c->p.dim;
-    hipStream_t s = c->stream;
-    if (c->p.smoother == MG_SMOOTH_WJACOBI) {
-        hipError_t e = cc_relax(dim, true, cur, other, f, L, 0, s);
-        std::swap(cur, other);
-        return e;
-    }
-    hipError_t e = cc_relax(dim, false, cur, cur, f, L, 0, s);
-    if (e != hipSuccess) return e;
-    return cc_relax(dim, false, cur, cur, f, L, 1, s);
-}
-
-hipError_t cc_cycle(mg_ctx* c, int l, int kind, double*& cur, double*& other, const double* f) {
-    const int dim = c->p.dim, n = c->ccn[(size_t)l];
-    hipStream_t s = c->stream;
-    hipError_t e = hipSuccess;
-    if (l + 1 == (int)c->ccn.size()) return cc_fill(cur, cc_cells(dim, n), 0.0, s);  // one cell: zero correction
-    const CCConst L = cc_const(dim, n, c->p.omega);
-    for (int i = 0; i < c->p.nu1 && e == hipSuccess; ++i) e = cc_smooth_level(c, l, cur, other, f, L);
-    if (e != hipSuccess) return e;
-    double* fc = c->ccf[(size_t)l + 1];
-    e = cc_restrict(dim, cur, f, fc, L, s);
-    if (e != hipSuccess) return e;
-    double* ucur = c->ccu[(size_t)l + 1];
-    double* uoth = c->cct[(size_t)l + 1];
-    e = cc_fill(ucur, cc_cells(dim, n / 2), 0.0, s);
-    if (e != hipSuccess) return e;
-    if (kind == MG_CYCLE_V) {
-        e = cc_cycle(c, l + 1, MG_CYCLE_V, ucur, uoth, fc);
-    } else if (kind == MG_CYCLE_W) {
-        e = cc_cycle(c, l + 1, MG_CYCLE_W, ucur, uoth, fc);
-        if (e == hipSuccess) e = cc_cycle(c, l + 1, MG_CYCLE_W, ucur, uoth, fc);
-    } else {
-        e = cc_cycle(c, l + 1, MG_CYCLE_F, ucur, uoth, fc);
-        if (e == hipSuccess) e = cc_cycle(c, l + 1, MG_CYCLE_V, ucur, uoth, fc);
-    }
-    if (e != hipSuccess) return e;
-    // the coarse buffers keep their roles for the next cycle
-    c->ccu[(size_t)l + 1] = ucur;
-    c->cct[(size_t)l + 1] = uoth;
-    e = cc_prolong(dim, cur, ucur, n, s);
-    for (int i = 0; i < c->p.nu2 && e == hipSuccess; ++i) e = cc_smooth_level(c, l, cur, other, f, L);
-    return e;
-}
-
-// One cycle on the caller's u (level 0), the result back in u.
-hipError_t cc_cycle_top(mg_ctx* c, double* u, const double* f) {
-    double* cur = u;
-    double* other = c->cct[0];
-    hipError_t e = cc_cycle(c, 0, c->p.cycle, cur, other, f);
-    if (e == hipSuccess && cur != u)
-        e = hipMemcpyAsync(u, cur, cc_cells(c->p.dim, c->p.n) * sizeof(double), hipMemcpyDeviceToDevice, c->stream);
-    return e;
-}
-
-int cc_setup(mg_ctx* c) {
-    const int dim = c->p.dim;
-    hipStream_t s = c->stream;
-    c->cc = true;
-    for (int m = c->p.n; m >= 1; m /= 2) c->ccn.push_back(m);
-    const size_t L = c->ccn.size();
-    c->ccu.assign(L, nullptr);
-    c->cct.assign(L, nullptr);
-    c->ccf.assign(L, nullptr);
-    for (size_t l = 0; l < L; ++l) {
-        const size_t bytes = cc_cells(dim, c->ccn[l]) * sizeof(double);
-        if (l > 0) CK(zalloc((void**)&c->ccu[l], bytes, s));
-        CK(zalloc((void**)&c->cct[l], bytes, s));
-        if (l > 0) CK(zalloc((void**)&c->ccf[l], bytes, s));
-    }
-    CK(zalloc((void**)&c->ccfh, cc_cells(dim, c->p.n) * sizeof(double), s));
-    CK(hipMalloc((void**)&c->cc_work, cc_work_doubles(dim, c->p.n) * sizeof(double)));
-    CK(hipMalloc((void**)&c->cc_mean, sizeof(double)));
-    c->nlev = (int)L;
-    c->pstride = cc_norm_parts(dim, c->p.n);
-    CK(hipMalloc((void**)&c->d_partial, sizeof(double) * (size_t)c->pstride));
-    CK(hipMalloc((void**)&c->d_norm, sizeof(double)));
-    CK(hipMalloc((void**)&c->d_norm0, sizeof(double)));
-    CK(hipMalloc((void**)&c->d_ctrl, 3 * sizeof(int)));
-    CK(launch_fill_int(c->d_ctrl, 0, 3, s));
-    int r = ensure_hist(c, 64);
-    if (r != MG_OK) return r;
-    CK(hipStreamSynchronize(s));
-    return MG_OK;
-}
-
-int cc_solve(mg_ctx* c, double* u, const double* f, double tol, int max_cycles, int* cycles_done, double* res_hist) {
-    const int dim = c->p.dim, n = c->p.n;
-    hipStream_t s = c->stream;
-    const CCConst L0 = cc_const(dim, n, c->p.omega);
-    int r = ensure_hist(c, max_cycles + 1);
-    if (r != MG_OK) return r;
-    CK(hipMemcpyAsync(c->ccfh, f, cc_cells(dim, n) * sizeof(double), hipMemcpyDeviceToDevice, s));
-    CK(cc_remove_mean(dim, n, c->ccfh, c->cc_work, c->cc_mean, s));
-    CK(cc_remove_mean(dim, n, u, c->cc_work, c->cc_mean, s));
-    CK(launch_fill_int(ctl_done(c), 0, 1, s));
-    CK(cc_norm(dim, u, c->ccfh, L0, c->d_partial, c->d_norm, s));
-    CK(launch_solve_init(c->d_norm, c->d_norm0, ctl_done(c), ctl_steps(c), ctl_status(c), c->d_hist, c->hist_cap, 1,
-                         s));
-    int* ctl = (int*)c->h_pin;
-    CK(hipMemcpyAsync(ctl, c->d_ctrl, 3 * sizeof(int), hipMemcpyDeviceToHost, s));
-    CK(hipStreamSynchronize(s));
-    int steps = 0;
-    // one cycle per round trip: the host keeps the Jacobi buffer roles, so no
-    // cycle is queued past the stop test
-    while (!ctl[0] && steps < max_cycles) {
-        CK(cc_cycle_top(c, u, c->ccfh));
-        CK(cc_remove_mean(dim, n, u, c->cc_work, c->cc_mean, s));
-        CK(cc_norm(dim, u, c->ccfh, L0, c->d_partial, c->d_norm, s));
-        CK(launch_stop_test(c->d_norm, c->d_norm0, ctl_done(c), ctl_steps(c), ctl_status(c), c->d_hist, c->hist_cap,
-                            tol, max_cycles, 1, s));
-        CK(hipMemcpyAsync(ctl, c->d_ctrl, 3 * sizeof(int), hipMemcpyDeviceToHost, s));
-        CK(hipStreamSynchronize(s));
-        ++steps;
-    }
-    steps = ctl[1];
-    const int status = ctl[2];
-    if (res_hist) {
-        CK(hipMemcpyAsync(c->h_pin, c->d_hist, sizeof(double) * (size_t)(steps + 1), hipMemcpyDeviceToHost, s));
-        CK(hipStreamSynchronize(s));
-        std::memcpy(res_hist, c->h_pin, sizeof(double) * (size_t)(steps + 1));
-    }
-    if (cycles_done) *cycles_done = steps;
-    if (status == 0) return MG_OK;
-    if (status == -5) return MG_EDIVERGED;
-    return MG_ENOTCONV;
-}
 
 // ---------------------------------------------------------------------------
 // Complex diffusion: FAS level by level.
@@ -1257,16 +1134,6 @@ int mg_setup(const mg_params* p, void* stream, mg_ctx** out) {
     c->p = *p;
     if (c->p.omega <= 0.0) c->p.omega = p->smoother == MG_SMOOTH_WJACOBI ? 0.8 : 1.0;
     c->stream = (hipStream_t)stream;
-    if (p->bc == MG_BC_NEUMANN_CC) {
-        (void)hipGetDevice(&c->device);
-        const int r = cc_setup(c);
-        if (r != MG_OK) {
-            destroy(c);
-            return r;
-        }
-        *out = c;
-        return MG_OK;
-    }
     c->use_graphs = std::getenv("MG_NO_GRAPHS") == nullptr;
     (void)hipGetDevice(&c->device);
     const int dim = p->dim;
@@ -1277,11 +1144,13 @@ int mg_setup(const mg_params* p, void* stream, mg_ctx** out) {
         for (int q = 0; q < 2 * dim + 1; ++q) c->prob.sc[q] = p->stencil[q];
         c->p.stencil = nullptr;  // the context keeps its own copy
     }
+    c->cc = c->prob.cc = p->bc == MG_BC_NEUMANN_CC;
     c->prob.sym = p->smoother == MG_SMOOTH_RBGS_SYM;
     c->prob.cycle = p->cycle;
     c->prob.cg_iters = p->cg_iters;
     const int coarse_n = p->coarse_n > 3 ? p->coarse_n : 3;
-    for (int m = p->n;; m = (m - 1) / 2 + 1) {
+    for (int m = p->n; c->cc && m >= 1; m /= 2) c->n.push_back(m);
+    for (int m = p->n; !c->cc; m = (m - 1) / 2 + 1) {
         c->n.push_back(m);
         if (m <= coarse_n) break;
     }
@@ -1299,7 +1168,7 @@ int mg_setup(const mg_params* p, void* stream, mg_ctx** out) {
     const char* at = std::getenv("MG_AUTOTUNE");
     // a constant stencil keeps the heuristic geometry: tuning its levels takes 40 .. 1000 ms at setup (against
     // 1 ms) and gains 5 % of a solve at 129^3 and 257^3, 19 % at 4097^2
-    c->autotune = !(at && at[0] == '0') && !c->st;
+    c->autotune = !(at && at[0] == '0') && !c->st && !c->cc;
     hipStream_t s = c->stream;
     const size_t N = npts(dim, p->n);
     hipError_t e = hipSuccess;
@@ -1317,6 +1186,11 @@ int mg_setup(const mg_params* p, void* stream, mg_ctx** out) {
     }
     SETUP_CK(hipMalloc((void**)&c->d_ctrl, 3 * sizeof(int)));
     SETUP_CK(launch_fill_int(c->d_ctrl, 0, 3, s));
+    if (c->cc) {
+        SETUP_CK(zalloc((void**)&c->ccfh, N * sizeof(double), s));
+        SETUP_CK(hipMalloc((void**)&c->cc_work, cc_work_doubles(dim, p->n) * sizeof(double)));
+        SETUP_CK(hipMalloc((void**)&c->cc_mean, sizeof(double)));
+    }
     if (p->precision == MG_PREC_FP64) {
         SETUP_CK(build_levels(c->L64, dim, c->n, 8, false, c->k64, s));
         SETUP_CK(build_faces(c->L64, s));
@@ -1372,19 +1246,24 @@ int mg_setup(const mg_params* p, void* stream, mg_ctx** out) {
                    std::getenv("MG_NO_FUSED_NORM") == nullptr;
     if (c->nrm_fused) {
         const int sm = c->prob.smoother;
-        int cap = smooth_tiles(dim, sm, p->n, c->tl64[0].smooth_nrm);
-        for (TileCfg t : tune_candidates(dim, p->n - 2, true, 0, 8, c->prob.var))
-            if (t.wv != 1) cap = std::max(cap, smooth_tiles(dim, sm, p->n, t));
+        int cap = smooth_tiles(dim, sm, p->n, c->tl64[0].smooth_nrm, c->prob.op());
+        if (c->autotune)
+            for (TileCfg t : tune_candidates(dim, p->n - 2, true, 0, 8, c->prob.var))
+                if (t.wv != 1) cap = std::max(cap, smooth_tiles(dim, sm, p->n, t));
         c->spart_cap = cap;
         SETUP_CK(hipMalloc((void**)&c->d_spart, sizeof(double) * (size_t)cap));
         GridDesc& d0 = c->G64[0].h[0];
         d0.npart = c->d_spart;
+        d0.mean = c->cc_mean;
         SETUP_CK(hipMemcpyAsync(c->G64[0].d, &d0, sizeof(GridDesc), hipMemcpyHostToDevice, s));
     }
     if (c->autotune) SETUP_CK(autotune(c));
-    if (c->nrm_fused && smooth_tiles(dim, c->prob.smoother, p->n, c->tl64[0].smooth_nrm) > c->spart_cap)
+    if (c->nrm_fused &&
+        smooth_tiles(dim, c->prob.smoother, p->n, c->tl64[0].smooth_nrm, c->prob.op()) > c->spart_cap)
         c->nrm_fused = false;
-    c->pstride = c->st ? st_norm_parts(dim, p->n) : std::max(1, norm_tiles(dim, p->n, c->top.norm));
+    c->pstride = c->st   ? st_norm_parts(dim, p->n)
+                 : c->cc ? cc_norm_parts(dim, p->n)
+                         : std::max(1, norm_tiles(dim, p->n, c->top.norm));
     SETUP_CK(hipMalloc((void**)&c->d_partial, sizeof(double) * (size_t)c->pstride));
     if (is_h16(c->p)) {
         SETUP_CK(hipMalloc((void**)&c->d_pmax, sizeof(double) * (size_t)c->pstride));
@@ -1393,7 +1272,7 @@ int mg_setup(const mg_params* p, void* stream, mg_ctx** out) {
     }
     SETUP_CK(hipMalloc((void**)&c->d_norm, sizeof(double)));
     SETUP_CK(hipMalloc((void**)&c->d_norm0, sizeof(double)));
-    if (!c->st) c->prof_ev.resize(512);
+    if (!c->st && !c->cc) c->prof_ev.resize(512);
     for (auto& ev : c->prof_ev) SETUP_CK(hipEventCreate(&ev));
     int r = ensure_hist(c, 64);
     if (r != MG_OK) {
@@ -1454,11 +1333,6 @@ int mg_vcycle(mg_ctx* c, double* u, const double* f) {
     if (!c) return MG_EINVAL;
     if (is_batch_handle(c)) return MG_EINVAL;
     if (c->cd) return MG_EINVAL;  // complex-diffusion handles take the mg_cdiff_* calls
-    if (c->cc) {
-        if (!u || !f) return MG_EINVAL;
-        CK(cc_cycle_top(c, u, f));
-        return MG_OK;
-    }
     int r = bind(c, u, f);
     if (r != MG_OK) return r;
     CK(launch_fill_int(ctl_done(c), 0, 1, c->stream));
@@ -1479,14 +1353,6 @@ int mg_residual_norm(mg_ctx* c, const double* u, const double* f, double* out) {
     if (!c || !out) return MG_EINVAL;
     if (is_batch_handle(c)) return MG_EINVAL;
     if (c->cd) return MG_EINVAL;  // complex-diffusion handles take the mg_cdiff_* calls
-    if (c->cc) {
-        if (!u || !f) return MG_EINVAL;
-        CK(cc_norm(c->p.dim, u, f, cc_const(c->p.dim, c->p.n, c->p.omega), c->d_partial, c->d_norm, c->stream));
-        CK(hipMemcpyAsync(c->h_pin, c->d_norm, sizeof(double), hipMemcpyDeviceToHost, c->stream));
-        CK(hipStreamSynchronize(c->stream));
-        *out = c->h_pin[0];
-        return MG_OK;
-    }
     int r = bind(c, u, f);
     if (r != MG_OK) return r;
     CK(enqueue_norm(c, c->stream));
@@ -1500,21 +1366,24 @@ int mg_solve(mg_ctx* c, double* u, const double* f, double tol, int max_cycles, 
     if (!c || max_cycles < 0 || !(tol >= 0.0)) return MG_EINVAL;
     if (is_batch_handle(c)) return MG_EINVAL;
     if (c->cd) return MG_EINVAL;  // complex-diffusion handles take the mg_cdiff_* calls
-    if (c->cc) {
+    hipStream_t s = c->stream;
+    if (c->cc) {  // the compatible right-hand side: f minus its mean
         if (!u || !f) return MG_EINVAL;
-        return cc_solve(c, u, f, tol, max_cycles, cycles_done, res_hist);
+        CK(hipMemcpyAsync(c->ccfh, f, npts(c->p.dim, c->p.n) * sizeof(double), hipMemcpyDeviceToDevice, s));
+        CK(cc_remove_mean(c->p.dim, c->p.n, c->ccfh, c->cc_work, c->cc_mean, s));
+        f = c->ccfh;
     }
     int r = bind(c, u, f);
     if (r != MG_OK) return r;
     r = ensure_hist(c, max_cycles + 1);
     if (r != MG_OK) return r;
-    hipStream_t s = c->stream;
     const bool ir = is_ir(c->p);
     c->prof_n = 0;  // measured launches are tagged per solve
     c->prof_step.clear();
     c->prof_kind.clear();
     // rho_0 (clear the stop flag a previous solve left set first: every kernel honours it)
     CK(launch_fill_int(ctl_done(c), 0, 1, s));
+    if (c->cc) CK(enqueue_mean(c, s));
     if (ir) CK(enqueue_ir_start(c, s));
     else if (c->nrm_fused) CK(enqueue_nrm_sweep(c, s));
     else CK(enqueue_norm(c, s));
@@ -1545,6 +1414,8 @@ int mg_solve(mg_ctx* c, double* u, const double* f, double tol, int max_cycles, 
         status = ((int*)c->h_pin)[2];
         K = next_chunk(c->h_pin + 2, steps, tol, kmax);
     }
+    // cells: the sweeps that summed the norms subtracted the mean on the way, u still has it
+    if (c->cc && c->nrm_fused) CK(cc_subtract(c->p.dim, c->p.n, u, nullptr, c->cc_mean, s));
     CK(hipMemcpyAsync(c->h_pin, c->d_ctrl, 3 * sizeof(int), hipMemcpyDeviceToHost, s));
     CK(hipStreamSynchronize(s));
     steps = ((int*)c->h_pin)[1];
@@ -1582,7 +1453,7 @@ int mg_solve(mg_ctx* c, double* u, const double* f, double tol, int max_cycles, 
 int mg_prof_enable(mg_ctx* c, int on) {
     if (!c) return MG_EINVAL;
     if (is_batch_handle(c)) return MG_EINVAL;
-    c->prof_on = on != 0 && !c->st;
+    c->prof_on = on != 0 && !c->st && !c->cc;
     c->prof_n = 0;
     c->prof_step.clear();
     c->prof_kind.clear();
@@ -1822,9 +1693,9 @@ int mg_level_prolong_correct(int dim, int n, int dtype, void* u, const void* ec,
     GridDesc* d = nullptr;
     int r = with_desc(h, s, &d);
     if (r != MG_OK) return r;
-    hipError_t e = elem == 8   ? launch_prolong<double>(dim, d, 1, n, 0, s)
-                   : elem == 4 ? launch_prolong<float>(dim, d, 1, n, 0, s)
-                               : launch_prolong<half_t>(dim, d, 1, n, 0, s);
+    hipError_t e = elem == 8   ? launch_prolong<double>(dim, OP_LAP, d, 1, n, 0, s)
+                   : elem == 4 ? launch_prolong<float>(dim, OP_LAP, d, 1, n, 0, s)
+                               : launch_prolong<half_t>(dim, OP_LAP, d, 1, n, 0, s);
     return finish_desc(d, s, e);
 }
 

@@ -41,9 +41,10 @@ inline int max_tile_rows(int dim, int elem, bool var, int family, int wv = 4) {
 
 enum Smoother { SM_RBGS = 0, SM_JACOBI = 1 };
 
-// Operators of the node-based kernels: the Laplacian, nodal coefficients, a
-// constant stencil (GridDesc::sc).
-enum Op { OP_LAP = 0, OP_VAR = 1, OP_STENCIL = 2 };
+// Operators of the kernels: on nodes the Laplacian, nodal coefficients, a
+// constant stencil (GridDesc::sc); on cells with a Neumann boundary the
+// Laplacian (its weights wd[0 .. 3] by boundary faces in GridDesc::sc).
+enum Op { OP_LAP = 0, OP_VAR = 1, OP_STENCIL = 2, OP_CC = 3 };
 
 // Kernel flags for the smoothing sweep.
 enum SweepFlags {
@@ -76,7 +77,9 @@ struct GridDesc {
     double omega;     // smoother weight
     double* npart;    // SWEEP_NORM: per-workgroup partial sums of r^2 (as many as the launch has
                       // workgroups in x), or null
-    double sc[7];     // OP_STENCIL: centre, -x, +x, -y, +y[, -z, +z] (times c)
+    double sc[7];     // OP_STENCIL: centre, -x, +x, -y, +y[, -z, +z] (times c); OP_CC: wd[m] of a cell
+                      // with m boundary faces
+    const double* mean;  // OP_CC: SWEEP_NORM sweeps and the norm pass subtract it from u, or null
 };
 
 // FP64 refinement pass of one grid: u_out = u_in + e (inner nodes),
@@ -102,7 +105,7 @@ struct IRDesc {
 
 // Coarse tail of a V-cycle for one instance: its levels from the tail's finest
 // (lv[0], edge at most tail_max_edge) down to n = 3, run by one workgroup.
-constexpr int kMaxTailLevels = 6;
+constexpr int kMaxTailLevels = 7;
 struct TailDesc {
     GridDesc lv[kMaxTailLevels];
     int nlev;
@@ -127,7 +130,7 @@ constexpr int SEL_BLACK_FIRST = 4;
 inline int sweep_arg(int sel, const TileCfg& c) { return (sel & (1 | SEL_BLACK_FIRST)) | (c.order ? 2 : 0); }
 
 // Number of workgroups in x for a level of n nodes per axis (one instance).
-int smooth_tiles(int dim, int sm, int n, TileCfg cfg);
+int smooth_tiles(int dim, int sm, int n, TileCfg cfg, int op = OP_LAP);
 int restrict_tiles(int dim, int nf, TileCfg cfg);
 int smooth_restrict_tiles(int nf, TileCfg cfg);
 int smooth2_tiles(int n, TileCfg cfg);
@@ -174,7 +177,7 @@ template <typename T>
 hipError_t launch_restrict(int dim, int op, const GridDesc* d, int ninst, int nf, int sel, TileCfg cfg,
                            hipStream_t s);
 template <typename T>
-hipError_t launch_prolong(int dim, const GridDesc* d, int ninst, int nf, int sel, hipStream_t s);
+hipError_t launch_prolong(int dim, int op, const GridDesc* d, int ninst, int nf, int sel, hipStream_t s);
 // Largest tail edge for a dimension, word size and operator (levels at or
 // below it can run in the single-workgroup tail kernel).
 int tail_max_edge(int dim, int elem, int op);

@@ -521,6 +521,17 @@ hipError_t launch_smooth3d(int sm, int op, const GridDesc* d, int sel, int flags
         }
     }
     if constexpr (sizeof(T) == 8) {
+        if (op == OP_CC && sm == SM_RBGS && cfg.wv == 1 && cfg.by == 8) {
+            const int arg = sweep_arg(sel, cfg);
+            switch (flags) {
+                case 0: k_smooth3d_rb<T, OP_CC, 8, 0><<<grid, 64, 0, s>>>(d, arg, cfg.zchunk); break;
+                case SWEEP_ZERO_GUESS: k_smooth3d_rb<T, OP_CC, 8, SWEEP_ZERO_GUESS><<<grid, 64, 0, s>>>(d, arg, cfg.zchunk); break;
+                case SWEEP_PROLONG: k_smooth3d_rb<T, OP_CC, 8, SWEEP_PROLONG><<<grid, 64, 0, s>>>(d, arg, cfg.zchunk); break;
+                case SWEEP_NORM: k_smooth3d_rb<T, OP_CC, 8, SWEEP_NORM><<<grid, 64, 0, s>>>(d, arg, cfg.zchunk); break;
+                default: return hipErrorInvalidValue;
+            }
+            return hipSuccess;
+        }
         if (op == OP_STENCIL) {
             if (sm == SM_RBGS) MG_FL(SM_RBGS, OP_STENCIL) else MG_FL(SM_JACOBI, OP_STENCIL)
         }

@@ -79,7 +79,8 @@ struct Problem {
     int cycle = 0;      // 0 V, 1 W, 2 F (Algorithm 1 with one / two recursive calls; F: F then V)
     bool stencil = false;  // a constant stencil (FP64), coefficients sc
     double sc[7] = {0, 0, 0, 0, 0, 0, 0};
-    int op() const { return stencil ? OP_STENCIL : (var ? OP_VAR : OP_LAP); }
+    bool cc = false;  // cells with a Neumann boundary (FP64)
+    int op() const { return cc ? OP_CC : stencil ? OP_STENCIL : (var ? OP_VAR : OP_LAP); }
     int cg_iters = 0;   // conjugate-gradient steps on a coarsest level with n > 3 (0: 4 (n - 1))
 };
 
@@ -177,14 +178,11 @@ struct mg_ctx {
     std::vector<ChunkGraph> graphs;
 
     // cell-centred Neumann grid (bc MG_BC_NEUMANN_CC): levels n, n/2, ..., 1 cells
-    // per axis; level 0's iterate is the caller's, its right-hand side the
-    // context's mean-zero copy ccfh
+    // per axis; a solve's right-hand side is the context's mean-zero copy ccfh
     bool cc = false;
-    std::vector<int> ccn;
-    std::vector<double*> ccu, cct, ccf;
     double* ccfh = nullptr;
     double* cc_work = nullptr;  // fixed-order sums (row and plane sums)
-    double* cc_mean = nullptr;  // [1]
+    double* cc_mean = nullptr;  // [1] mean of the cycle's result, subtracted by the next sweep
 
     // complex diffusion (mg_cdiff_setup): its level hierarchy
     struct CDState* cd = nullptr;

@@ -4,6 +4,7 @@
 #include <cstdlib>
 #include <cstring>
 
+#include "mg_cc.h"
 #include "mg_solver.h"
 
 namespace mg {
@@ -57,6 +58,13 @@ Tiles lds_tiles(int dim, int n, int smoother) {
 }
 
 Tiles default_tiles(int dim, int elem_bytes, int n, int smoother, int op) {
+    if (op == OP_CC) {  // edges down to one cell
+        Tiles t;
+        if (dim == 2) t.smooth = {n <= 512 ? 8 : 16, 1};
+        else t.smooth = {8, std::min(32, std::max(2, n / 16)), 1, 1};
+        t.smooth_zg = t.smooth_pro = t.smooth_nrm = t.smooth;
+        return t;
+    }
     Tiles t = lds_tiles(dim, n, smoother);
     if (dim == 3 && smoother == SM_RBGS && op != OP_VAR) {
         // One wavefront per 64 x 8 tile, nodes held by colour: measured against
@@ -77,6 +85,10 @@ Tiles default_tiles(int dim, int elem_bytes, int n, int smoother, int op) {
 template <typename T>
 hipError_t launch_smooth(int dim, int sm, int op, const GridDesc* d, int ninst, int n, int sel, int flags,
                          TileCfg cfg, hipStream_t s) {
+    if (op == OP_CC) {
+        if constexpr (sizeof(T) == 8) return cc_launch_smooth(dim, sm, d, ninst, n, sel, flags, cfg, s);
+        return hipErrorInvalidValue;
+    }
     if (n < 5 || ninst <= 0) return hipErrorInvalidValue;
     if ((flags & SWEEP_NORM) && ninst != 1) return hipErrorInvalidValue;  // one partial row
     const dim3 grid(smooth_tiles(dim, sm, n, cfg), ninst);
@@ -119,7 +131,7 @@ struct Prof {
 
 int tail_first_level(int dim, int elem, int op, const std::vector<int>& n, bool zero_top) {
     if (std::getenv("MG_NO_TAIL")) return -1;
-    if (n.empty() || n.back() != 3) return -1;  // the tail ends in the exact 3-node solve
+    if (n.empty() || n.back() != (op == OP_CC ? 1 : 3)) return -1;  // the tail ends in the exact coarsest solve
     const int tmax = tail_max_edge(dim, elem, op);
     for (int l = zero_top ? 0 : 1; l < (int)n.size(); ++l)
         if (n[(size_t)l] <= tmax && (int)n.size() - l <= kMaxTailLevels) return l;
@@ -130,6 +142,7 @@ int tail_first_level(int dim, int elem, int op, const std::vector<int>& n, bool 
 // gradients (n > 3), from a zero iterate.
 template <typename T>
 hipError_t coarse_solve(const Problem& P, const Group& g, hipStream_t s) {
+    if (P.cc) return launch_zero_u<T>(P.dim, g.d, g.ninst, g.n, s);  // one cell: zero correction
     if (g.n == 3) return launch_coarsest<T>(P.dim, P.op(), g.d, g.ninst, s);
     return launch_cg<T>(P.dim, P.var, g.d, g.ninst, g.n, P.cg_iters > 0 ? P.cg_iters : 4 * (g.n - 1), s);
 }
@@ -211,7 +224,7 @@ hipError_t cycle_rec(const Problem& P, const std::vector<Group>& G, int l, int k
         MG_TRY(cycle_rec<T>(P, G, l + 1, 0, false, tiles, s, prof, tail));
     }
     const bool fuse = P.nu2 > 0;
-    if (!fuse) MG_TRY(launch_prolong<T>(dim, g.d, g.ninst, g.n, cur, s));
+    if (!fuse) MG_TRY(launch_prolong<T>(dim, P.op(), g.d, g.ninst, g.n, cur, s));
     for (int i = 0; i < P.nu2; ++i) {
         const int flags = (i == 0 && fuse) ? SWEEP_PROLONG : 0;
         const bool timed = l == 0 && flags == 0;
@@ -292,7 +305,7 @@ hipError_t vcycle(const Problem& P, const std::vector<Group>& G, bool zero_top, 
         const Group& g = G[(size_t)l];
         int cur = sel[(size_t)l];
         const bool fuse = P.nu2 > 0;  // the first post-sweep adds P uc while loading
-        if (!fuse) MG_TRY(launch_prolong<T>(dim, g.d, g.ninst, g.n, cur, s));
+        if (!fuse) MG_TRY(launch_prolong<T>(dim, P.op(), g.d, g.ninst, g.n, cur, s));
         int i0 = 0;
         if (cur == 1 && post2_ok<T>(P, dim, tiles[(size_t)l])) {
             // post-sweeps 1 and 2 (correction in the first), t -> u

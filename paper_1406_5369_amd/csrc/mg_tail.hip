@@ -35,6 +35,7 @@
 // solve takes 10.6 ms (61.6 ms with every level's steps launched apart).  One
 // copy of the code with run-time geometry was slower again (27.6 us): the
 // address arithmetic costs more than the cold instruction cache.
+#include "mg_cc.h"
 #include "mg_kern.h"
 
 namespace mg {
@@ -598,6 +599,7 @@ __global__ __launch_bounds__(TNT) void k_cg(const GridDesc* __restrict__ descs, 
 // coefficients (a 65 x 65 FP64 tail takes 125 KB, with faces it would take
 // 217).
 int tail_max_edge(int dim, int elem, int op) {
+    if (op == OP_CC) return cc_tail_max_edge(dim);
     const bool big = elem <= 4 || op != OP_VAR;
     return dim == 2 ? (big ? 65 : 33) : (big ? 17 : 9);
 }
@@ -611,6 +613,7 @@ template <typename T>
 hipError_t launch_tail(int dim, int sm, int op, const TailDesc* d, int ninst, int nu1, int nu2, int post_first,
                        int kind, bool zero, hipStream_t s) {
     if (ninst <= 0) return hipSuccess;
+    if (op == OP_CC) return cc_launch_tail(dim, sm, d, ninst, nu1, nu2, post_first, kind, zero, s);
     constexpr bool F = sizeof(arith_t<T>) == 4;
     const int z = zero ? 1 : 0;
 #define MG_TAIL(DIMV, OPV, CMV)                                                                                \

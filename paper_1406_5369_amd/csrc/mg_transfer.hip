@@ -1,4 +1,5 @@
 // Residual + full-weighting restriction, interpolation + correction, coarsest solve, copies.
+#include "mg_cc.h"
 #include "mg_kern.h"
 
 namespace mg {
@@ -436,10 +437,12 @@ __global__ __launch_bounds__(NT) void k_copy_bytes(uint4* __restrict__ dst, cons
 
 }  // namespace
 
-int smooth_tiles(int dim, int sm, int n, TileCfg cfg) {
+int smooth_tiles(int dim, int sm, int n, TileCfg cfg, int op) {
+    if (op == OP_CC && sm == SM_JACOBI)  // one cell per thread
+        return (int)(((dim == 2 ? (size_t)n * n : (size_t)n * n * n) + NT - 1) / NT);
     const int H = sm == SM_RBGS ? 2 : 1;
     const int TX = BX - 2 * H, TY = cfg.by - 2 * H;
-    const int m = n - 2;
+    const int m = op == OP_CC ? n : n - 2;
     if (dim == 2) return cdiv(m, TX) * cdiv(m, TY);
     return cdiv(m, TX) * cdiv(m, TY) * nzchunks(m, cfg.zchunk);
 }
@@ -508,6 +511,7 @@ hipError_t launch_coarsest_op(int dim, const GridDesc* d, int ninst, hipStream_t
 template <typename T>
 hipError_t launch_restrict(int dim, int op, const GridDesc* d, int ninst, int nf, int sel, TileCfg cfg,
                            hipStream_t s) {
+    if (op == OP_CC) return cc_launch_restrict(dim, d, ninst, nf, sel, s);
     if (nf < 5 || ninst <= 0) return hipErrorInvalidValue;
     const dim3 grid(restrict_tiles(dim, nf, cfg), ninst);
     if (op == OP_LAP) return launch_restrict_op<T, OP_LAP>(dim, d, sel, cfg, grid, s);
@@ -521,7 +525,8 @@ hipError_t launch_restrict(int dim, int op, const GridDesc* d, int ninst, int nf
 }
 
 template <typename T>
-hipError_t launch_prolong(int dim, const GridDesc* d, int ninst, int nf, int sel, hipStream_t s) {
+hipError_t launch_prolong(int dim, int op, const GridDesc* d, int ninst, int nf, int sel, hipStream_t s) {
+    if (op == OP_CC) return cc_launch_prolong(dim, d, ninst, nf, sel, s);
     const int m = nf - 2;
     const int rows = dim == 2 ? m : m * m;
     const dim3 grid(cdiv(rows, NT / 64), ninst);
@@ -569,7 +574,7 @@ hipError_t launch_copy_bytes(void* dst, const void* src, size_t bytes, hipStream
 
 #define MG_INST(T)                                                                                              \
     template hipError_t launch_restrict<T>(int, int, const GridDesc*, int, int, int, TileCfg, hipStream_t);    \
-    template hipError_t launch_prolong<T>(int, const GridDesc*, int, int, int, hipStream_t);                    \
+    template hipError_t launch_prolong<T>(int, int, const GridDesc*, int, int, int, hipStream_t);                    \
     template hipError_t launch_coarsest<T>(int, int, const GridDesc*, int, hipStream_t);                       \
     template hipError_t launch_copy_t_to_u<T>(int, const GridDesc*, int, int, hipStream_t);                     \
     template hipError_t launch_zero_u<T>(int, const GridDesc*, int, int, hipStream_t);                       \
