@@ -481,10 +481,9 @@ struct Engine {
             e = launch_ir_update(dim, false, g.d, g.cnt, g.n, 0, 0, d_partial, pstride, tiles[(size_t)g.a].norm, q);
             if (e != hipSuccess) return e;
         }
-        e = launch_norm_finalize_rows(d_partial, pstride, d_nparts, d_rows, (int)h_rows.size(), d_norm, q);
-        if (e != hipSuccess) return e;
-        return launch_stop_test(d_norm, d_norm0, d_done, d_steps, d_status, nullptr, 0, tol, max_steps, cap, q,
-                                d_par);
+        const StopTest stop{d_norm0, d_done, d_steps, d_status, nullptr, 0, max_steps, tol};
+        return launch_norm_finalize_rows(d_partial, pstride, d_nparts, d_rows, (int)h_rows.size(), d_norm, q, &stop,
+                                         d_par);
     }
 
     int run_chunk(int K, double tol, int max_steps, bool use_graph) {

@@ -315,7 +315,6 @@ void destroy(mg_ctx* c) {
     ffree(c->d_norm);
     ffree(c->d_norm0);
     ffree(c->d_ctrl);
-    ffree(c->d_hist);
     if (c->h_pin) (void)hipHostFree(c->h_pin);
     for (auto e : c->prof_ev) (void)hipEventDestroy(e);
     delete c;
@@ -362,16 +361,16 @@ void prof_end(mg_ctx* c, int step, int kind, hipStream_t s) {
     c->prof_kind.push_back(kind);
 }
 
-hipError_t enqueue_norm(mg_ctx* c, hipStream_t s, int step = 0) {
-    if (c->cc) return cc_norm(c->p.dim, c->d_top, c->p.n, c->d_partial, c->d_norm, s);
-    if (c->st) return st_norm(c->p.dim, c->d_top, c->p.n, c->d_partial, c->d_norm, s);
+hipError_t enqueue_norm(mg_ctx* c, hipStream_t s, int step = 0, const StopTest* stop = nullptr) {
+    if (c->cc) return cc_norm(c->p.dim, c->d_top, c->p.n, c->d_partial, c->d_norm, s, stop);
+    if (c->st) return st_norm(c->p.dim, c->d_top, c->p.n, c->d_partial, c->d_norm, s, stop);
     const bool var = c->prob.var;
     const int nparts = norm_tiles(c->p.dim, c->p.n, c->top.norm);
     const bool timed = prof_begin(c, step, s);
     hipError_t e = launch_norm(c->p.dim, var, c->d_top, 1, c->p.n, 0, c->d_partial, c->pstride, c->top.norm, s);
     if (timed) prof_end(c, step, 1, s);
     if (e != hipSuccess) return e;
-    return launch_norm_finalize(c->d_partial, c->pstride, nparts, 0, 1, c->d_norm, s);
+    return launch_norm_finalize(c->d_partial, c->pstride, nparts, 0, 1, c->d_norm, s, stop);
 }
 
 // Cells: the mean of the bound iterate into cc_mean.  The next sweep subtracts
@@ -387,7 +386,7 @@ hipError_t enqueue_mean(mg_ctx* c, hipStream_t s) {
 // (reads the bound u, writes its ping-pong partner, leaving u as it is) and
 // the norm of u's residual that it sums, into d_norm.  With 'step' > 0 and
 // measurement on, the sweep is bracketed and tagged (step, kernel 1).
-hipError_t enqueue_nrm_sweep(mg_ctx* c, hipStream_t s, int step = 0) {
+hipError_t enqueue_nrm_sweep(mg_ctx* c, hipStream_t s, int step = 0, const StopTest* stop = nullptr) {
     const TileCfg cfg = c->tl64[0].smooth_nrm;
     const int nparts = smooth_tiles(c->p.dim, c->prob.smoother, c->p.n, cfg, c->prob.op());
     const bool timed = prof_begin(c, step, s);
@@ -395,10 +394,10 @@ hipError_t enqueue_nrm_sweep(mg_ctx* c, hipStream_t s, int step = 0) {
                                          SWEEP_NORM, cfg, s);
     if (timed) prof_end(c, step, 1, s);
     if (e != hipSuccess) return e;
-    return launch_norm_finalize(c->d_spart, nparts, nparts, 0, 1, c->d_norm, s);
+    return launch_norm_finalize(c->d_spart, nparts, nparts, 0, 1, c->d_norm, s, stop);
 }
 
-hipError_t enqueue_ir(mg_ctx* c, int sel, int flags, hipStream_t s, int step = 0) {
+hipError_t enqueue_ir(mg_ctx* c, int sel, int flags, hipStream_t s, int step = 0, const StopTest* stop = nullptr) {
     const int nparts = norm_tiles(c->p.dim, c->p.n, c->top.norm);
     const bool timed = prof_begin(c, step, s);
     const bool h16 = is_h16(c->p);
@@ -408,8 +407,8 @@ hipError_t enqueue_ir(mg_ctx* c, int sel, int flags, hipStream_t s, int step = 0
                                           c->pstride, c->top.norm, s);
     if (timed) prof_end(c, step, 1, s);
     if (e != hipSuccess) return e;
-    if (h16) return launch_norm_finalize_f16(c->d_partial, c->d_pmax, nparts, c->d_norm, c->d_scl, ctl_done(c), s);
-    return launch_norm_finalize(c->d_partial, c->pstride, nparts, 0, 1, c->d_norm, s);
+    if (h16) return launch_norm_finalize_f16(c->d_partial, c->d_pmax, nparts, c->d_norm, c->d_scl, ctl_done(c), s, stop);
+    return launch_norm_finalize(c->d_partial, c->pstride, nparts, 0, 1, c->d_norm, s, stop);
 }
 
 // Residual of the bound (u, f) handed to the refinement's first cycle, with
@@ -432,6 +431,8 @@ hipError_t enqueue_steps(mg_ctx* c, int K, double tol, int max_cycles, hipStream
     hipEvent_t* pev = prof ? c->prof_ev.data() : nullptr;
     int* pn = prof ? &c->prof_n : nullptr;
     const int pcap = (int)c->prof_ev.size();
+    const StopTest stop{c->d_norm0, ctl_done(c), ctl_steps(c), ctl_status(c), c->h_pin + kPinHist, c->hist_cap, max_cycles, tol,
+                        (int*)c->h_pin};
     for (int i = 0; i < K; ++i) {
         hipError_t e;
         const int step = prof ? step0 + i + 1 : 0;
@@ -443,17 +444,14 @@ hipError_t enqueue_steps(mg_ctx* c, int K, double tol, int max_cycles, hipStream
             for (int j = n0; prof && j < c->prof_n; j += 2) c->prof_step.push_back(step), c->prof_kind.push_back(0);
             if (e != hipSuccess) return e;
             if (c->cc && (e = enqueue_mean(c, s)) != hipSuccess) return e;
-            e = c->nrm_fused ? enqueue_nrm_sweep(c, s, step) : enqueue_norm(c, s, step);
+            e = c->nrm_fused ? enqueue_nrm_sweep(c, s, step, &stop) : enqueue_norm(c, s, step, &stop);
         } else {
             e = is_h16(c->p) ? vcycle<half_t>(c->prob, c->G32, true, c->tl32, s, pev, pn, pcap, &c->tail32)
                              : vcycle<float>(c->prob, c->G32, true, c->tl32, s, pev, pn, pcap, &c->tail32);
             for (int j = n0; prof && j < c->prof_n; j += 2) c->prof_step.push_back(step), c->prof_kind.push_back(0);
             if (e != hipSuccess) return e;
-            e = enqueue_ir(c, (par0 + i) & 1, 0, s, step);
+            e = enqueue_ir(c, (par0 + i) & 1, 0, s, step, &stop);
         }
-        if (e != hipSuccess) return e;
-        e = launch_stop_test(c->d_norm, c->d_norm0, ctl_done(c), ctl_steps(c), ctl_status(c), c->d_hist,
-                             c->hist_cap, tol, max_cycles, 1, s);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -461,13 +459,10 @@ hipError_t enqueue_steps(mg_ctx* c, int K, double tol, int max_cycles, hipStream
 
 int ensure_hist(mg_ctx* c, int cap) {
     if (cap <= c->hist_cap) return MG_OK;
-    ffree(c->d_hist);
-    c->d_hist = nullptr;
     if (c->h_pin) (void)hipHostFree(c->h_pin);
     c->h_pin = nullptr;
     c->hist_cap = 0;
-    CK(hipMalloc((void**)&c->d_hist, sizeof(double) * (size_t)cap));
-    CK(hipHostMalloc((void**)&c->h_pin, sizeof(double) * (size_t)(cap + 8), hipHostMallocDefault));
+    CK(hipHostMalloc((void**)&c->h_pin, sizeof(double) * (size_t)(cap + kPinHist), hipHostMallocDefault));
     c->hist_cap = cap;
     // the hist pointer is baked into captured graphs
     for (auto& g : c->graphs) (void)hipGraphExecDestroy(g.exec);
@@ -1387,44 +1382,34 @@ int mg_solve(mg_ctx* c, double* u, const double* f, double tol, int max_cycles, 
     if (ir) CK(enqueue_ir_start(c, s));
     else if (c->nrm_fused) CK(enqueue_nrm_sweep(c, s));
     else CK(enqueue_norm(c, s));
-    CK(launch_solve_init(c->d_norm, c->d_norm0, ctl_done(c), ctl_steps(c), ctl_status(c), c->d_hist, c->hist_cap, 1,
-                         s));
+    // The control words and the history lie in pinned host memory: the kernels
+    // that advance them write them there, so the host waits for a chunk and
+    // reads, with no copies and no wait before the first chunk (a solve had
+    // five copies and four waits, 40 us of the 550 us of ten 129 x 129 cycles).
+    const double* hist = c->h_pin + kPinHist;
+    const int* ctl = (const int*)c->h_pin;  // done, steps, status
+    CK(launch_solve_init(c->d_norm, c->d_norm0, ctl_done(c), ctl_steps(c), ctl_status(c), c->h_pin + kPinHist,
+                         c->hist_cap, 1, s, (int*)c->h_pin));
     // steps in chunks: the first of kmax steps, later ones sized by
     // next_chunk; kernels of a finished solve exit at once
     const size_t N = npts(c->p.dim, c->p.n);
     const int kmax = N > (size_t)(1 << 20) ? 4 : 10;
-    int K = kmax;
-    int steps = 0, status = 1, done = 0;
-    CK(hipMemcpyAsync(c->h_pin, c->d_ctrl, 3 * sizeof(int), hipMemcpyDeviceToHost, s));
-    CK(hipStreamSynchronize(s));
-    done = ((int*)c->h_pin)[0];
-    status = ((int*)c->h_pin)[2];
-    int enqueued = 0;
-    while (!done && enqueued < max_cycles) {
+    int K = kmax, enqueued = 0;
+    do {
         const int k = std::min(K, max_cycles - enqueued);
-        r = run_chunk(c, k, tol, max_cycles, enqueued);
+        if (k > 0) r = run_chunk(c, k, tol, max_cycles, enqueued);
         if (r != MG_OK) return r;
         enqueued += k;
-        CK(hipMemcpyAsync(c->h_pin, c->d_ctrl, 3 * sizeof(int), hipMemcpyDeviceToHost, s));
-        CK(hipMemcpyAsync(c->h_pin + 2, c->d_hist, sizeof(double) * (size_t)(enqueued + 1), hipMemcpyDeviceToHost,
-                          s));
         CK(hipStreamSynchronize(s));
-        done = ((int*)c->h_pin)[0];
-        steps = ((int*)c->h_pin)[1];
-        status = ((int*)c->h_pin)[2];
-        K = next_chunk(c->h_pin + 2, steps, tol, kmax);
-    }
+        K = next_chunk(hist, ctl[1], tol, kmax);
+    } while (!ctl[0] && enqueued < max_cycles);
+    const int steps = ctl[1], status = ctl[2];
     // cells: the sweeps that summed the norms subtracted the mean on the way, u still has it
-    if (c->cc && c->nrm_fused) CK(cc_subtract(c->p.dim, c->p.n, u, nullptr, c->cc_mean, s));
-    CK(hipMemcpyAsync(c->h_pin, c->d_ctrl, 3 * sizeof(int), hipMemcpyDeviceToHost, s));
-    CK(hipStreamSynchronize(s));
-    steps = ((int*)c->h_pin)[1];
-    status = ((int*)c->h_pin)[2];
-    if (res_hist) {
-        CK(hipMemcpyAsync(c->h_pin, c->d_hist, sizeof(double) * (size_t)(steps + 1), hipMemcpyDeviceToHost, s));
+    if (c->cc && c->nrm_fused) {
+        CK(cc_subtract(c->p.dim, c->p.n, u, nullptr, c->cc_mean, s));
         CK(hipStreamSynchronize(s));
-        std::memcpy(res_hist, c->h_pin, sizeof(double) * (size_t)(steps + 1));
     }
+    if (res_hist) std::memcpy(res_hist, hist, sizeof(double) * (size_t)(steps + 1));
     if (ir && (steps & 1)) {  // the last refinement step wrote the scratch iterate
         CK(hipMemcpyAsync(u, c->u64_scratch, N * sizeof(double), hipMemcpyDeviceToDevice, s));
         CK(hipStreamSynchronize(s));

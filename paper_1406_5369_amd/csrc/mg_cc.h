@@ -31,7 +31,8 @@ hipError_t cc_remove_mean(int dim, int n, double* v, double* work, double* mean,
 size_t cc_work_doubles(int dim, int n);
 // norm[0] = ||f - A u||_2 of the grid d (partials: cc_norm_parts doubles)
 int cc_norm_parts(int dim, int n);
-hipError_t cc_norm(int dim, const GridDesc* d, int n, double* part, double* norm, hipStream_t s);
+hipError_t cc_norm(int dim, const GridDesc* d, int n, double* part, double* norm, hipStream_t s,
+                   const StopTest* stop = nullptr);
 
 // The steps of a cycle on a level given by its descriptor (OP_CC of the
 // launchers in mg_internal.h), and the coarse tail.

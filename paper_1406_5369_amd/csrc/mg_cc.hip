@@ -663,13 +663,14 @@ hipError_t cc_subtract(int dim, int n, double* v, const GridDesc* d, const doubl
 
 int cc_norm_parts(int dim, int n) { return (int)blocks_for(cc_cells(dim, n)); }
 
-hipError_t cc_norm(int dim, const GridDesc* d, int n, double* part, double* norm, hipStream_t s) {
+hipError_t cc_norm(int dim, const GridDesc* d, int n, double* part, double* norm, hipStream_t s,
+                   const StopTest* stop) {
     const int nparts = cc_norm_parts(dim, n);
     if (dim == 2) k_cc_norm<2><<<nparts, NT, 0, s>>>(d, part);
     else k_cc_norm<3><<<nparts, NT, 0, s>>>(d, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_norm_finalize(part, nparts, nparts, 0, 1, norm, s);
+    return launch_norm_finalize(part, nparts, nparts, 0, 1, norm, s, stop);
 }
 
 namespace {

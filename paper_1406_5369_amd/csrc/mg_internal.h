@@ -199,6 +199,17 @@ hipError_t launch_copy_t_to_u(int dim, const GridDesc* d, int ninst, int n, hipS
 template <typename T>
 hipError_t launch_zero_u(int dim, const GridDesc* d, int ninst, int n, hipStream_t s);
 
+// The stop test after a cycle (see the solve control below); arrays by row where
+// a launch finalizes several.
+struct StopTest {
+    const double* norm0;
+    int *done, *steps, *status;
+    double* hist;
+    int hstride, max_steps;
+    double tol;
+    int* mirror = nullptr;  // host-visible copy of done, steps, status (one instance), or null
+};
+
 // FP64 residual norm partials: partial[inst * pstride + block] = sum r^2 over the block.
 hipError_t launch_norm(int dim, bool var, const GridDesc* d, int ninst, int n, int sel, double* partial,
                        int pstride, TileCfg cfg, hipStream_t s);
@@ -215,27 +226,29 @@ hipError_t launch_ir_update_f16(int dim, const IRDesc* d, int ninst, int n, int 
 // launch_norm_finalize; unless *done: scl[0] = fp16 scale of scl[1] (the
 // scale that pass wrote r with), scl[1] = max of the partial maxima.
 hipError_t launch_norm_finalize_f16(const double* partial, const double* pmax, int nparts, double* norm, double* scl,
-                                    const int* done, hipStream_t s);
+                                    const int* done, hipStream_t s, const StopTest* stop = nullptr);
 // norm[inst] = sqrt(sum of partial[inst*pstride + 0 .. nparts-1]) in a fixed order; for
-// each of 'ninst' rows starting at row 'row0'.
+// each of 'ninst' rows starting at row 'row0'; with 'stop' (one row) followed
+// by the stop test of that instance in the same launch.
 hipError_t launch_norm_finalize(const double* partial, int pstride, int nparts, int row0, int ninst,
-                                double* norm, hipStream_t s);
+                                double* norm, hipStream_t s, const StopTest* stop = nullptr);
 
 // Device-side solve control, one entry per instance i in [0, ninst):
 //   solve_init: norm0[i] = norm[i], hist[i*hstride] = norm[i], steps[i] = 0,
 //               status[i] = 1 (running) / 0 (zero residual) / -5, done[i] set unless running.
-//   stop_test:  for running instances: steps[i]++, hist[i*hstride+steps] = norm[i],
-//               status 0 when norm <= tol*norm0, -5 on NaN/Inf/growth > 1e6,
-//               2 when steps reaches max_steps; done[i] = 1 once status != 1.
+//   stop test (StopTest, in the launch that finalizes the norm): for a running
+//               instance steps[i]++, hist[i*hstride+steps] = norm[i], status 0
+//               when norm <= tol*norm0, -5 on NaN/Inf/growth > 1e6, 2 when
+//               steps reaches max_steps; done[i] = 1 once status != 1.
+// hist and mirror (done, steps, status of one instance) may be host memory.
 hipError_t launch_solve_init(const double* norm, double* norm0, int* done, int* steps, int* status, double* hist,
-                             int hstride, int ninst, hipStream_t s);
-hipError_t launch_stop_test(const double* norm, const double* norm0, int* done, int* steps, int* status, double* hist,
-                            int hstride, double tol, int max_steps, int ninst, hipStream_t s, int* par = nullptr);
+                             int hstride, int ninst, hipStream_t s, int* mirror = nullptr);
 // Batched variants over an explicit list of instance rows.
 //   finalize_rows: norm[r] = sqrt(sum of partial[r*pstride + 0 .. nparts[r]-1]) for r in rows
 //   solve_init_rows: as launch_solve_init for the listed rows (par[r] = 0 when par is given)
+//                  with 'stop' followed by the stop test of each row (par[r] ^= 1 where it ran)
 hipError_t launch_norm_finalize_rows(const double* partial, int pstride, const int* nparts, const int* rows, int nrows,
-                                     double* norm, hipStream_t s);
+                                     double* norm, hipStream_t s, const StopTest* stop = nullptr, int* par = nullptr);
 // arr[rows[j]] = v for j < nrows.
 hipError_t launch_set_rows(int* arr, int v, const int* rows, int nrows, hipStream_t s);
 hipError_t launch_solve_init_rows(const double* norm, double* norm0, int* done, int* steps, int* status, int* par,

@@ -13,6 +13,8 @@ struct mg_ctx;
 
 namespace mg {
 
+constexpr int kPinHist = 8;  // doubles before the history in mg_ctx::h_pin
+
 // Launch geometry of every kernel family of one hierarchy.
 struct Tiles {
     TileCfg smooth{16, 128};      // plain sweep
@@ -155,9 +157,8 @@ struct mg_ctx {
     int spart_cap = 0;
     double* d_norm = nullptr;   // [1]
     double* d_norm0 = nullptr;  // [1]
-    double* d_hist = nullptr;
     int hist_cap = 0;
-    double* h_pin = nullptr;  // pinned host staging
+    double* h_pin = nullptr;  // pinned host memory: staging / the solve's control words, then (at kPinHist) its history
 
     mg::GridDesc* d_top = nullptr;  // FP64 view of the finest level (residual norms)
     mg::GridDesc h_top{};

@@ -26,6 +26,7 @@ hipError_t st_coarsest(int dim, double* u, const double* f, const STConst& L, hi
 // norm[0] = ||f - A u||_2 over inner nodes of the grid (device descriptor) of
 // edge n (part: st_norm_parts doubles)
 int st_norm_parts(int dim, int n);
-hipError_t st_norm(int dim, const GridDesc* d, int n, double* part, double* norm, hipStream_t s);
+hipError_t st_norm(int dim, const GridDesc* d, int n, double* part, double* norm, hipStream_t s,
+                   const StopTest* stop = nullptr);
 
 }  // namespace mg

@@ -174,13 +174,14 @@ hipError_t st_coarsest(int dim, double* u, const double* f, const STConst& L, hi
 
 int st_norm_parts(int dim, int n) { return (int)nblk(nodes(dim, n)); }
 
-hipError_t st_norm(int dim, const GridDesc* d, int n, double* part, double* norm, hipStream_t s) {
+hipError_t st_norm(int dim, const GridDesc* d, int n, double* part, double* norm, hipStream_t s,
+                   const StopTest* stop) {
     const int np = st_norm_parts(dim, n);
     if (dim == 2) k_st_norm<2><<<np, NT, 0, s>>>(d, part);
     else k_st_norm<3><<<np, NT, 0, s>>>(d, part);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_norm_finalize(part, np, np, 0, 1, norm, s);
+    return launch_norm_finalize(part, np, np, 0, 1, norm, s, stop);
 }
 
 }  // namespace mg
