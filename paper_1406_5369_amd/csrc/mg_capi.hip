@@ -24,6 +24,7 @@ struct CDState {
     CDConst K{};
     bool jacobi = false;
     int nu1 = 2, nu2 = 2;
+    bool tail = true;  // the coarse levels in one launch (MG_NO_TAIL: apart)
     std::vector<int> ln;
     std::vector<void*> u, t, f, g, uh;
     double* part = nullptr;
@@ -550,6 +551,8 @@ hipError_t cd_sweep_level(CDState& S, int l, void*& cur, void*& other, const voi
 
 hipError_t cd_fas_level(CDState& S, int l, void*& cur, void*& other, const void* f, hipStream_t s) {
     const size_t N = cd_cells(S, l);
+    if (S.ln[(size_t)l] <= cd_tail_max_edge(S.dim) && S.tail)
+        return cd_tail(S.dim, S.jacobi, cur, f, S.K, S.tau, cd_level(S.ln[(size_t)l]), S.nu1, S.nu2, s);
     if (l + 1 == (int)S.ln.size()) return cd_scale(f, cur, N, S.tau, s);  // one cell: N(u) = u / tau
     const CDLevel L = cd_level(S.ln[(size_t)l]), Lc = cd_level(S.ln[(size_t)l + 1]);
     hipError_t e = hipSuccess;
@@ -1847,6 +1850,7 @@ int mg_cdiff_setup(const mg_cdiff_params* p, void* stream, mg_ctx** out) {
     S.jacobi = p->smoother == MG_SMOOTH_WJACOBI;
     S.nu1 = p->nu1;
     S.nu2 = p->nu2;
+    S.tail = std::getenv("MG_NO_TAIL") == nullptr;
     S.K.itau = 1.0 / p->tau;
     S.K.ktheta = p->k * p->theta;
     S.K.ct = std::cos(p->theta);

@@ -42,6 +42,11 @@ hipError_t cd_coarse_rhs(int dim, const void* uh, void* fc, void* uc, CDConst K,
 hipError_t cd_prolong(int dim, void* u, const void* uc, const void* uh, int n, hipStream_t s);
 hipError_t cd_scale(const void* a, void* out, size_t N, double sc, hipStream_t s);
 hipError_t cd_apply_op(int dim, const void* u, const void* g, void* out, CDConst K, CDLevel L, hipStream_t s);
+// One FAS cycle on u for f of a level up to cd_tail_max_edge cells per axis and
+// every level below it, in one launch
+int cd_tail_max_edge(int dim);
+hipError_t cd_tail(int dim, bool jacobi, void* u, const void* f, CDConst K, double tau, CDLevel L, int nu1, int nu2,
+                   hipStream_t s);
 int cd_norm_parts(int dim, int n);
 // ||f - N(u)|| (g of u formed on the fly) into *norm (device), part: cd_norm_parts doubles
 hipError_t cd_norm(int dim, const void* u, const void* f, CDConst K, CDLevel L, double* part, double* norm,

@@ -931,6 +931,234 @@ __global__ __launch_bounds__(NT) void k_cd_resblk(const Cx* __restrict__ u_, con
     }
 }
 
+// ---------------------------------------------------------------------------
+// Coarse tail of a FAS cycle: every level from 2^C cells per axis (32^2 or 8^3
+// and below) down to one cell in one launch, one workgroup, all fields in LDS.
+// Launched apart these levels took 50 launches of 2 - 4 us each in 2D (2 - 4
+// us is what an empty launch and a few dependent divisions cost).  Here a step
+// ends with a barrier, or, for levels of at most 16^2 / 4^3 cells, which the
+// first wavefront runs alone, with none.  Per cell the expressions are those
+// of the tiled sweeps (boundary faces through mirror ghosts) and of the
+// residual and transfer kernels; each sweep and residual forms q of the
+// iterate it starts from first.
+// ---------------------------------------------------------------------------
+constexpr int CDT_N = 1024;
+__host__ __device__ constexpr int cdt_cells(int dim, int C) { return 1 << (dim * C); }
+__host__ __device__ constexpr int cdt_off(int dim, int C) {
+    int s = 0;
+    for (int c = 0; c < C; ++c) s += cdt_cells(dim, c);
+    return s;
+}
+__host__ __device__ constexpr int cdt_wave_level(int dim) { return dim == 2 ? 3 : 2; }
+__host__ __device__ constexpr int cdt_top(int dim) { return dim == 2 ? 5 : 3; }
+
+struct CDTail {
+    d2v *U, *F, *H, *W;  // iterate, right-hand side and restricted iterate of all levels; residual of one
+    double* Q;           // diffusivity factor of one level
+    CDConst K;
+    double tau;
+    int nu1, nu2;
+};
+
+template <bool WAVE>
+__device__ __forceinline__ void cdt_sync() {
+    if constexpr (WAVE) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    } else {
+        __syncthreads();
+    }
+}
+// The thread's number, opaque to the compiler (a step's coordinates are formed
+// in the step, not kept in registers for every level).
+__device__ __forceinline__ int cdt_tid() {
+    int t = (int)threadIdx.x;
+    asm volatile("" : "+v"(t));
+    return t;
+}
+
+template <int DIM, bool JAC, int C>
+struct CDTLevel {
+    static constexpr int M = 1 << C, OFF = cdt_off(DIM, C), CELLS = cdt_cells(DIM, C);
+    static constexpr bool WAVE = C <= cdt_wave_level(DIM);
+    static constexpr int NTH = WAVE ? 64 : CDT_N;
+    static constexpr double c = (double)M * (double)M;  // 1/h^2, h = 1/M (exact)
+
+    static __device__ __forceinline__ int at(int i, int j, int k) { return ((k << C) + j) * M + i; }
+
+    // q of every cell of u
+    static __device__ __forceinline__ void form_q(const CDTail& x, const d2v* u) {
+        const int tid = cdt_tid();
+        for (int q = tid; q < CELLS; q += NTH) x.Q[q] = cd_q(x.K, lds_c(u[q]));
+        cdt_sync<WAVE>();
+    }
+    // Face sums of cell (i, j, k) with value up; a face on the boundary sees
+    // the cell itself with q negated (a flux and a diffusivity of +0).
+    static __device__ __forceinline__ void sums(const CDTail& x, const d2v* u, int i, int j, int k, Cx up, Cx& F, Cx& S) {
+        const int p = at(i, j, k);
+        const double qp = x.Q[p];
+        const Cx gpv{x.K.ct * qp, x.K.st * qp};
+        auto face = [&](bool in, int q) {
+            const int a = in ? q : p;
+            const double qq = x.Q[a];
+            return cd_face_m(up, gpv, lds_c(u[a]), in ? qq : -qq, x.K);
+        };
+        const CDFace fW = face(i > 0, p - 1), fE = face(i < M - 1, p + 1);
+        const CDFace fS = face(j > 0, p - M), fN = face(j < M - 1, p + M);
+        F = Cx{(fW.tr + fE.tr) + (fS.tr + fN.tr), (fW.ti + fE.ti) + (fS.ti + fN.ti)};
+        S = Cx{(fW.gr + fE.gr) + (fS.gr + fN.gr), (fW.gi + fE.gi) + (fS.gi + fN.gi)};
+        if constexpr (DIM == 3) {
+            const CDFace fB = face(k > 0, p - M * M), fT = face(k < M - 1, p + M * M);
+            F = Cx{F.re + (fB.tr + fT.tr), F.im + (fB.ti + fT.ti)};
+            S = Cx{S.re + (fB.gr + fT.gr), S.im + (fB.gi + fT.gi)};
+        }
+    }
+    static __device__ __forceinline__ Cx relaxed(const CDTail& x, const d2v* u, int i, int j, int k) {
+        const int p = at(i, j, k);
+        const Cx up = lds_c(u[p]);
+        Cx F, S;
+        sums(x, u, i, j, k, up, F, S);
+        return cd_relax_v(x.K, c, up, F, S, lds_c(x.F[OFF + p]));
+    }
+    static __device__ __forceinline__ void sweep(const CDTail& x) {
+        d2v* u = x.U + OFF;
+        form_q(x, u);
+        const int tid = cdt_tid();
+        if constexpr (JAC) {
+            constexpr int R = (CELLS + NTH - 1) / NTH;
+            d2v v[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int q = r * NTH + tid;
+                if (q < CELLS) v[r] = to_v(relaxed(x, u, q & (M - 1), (q >> C) & (M - 1), DIM == 3 ? q >> (2 * C) : 0));
+            }
+            cdt_sync<WAVE>();
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (r * NTH + tid < CELLS) u[r * NTH + tid] = v[r];
+            cdt_sync<WAVE>();
+        } else {
+            for (int colour = 0; colour < 2; ++colour) {
+                for (int q = tid; q < CELLS / 2; q += NTH) {
+                    const int j = (q >> (C - 1)) & (M - 1), k = DIM == 3 ? q >> (2 * C - 1) : 0;
+                    const int i = 2 * (q & (M / 2 - 1)) + ((j + k + colour) & 1);
+                    u[at(i, j, k)] = to_v(relaxed(x, u, i, j, k));
+                }
+                cdt_sync<WAVE>();
+            }
+        }
+    }
+    // uh = average of u, coarse F = N_c(uh) + average of f - N(u), coarse u = uh
+    static __device__ __forceinline__ void restrict_fas(const CDTail& x) {
+        using Next = CDTLevel<DIM, JAC, C - 1>;
+        constexpr int MC = M / 2, NC = Next::CELLS;
+        const d2v* u = x.U + OFF;
+        form_q(x, u);
+        const int tid = cdt_tid();
+        for (int q = tid; q < CELLS; q += NTH) {
+            const int i = q & (M - 1), j = (q >> C) & (M - 1), k = DIM == 3 ? q >> (2 * C) : 0;
+            const Cx up = lds_c(u[q]);
+            Cx F, S;
+            sums(x, u, i, j, k, up, F, S);
+            const Cx Nu{x.K.itau * up.re - c * F.re, x.K.itau * up.im - c * F.im};
+            x.W[q] = to_v(cx_sub(lds_c(x.F[OFF + q]), Nu));
+        }
+        cdt_sync<WAVE>();
+        d2v* h = x.H + Next::OFF;
+        for (int q = tid; q < NC; q += NTH) {
+            const int i = 2 * (q & (MC - 1)), j = 2 * ((q >> (C - 1)) & (MC - 1));
+            const int k = DIM == 3 ? 2 * (q >> (2 * (C - 1))) : 0;
+            auto avg = [&](const d2v* a) {
+                auto v = [&](int di, int dj, int dk) { return lds_c(a[at(i + di, j + dj, k + dk)]); };
+                const Cx q0 = cx_add(cx_add(v(0, 0, 0), v(1, 0, 0)), cx_add(v(0, 1, 0), v(1, 1, 0)));
+                if constexpr (DIM == 2) return cx_scale(0.25, q0);
+                else
+                    return cx_scale(0.125, cx_add(q0, cx_add(cx_add(v(0, 0, 1), v(1, 0, 1)), cx_add(v(0, 1, 1), v(1, 1, 1)))));
+            };
+            const Cx r = avg(x.W), a = avg(u);
+            x.F[Next::OFF + q] = to_v(r);
+            h[q] = to_v(a);
+            x.U[Next::OFF + q] = to_v(a);
+        }
+        cdt_sync<WAVE>();
+        // the coarse level's q and operator (still this level's threads)
+        for (int q = tid; q < NC; q += NTH) x.Q[q] = cd_q(x.K, lds_c(h[q]));
+        cdt_sync<WAVE>();
+        for (int q = tid; q < NC; q += NTH) {
+            const int i = q & (MC - 1), j = (q >> (C - 1)) & (MC - 1), k = DIM == 3 ? q >> (2 * (C - 1)) : 0;
+            const Cx up = lds_c(h[q]);
+            Cx F, S;
+            Next::sums(x, h, i, j, k, up, F, S);
+            const Cx Nv{x.K.itau * up.re - Next::c * F.re, x.K.itau * up.im - Next::c * F.im};
+            x.F[Next::OFF + q] = to_v(cx_add(Nv, lds_c(x.F[Next::OFF + q])));
+        }
+        cdt_sync<WAVE>();
+    }
+    static __device__ __forceinline__ void correct(const CDTail& x) {
+        using Next = CDTLevel<DIM, JAC, C - 1>;
+        const int tid = cdt_tid();
+        for (int q = tid; q < CELLS; q += NTH) {
+            const int i = q & (M - 1), j = (q >> C) & (M - 1), k = DIM == 3 ? q >> (2 * C) : 0;
+            const int p = Next::OFF + Next::at(i >> 1, j >> 1, k >> 1);
+            x.U[OFF + q] = to_v(cx_add(lds_c(x.U[OFF + q]), cx_sub(lds_c(x.U[p]), lds_c(x.H[p]))));
+        }
+        cdt_sync<WAVE>();
+    }
+    static __device__ __forceinline__ void cycle(const CDTail& x) {
+        if constexpr (C == 0) {
+            if (threadIdx.x == 0) x.U[0] = to_v(cx_scale(x.tau, lds_c(x.F[0])));  // N(u) = u / tau
+            cdt_sync<WAVE>();
+        } else {
+            for (int s = 0; s < x.nu1; ++s) sweep(x);
+            restrict_fas(x);
+            using Next = CDTLevel<DIM, JAC, C - 1>;
+            if constexpr (Next::WAVE && !WAVE) {
+                if (threadIdx.x < 64) Next::cycle(x);
+                __syncthreads();
+            } else {
+                Next::cycle(x);
+            }
+            correct(x);
+            for (int s = 0; s < x.nu2; ++s) sweep(x);
+        }
+    }
+    static __device__ __forceinline__ void top(const CDTail& x, int n) {
+        if (n == M) {
+            if constexpr (WAVE) {
+                if (threadIdx.x < 64) cycle(x);
+                __syncthreads();
+            } else {
+                cycle(x);
+            }
+        } else if constexpr (C > 0) {
+            CDTLevel<DIM, JAC, C - 1>::top(x, n);
+        }
+    }
+};
+
+// One FAS cycle of a level of n cells per axis (up to 2^cdt_top) on u for f.
+template <int DIM, bool JAC>
+__global__ __launch_bounds__(CDT_N) void k_cd_tail(Cx* __restrict__ u_, const Cx* __restrict__ f_, CDConst K, double tau,
+                                                   CDLevel L, int nu1, int nu2) {
+    constexpr int CM = cdt_top(DIM), TOT = cdt_off(DIM, CM + 1);
+    __shared__ d2v Us[TOT], Fs[TOT], Hs[cdt_off(DIM, CM)], Ws[cdt_cells(DIM, CM)];
+    __shared__ double Qs[cdt_cells(DIM, CM)];
+    const int n = L.n, N = DIM == 2 ? n * n : n * n * n;
+    int off = 0;
+#pragma unroll
+    for (int c = 0; c < CM; ++c) off += (1 << c) < n ? cdt_cells(DIM, c) : 0;
+    MG_GLOBAL d2v* u = (MG_GLOBAL d2v*)gp(u_);
+    const MG_GLOBAL d2v* f = (const MG_GLOBAL d2v*)gp(f_);
+    for (int p = threadIdx.x; p < N; p += CDT_N) {
+        Us[off + p] = u[p];
+        Fs[off + p] = f[p];
+    }
+    __syncthreads();
+    const CDTail x{Us, Fs, Hs, Ws, Qs, K, tau, nu1, nu2};
+    CDTLevel<DIM, JAC, CM>::top(x, n);
+    for (int p = threadIdx.x; p < N; p += CDT_N) u[p] = Us[off + p];
+}
+
 inline unsigned nblk(size_t N) { return (unsigned)((N + NT - 1) / NT); }
 inline size_t ncells(int dim, int n) { return dim == 2 ? (size_t)n * n : (size_t)n * n * n; }
 
@@ -1023,6 +1251,22 @@ hipError_t cd_sweep(int dim, bool jacobi, const void* uin, void* uout, const voi
             if (C.uc) k_cd_sweep3d_rb<NW, kCDSweep3MinWaves, true><<<b, 64 * NW, 0, s>>>(ui, uo, ff, K, L, zc, C);
             else k_cd_sweep3d_rb<NW, kCDSweep3MinWaves, false><<<b, 64 * NW, 0, s>>>(ui, uo, ff, K, L, zc, C);
         }
+    }
+    return hipGetLastError();
+}
+
+int cd_tail_max_edge(int dim) { return 1 << cdt_top(dim); }
+hipError_t cd_tail(int dim, bool jacobi, void* u, const void* f, CDConst K, double tau, CDLevel L, int nu1, int nu2,
+                   hipStream_t s) {
+    if (L.n > cd_tail_max_edge(dim)) return hipErrorInvalidValue;
+    auto uu = (Cx*)u;
+    auto ff = (const Cx*)f;
+    if (dim == 2) {
+        if (jacobi) k_cd_tail<2, true><<<1, CDT_N, 0, s>>>(uu, ff, K, tau, L, nu1, nu2);
+        else k_cd_tail<2, false><<<1, CDT_N, 0, s>>>(uu, ff, K, tau, L, nu1, nu2);
+    } else {
+        if (jacobi) k_cd_tail<3, true><<<1, CDT_N, 0, s>>>(uu, ff, K, tau, L, nu1, nu2);
+        else k_cd_tail<3, false><<<1, CDT_N, 0, s>>>(uu, ff, K, tau, L, nu1, nu2);
     }
     return hipGetLastError();
 }
