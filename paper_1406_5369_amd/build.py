@@ -26,6 +26,7 @@ SOURCES = [
     "mg_resid.hip",
     "mg_transfer.hip",
     "mg_smooth2d.hip",
+    "mg_leg2d.hip",
     "mg_solver.hip",
     "mg_capi.hip",
     "mg_batch.hip",

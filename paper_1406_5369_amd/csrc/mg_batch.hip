@@ -444,7 +444,7 @@ struct Engine {
         BCK(launch_fill_int(d_done, 0, cap, s));  // kernels skip instances whose flag is set
         for (int g = 0; g < stop; ++g) {
             const int a = amax - g;
-            BCK(tune_group(dim, prob.smoother, groups[(size_t)g].d, groups[(size_t)g].ninst, groups[(size_t)g].n,
+            BCK(tune_group(prob, groups[(size_t)g].d, groups[(size_t)g].ninst, groups[(size_t)g].n,
                            tiles[(size_t)a], s));
         }
         BCK(launch_fill_int(d_done, 1, cap, s));

@@ -389,9 +389,12 @@ hipError_t enqueue_mean(mg_ctx* c, hipStream_t s) {
 // measurement on, the sweep is bracketed and tagged (step, kernel 1).
 hipError_t enqueue_nrm_sweep(mg_ctx* c, hipStream_t s, int step = 0, const StopTest* stop = nullptr) {
     const TileCfg cfg = c->tl64[0].smooth_nrm;
-    const int nparts = smooth_tiles(c->p.dim, c->prob.smoother, c->p.n, cfg, c->prob.op());
+    const bool leg = leg_first(c->prob, c->p.n);
+    const int nparts = leg ? down2d_tiles(c->prob.op(), c->p.n)
+                           : smooth_tiles(c->p.dim, c->prob.smoother, c->p.n, cfg, c->prob.op());
     const bool timed = prof_begin(c, step, s);
-    hipError_t e = launch_smooth<double>(c->p.dim, c->prob.smoother, c->prob.op(), c->G64[0].d, 1, c->p.n, 0,
+    hipError_t e = leg ? launch_down2d<double>(c->prob.op(), c->G64[0].d, 1, c->p.n, 0, c->p.nu1, SWEEP_NORM, s)
+                       : launch_smooth<double>(c->p.dim, c->prob.smoother, c->prob.op(), c->G64[0].d, 1, c->p.n, 0,
                                          SWEEP_NORM, cfg, s);
     if (timed) prof_end(c, step, 1, s);
     if (e != hipSuccess) return e;
@@ -873,7 +876,8 @@ hipError_t tune_levels(mg_ctx* c, const Levels& L, std::vector<Tiles>& tl, void*
         }
         // the first two pre-smoothing sweeps from a zero iterate in one launch,
         // kept if it beats the two sweeps it replaces
-        if (!var && sm == SM_RBGS && L.elem <= 4 && c->p.nu1 >= 2) {
+        const bool leg = leg_ok(c->prob, n);
+        if (!var && sm == SM_RBGS && L.elem <= 4 && c->p.nu1 >= 2 && !leg) {
             TuneKey k2{dim, L.elem, n, 6, sm, 0, 0, 0};
             if (!tune_lookup(k2, &cfg)) {
                 const std::vector<TileCfg> cands = smooth2_candidates(dim, n);
@@ -903,7 +907,7 @@ hipError_t tune_levels(mg_ctx* c, const Levels& L, std::vector<Tiles>& tl, void*
             if (cfg.zchunk < 0) tl[(size_t)l].smooth_zg2.zchunk = std::getenv("MG_FUSED_SMOOTH2") ? -cfg.zchunk : 0;
         }
         // 2D: the first two post-smoothing sweeps in one launch, kept if faster
-        if (dim == 2 && !var && sm == SM_RBGS && L.elem <= 4 && c->p.nu2 >= 2) {
+        if (dim == 2 && !var && sm == SM_RBGS && L.elem <= 4 && c->p.nu2 >= 2 && !leg) {
             TuneKey kp{dim, L.elem, n, 7, sm, 0, 0, 0};
             if (!tune_lookup(kp, &cfg)) {
                 const std::vector<TileCfg> cands = smooth2_candidates(dim, n);
@@ -942,7 +946,9 @@ hipError_t tune_levels(mg_ctx* c, const Levels& L, std::vector<Tiles>& tl, void*
 // batched V-cycle launches them.  Runs on the instances' own level arrays
 // (clear at setup; sweeps and restrictions write inner nodes only).
 namespace mg {
-hipError_t tune_group(int dim, int smoother, const GridDesc* d, int count, int n, Tiles& t, hipStream_t s) {
+hipError_t tune_group(const Problem& P, const GridDesc* d, int count, int n, Tiles& t, hipStream_t s) {
+    const int dim = P.dim, smoother = P.smoother;
+    const bool leg = leg_ok(P, n);
     if (count <= 0 || n <= 3 || npts(dim, n) * (size_t)count < kTuneMinPoints) return hipSuccess;
     int bucket = 0;
     for (int c = count; c; c >>= 1) ++bucket;
@@ -972,7 +978,7 @@ hipError_t tune_group(int dim, int smoother, const GridDesc* d, int count, int n
     }
     t.restr = cfg;
     // the two fused pre-smoothing sweeps from a zero iterate, kept if faster
-    if (smoother == SM_RBGS) {
+    if (smoother == SM_RBGS && !leg) {
         TuneKey k2{dim, 4, n, 6, smoother, 0, 0, bucket};
         if (!tune_lookup(k2, &cfg)) {
             auto run2 = [&](TileCfg c) {
@@ -994,7 +1000,7 @@ hipError_t tune_group(int dim, int smoother, const GridDesc* d, int count, int n
         t.smooth_zg2 = cfg;
         if (cfg.zchunk < 0) t.smooth_zg2.zchunk = std::getenv("MG_FUSED_SMOOTH2") ? -cfg.zchunk : 0;
     }
-    if (smoother == SM_RBGS && dim == 2) {
+    if (smoother == SM_RBGS && dim == 2 && !leg) {
         TuneKey kp{dim, 4, n, 7, smoother, 0, 0, bucket};
         if (!tune_lookup(kp, &cfg)) {
             auto runp = [&](TileCfg c) { return launch_smooth2d_pro2<float>(d, count, n, 0, c, s); };
@@ -1245,6 +1251,7 @@ int mg_setup(const mg_params* p, void* stream, mg_ctx** out) {
     if (c->nrm_fused) {
         const int sm = c->prob.smoother;
         int cap = smooth_tiles(dim, sm, p->n, c->tl64[0].smooth_nrm, c->prob.op());
+        if (dim == 2 && !c->cc) cap = std::max(cap, down2d_tiles(c->prob.op(), p->n));
         if (c->autotune)
             for (TileCfg t : tune_candidates(dim, p->n - 2, true, 0, 8, c->prob.var))
                 if (t.wv != 1) cap = std::max(cap, smooth_tiles(dim, sm, p->n, t));

@@ -167,6 +167,17 @@ int smooth2d_zg2_tiles(int n, int ychunk);
 template <typename T>
 hipError_t launch_smooth2d_pro2(const GridDesc* d, int ninst, int n, int sel, TileCfg cfg, hipStream_t s);
 int smooth2d_pro2_tiles(int n, int ychunk);
+// 2D, red-black, edges 5 .. kLegMaxN: the last 'ns' (1 or 2) pre-smoothing sweeps
+// of a level (from input 'sel'; flags 0, SWEEP_ZERO_GUESS or SWEEP_NORM), residual
+// and full weighting into fc in one launch, and its correction from uc and first
+// 'ns' post-smoothing sweeps; the iterate goes to the partner of the input.
+// SWEEP_NORM writes down2d_tiles(op, n) partials.
+constexpr int kLegMaxN = 8193;  // byte offsets in a grid fit 32 bits
+template <typename T>
+hipError_t launch_down2d(int op, const GridDesc* d, int ninst, int n, int sel, int ns, int flags, hipStream_t s);
+template <typename T>
+hipError_t launch_up2d(int op, const GridDesc* d, int ninst, int n, int sel, int ns, hipStream_t s);
+int down2d_tiles(int op, int n);
 // 3D Laplacian, FP32 or binary16 storage: the last red-first RBGS pre-smoothing
 // sweep of input 'sel' fused with the residual of its result and full
 // weighting into fc (cfg.by 16 rows, cfg.zchunk coarse planes per workgroup,

@@ -287,6 +287,42 @@ __device__ __forceinline__ double lane_next(double v) {
     return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
+// A choice between two values (never between two addresses of an array: that
+// would put the array into memory).
+template <typename T>
+__device__ __forceinline__ T pick(bool b, T x, T y) {
+    return b ? x : y;
+}
+
+// A plane of values behind a buffer descriptor: an access takes the scalar
+// descriptor and one 32-bit byte offset per lane (no 64-bit address per lane
+// and row), and one outside the plane reads zero or is dropped.
+template <typename ST>
+struct PlaneBuf {
+    __amdgpu_buffer_rsrc_t d;
+    __device__ __forceinline__ PlaneBuf(const MG_GLOBAL ST* base, size_t values)
+        : d(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)(values * sizeof(ST)), 0x00020000)) {}
+    __device__ __forceinline__ ST load(unsigned off) const {
+        if constexpr (sizeof(ST) == 8) {
+            return __builtin_bit_cast(ST, __builtin_amdgcn_raw_buffer_load_b64(d, off, 0, 0));
+        } else if constexpr (sizeof(ST) == 4) {
+            return __builtin_bit_cast(ST, __builtin_amdgcn_raw_buffer_load_b32(d, off, 0, 0));
+        } else {
+            return __builtin_bit_cast(ST, __builtin_amdgcn_raw_buffer_load_b16(d, off, 0, 0));
+        }
+    }
+    __device__ __forceinline__ void store(unsigned off, ST v) const {
+        if constexpr (sizeof(ST) == 8) {
+            typedef unsigned int u2 __attribute__((ext_vector_type(2)));
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), d, off, 0, 0);
+        } else if constexpr (sizeof(ST) == 4) {
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), d, off, 0, 0);
+        } else {
+            __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), d, off, 0, 0);
+        }
+    }
+};
+
 // 3D residual from explicit neighbour values.
 template <typename T, int OP>
 __device__ __forceinline__ T res3(T uC, T uW, T uE, T uS, T uN, T uB, T uT, T kC, T kW, T kE, T kS, T kN, T kB, T kT,

@@ -5,35 +5,6 @@
 namespace mg {
 namespace {
 
-// A plane of values behind a buffer descriptor: an access takes the scalar
-// descriptor and one 32-bit byte offset per lane (no 64-bit address per lane
-// and row), and one outside the plane reads zero or is dropped.
-template <typename ST>
-struct PlaneBuf {
-    __amdgpu_buffer_rsrc_t d;
-    __device__ __forceinline__ PlaneBuf(const MG_GLOBAL ST* base, size_t values)
-        : d(__builtin_amdgcn_make_buffer_rsrc((void*)base, 0, (int)(values * sizeof(ST)), 0x00020000)) {}
-    __device__ __forceinline__ ST load(unsigned off) const {
-        if constexpr (sizeof(ST) == 8) {
-            return __builtin_bit_cast(ST, __builtin_amdgcn_raw_buffer_load_b64(d, off, 0, 0));
-        } else if constexpr (sizeof(ST) == 4) {
-            return __builtin_bit_cast(ST, __builtin_amdgcn_raw_buffer_load_b32(d, off, 0, 0));
-        } else {
-            return __builtin_bit_cast(ST, __builtin_amdgcn_raw_buffer_load_b16(d, off, 0, 0));
-        }
-    }
-    __device__ __forceinline__ void store(unsigned off, ST v) const {
-        if constexpr (sizeof(ST) == 8) {
-            typedef unsigned int u2 __attribute__((ext_vector_type(2)));
-            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2, v), d, off, 0, 0);
-        } else if constexpr (sizeof(ST) == 4) {
-            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), d, off, 0, 0);
-        } else {
-            __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), d, off, 0, 0);
-        }
-    }
-};
-
 // ---------------------------------------------------------------------------
 // A wavefront marches a 64 x 2P box along z; lane = x position, the thread
 // holds the rows of its column as P row pairs (rows 2p, 2p+1).  Colours
@@ -147,9 +118,6 @@ struct PairTile {
     }
     // The lane's node X[p] is an inner node of an inner plane.
     __device__ __forceinline__ bool inner(bool up, int p) const { return coli && (up ? yin(2 * p + 1) : yin(2 * p)); }
-    // A choice between two values (never between two addresses of an array:
-    // that would put the array into memory).
-    static __device__ __forceinline__ T pick(bool b, T x, T y) { return b ? x : y; }
 };
 
 // One red-black sweep.  Step kk (plane kk enters): the first colour on plane
@@ -233,7 +201,7 @@ struct SweepRB : PairTile<ST, OP, P, YE> {
 #pragma unroll
         for (int r = 0; r < 2 * P; ++r) {
             const T v = stored<ST>(raw[r] + ((r & 1) ? w1 : w2) * sum[r]);
-            raw[r] = Base::pick(zin && coli && yin(r), v, raw[r]);
+            raw[r] = pick(zin && coli && yin(r), v, raw[r]);
         }
     }
 
@@ -274,7 +242,7 @@ struct SweepRB : PairTile<ST, OP, P, YE> {
                 if constexpr (NRM) {
                     if (p >= 1 && p < P - 1 && m1 >= z0 && m1 < z1 && tile && in) acc += r * r;
                 }
-                A[Q1][p] = Base::pick(in, this->relaxed(A[Q1][p], r, !s, m1, p), A[Q1][p]);
+                A[Q1][p] = pick(in, this->relaxed(A[Q1][p], r, !s, m1, p), A[Q1][p]);
             }
         }
         if (m2 >= z0 && m2 < z1) {
@@ -283,8 +251,8 @@ struct SweepRB : PairTile<ST, OP, P, YE> {
             for (int p = 1; p < P - 1; ++p) {
                 const T r = this->res(B[Q2], A[Q2], A[Q3], A[Q1], fB[Q2][p], !s, m2, p);
                 const T v = this->relaxed(B[Q2][p], r, !s, m2, p);
-                if (tile && yin(2 * p)) out.store(rb[2 * p], (ST)Base::pick(s, v, A[Q2][p]));
-                if (tile && yin(2 * p + 1)) out.store(rb[2 * p + 1], (ST)Base::pick(s, A[Q2][p], v));
+                if (tile && yin(2 * p)) out.store(rb[2 * p], (ST)pick(s, v, A[Q2][p]));
+                if (tile && yin(2 * p + 1)) out.store(rb[2 * p + 1], (ST)pick(s, A[Q2][p], v));
             }
         }
     }
@@ -426,7 +394,7 @@ struct Sweep2RB : PairTile<ST, OP_LAP, P, YE> {
 #pragma unroll
             for (int p = 1; p < P - 1; ++p) {
                 const T v = this->relaxed(A[Q2][p], this->res(A[Q2], B[Q2], B[Q3], B[Q1], fA[Q2][p], s, p2, p), s, p2, p);
-                A[Q2][p] = Base::pick(this->inner(s, p), v, A[Q2][p]);
+                A[Q2][p] = pick(this->inner(s, p), v, A[Q2][p]);
             }
         }
         if (p3 >= z0 && p3 < z1) {
@@ -436,10 +404,10 @@ struct Sweep2RB : PairTile<ST, OP_LAP, P, YE> {
             for (int p = 1; p < P - 1; ++p) {
                 // plane kk-3 has the other parity: its second colour is in the pair's second row where s holds
                 const T v = this->relaxed(B[Q3][p], this->res(B[Q3], A[Q3], A[Q4], A[Q2], fB[Q3][p], s, p3, p), s, p3, p);
-                if (p > 1 && ok && yin(2 * p)) out.store(rb[2 * p], (ST)Base::pick(s, A[Q3][p], v));
-                if (p == 1 && ok && yin(2 * p + 1)) out.store(rb[2 * p + 1], (ST)Base::pick(s, v, A[Q3][p]));
+                if (p > 1 && ok && yin(2 * p)) out.store(rb[2 * p], (ST)pick(s, A[Q3][p], v));
+                if (p == 1 && ok && yin(2 * p + 1)) out.store(rb[2 * p + 1], (ST)pick(s, v, A[Q3][p]));
                 if (p > 1 && p < P - 2 && ok && yin(2 * p + 1))
-                    out.store(rb[2 * p + 1], (ST)Base::pick(s, v, A[Q3][p]));
+                    out.store(rb[2 * p + 1], (ST)pick(s, v, A[Q3][p]));
             }
         }
     }

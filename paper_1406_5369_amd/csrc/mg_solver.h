@@ -15,6 +15,8 @@ namespace mg {
 
 constexpr int kPinHist = 8;  // doubles before the history in mg_ctx::h_pin
 
+struct Problem;
+
 // Launch geometry of every kernel family of one hierarchy.
 struct Tiles {
     TileCfg smooth{16, 128};      // plain sweep
@@ -51,7 +53,7 @@ Tiles default_tiles(int dim, int elem_bytes, int n, int smoother, int op);
 Tiles lds_tiles(int dim, int n, int smoother);
 // Autotune the FP32 sweeps and restriction of one absolute level of a batch:
 // 'count' instances of edge n, descriptors d (device).  Cached per process.
-hipError_t tune_group(int dim, int smoother, const GridDesc* d, int count, int n, Tiles& t, hipStream_t s);
+hipError_t tune_group(const Problem& P, const GridDesc* d, int count, int n, Tiles& t, hipStream_t s);
 int heuristic_zchunk(int dim, int n, int by, int halo, int target_blocks);
 
 // Device buffers of one instance's hierarchy in working precision T
@@ -86,6 +88,12 @@ struct Problem {
     int cg_iters = 0;   // conjugate-gradient steps on a coarsest level with n > 3 (0: 4 (n - 1))
 };
 
+// Whether a level of edge n runs each of its legs with its last two pre- and
+// first two post-smoothing sweeps in one launch (launch_down2d, launch_up2d).
+bool leg_ok(const Problem& P, int n);
+// Whether the first pre-smoothing sweep is in that launch.
+inline bool leg_first(const Problem& P, int n) { return leg_ok(P, n) && P.nu1 <= 2; }
+
 // Coarse levels of a V-cycle run by the single-workgroup tail kernel:
 // groups[first..L-1], one TailDesc per instance (first = -1: no tail).
 struct TailPlan {
@@ -102,7 +110,8 @@ int tail_first_level(int dim, int elem, int op, const std::vector<int>& n, bool 
 // V-cycle over groups[0..L-1] (groups[l] holds every instance's level l);
 // zero_top: the iterate at level 0 is known to be zero.  Works in precision T.
 // first_done: level 0's first pre-smoothing sweep has already run (its result
-// is in the ping-pong partner t; the cycle continues from the second sweep).
+// is in the ping-pong partner t; the cycle continues from the second sweep),
+// or, with leg_first, its whole descending leg.
 template <typename T>
 hipError_t vcycle(const Problem& P, const std::vector<Group>& groups, bool zero_top, const std::vector<Tiles>& tiles,
                   hipStream_t s, hipEvent_t* prof_ev, int* prof_n, int prof_cap, const TailPlan* tail = nullptr,

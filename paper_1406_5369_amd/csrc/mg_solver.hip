@@ -177,8 +177,52 @@ bool post2_ok(const Problem& P, int dim, const Tiles& t) {
            t.smooth_pro2.zchunk > 0 && std::getenv("MG_NO_FUSED_POST2") == nullptr;
 }
 
+bool leg_ok(const Problem& P, int n) {
+    return P.dim == 2 && P.smoother == SM_RBGS && P.op() != OP_CC && P.nu1 >= 1 && P.nu2 >= 1 && n >= 5 &&
+           n <= kLegMaxN;
+}
+
 // Post-smoothing select bits: the symmetric red-black smoother relaxes black first.
 inline int post_sel(const Problem& P, int cur) { return cur | (P.sym ? SEL_BLACK_FIRST : 0); }
+
+// The descending leg of a leg_ok level: nu1 - ns plain sweeps, then the launch
+// that also restricts.  first_done as in vcycle.  'top': level 0, whose plain
+// sweeps are measured.  Returns the buffer of the iterate in cur.
+template <typename T>
+hipError_t leg_down(const Problem& P, const Group& g, const Tiles& t, bool top, bool zero, bool first_done, int& cur,
+                    hipStream_t s, Prof& prof) {
+    cur = first_done ? 1 : 0;
+    if (first_done && leg_first(P, g.n)) return hipSuccess;
+    const int ns = P.nu1 >= 2 ? 2 : 1;
+    int i = first_done ? 1 : 0;
+    for (; i < P.nu1 - ns; ++i) {
+        const int flags = (i == 0 && zero) ? SWEEP_ZERO_GUESS : 0;
+        const bool timed = top && flags == 0;
+        if (timed) prof.begin();
+        MG_TRY(launch_smooth<T>(2, P.smoother, P.op(), g.d, g.ninst, g.n, cur, flags, t.sweep(flags), s));
+        if (timed) prof.end();
+        cur ^= 1;
+    }
+    MG_TRY(launch_down2d<T>(P.op(), g.d, g.ninst, g.n, cur, ns, (i == 0 && zero) ? SWEEP_ZERO_GUESS : 0, s));
+    cur ^= 1;
+    return hipSuccess;
+}
+
+// The ascending leg of a leg_ok level; the iterate ends in u.
+template <typename T>
+hipError_t leg_up(const Problem& P, const Group& g, const Tiles& t, bool top, int cur, hipStream_t s, Prof& prof) {
+    const int ns = P.nu2 >= 2 ? 2 : 1;
+    MG_TRY(launch_up2d<T>(P.op(), g.d, g.ninst, g.n, post_sel(P, cur), ns, s));
+    cur ^= 1;
+    for (int i = ns; i < P.nu2; ++i) {
+        if (top) prof.begin();
+        MG_TRY(launch_smooth<T>(2, P.smoother, P.op(), g.d, g.ninst, g.n, post_sel(P, cur), 0, t.sweep(0), s));
+        if (top) prof.end();
+        cur ^= 1;
+    }
+    if (cur == 1) MG_TRY(launch_copy_t_to_u<T>(2, g.d, g.ninst, g.n, s));
+    return hipSuccess;
+}
 
 // Algorithm 1 on level l with gamma recursive calls: kind 0 V (one call), 1 W
 // (two), 2 F (an F-cycle then a V-cycle).  The zero guess precedes the first
@@ -196,9 +240,13 @@ hipError_t cycle_rec(const Problem& P, const std::vector<Group>& G, int l, int k
         return launch_tail<T>(dim, P.smoother, P.op(), tail->d, tail->ninst, P.nu1, P.nu2, P.sym ? 1 : 0, kind, zero,
                               s);
     if (l == L - 1) return coarse_solve<T>(P, g, s);
+    const bool leg = leg_ok(P, g.n);
     int cur = first_done ? 1 : 0;
     int i0 = first_done ? 1 : 0;
-    if (!first_done && smooth2_ok<T>(P, dim, tiles[(size_t)l], zero)) {
+    if (leg) {
+        MG_TRY(leg_down<T>(P, g, tiles[(size_t)l], l == 0, zero, first_done, cur, s, prof));
+        i0 = P.nu1;
+    } else if (!first_done && smooth2_ok<T>(P, dim, tiles[(size_t)l], zero)) {
         // sweeps 1 and 2 from the zero iterate: the result lands in u
         MG_TRY(launch_smooth2<T>(dim, g, tiles[(size_t)l], 1, s));
         i0 = 2;
@@ -213,7 +261,7 @@ hipError_t cycle_rec(const Problem& P, const std::vector<Group>& G, int l, int k
         cur ^= 1;
     }
     if (P.nu1 == 0 && zero) MG_TRY(launch_zero_u<T>(dim, g.d, g.ninst, g.n, s));
-    MG_TRY(launch_restrict<T>(dim, P.op(), g.d, g.ninst, g.n, cur, tiles[(size_t)l].restr, s));
+    if (!leg) MG_TRY(launch_restrict<T>(dim, P.op(), g.d, g.ninst, g.n, cur, tiles[(size_t)l].restr, s));
     if (kind == 0) {
         MG_TRY(cycle_rec<T>(P, G, l + 1, 0, true, tiles, s, prof, tail));
     } else if (kind == 1) {
@@ -223,6 +271,7 @@ hipError_t cycle_rec(const Problem& P, const std::vector<Group>& G, int l, int k
         MG_TRY(cycle_rec<T>(P, G, l + 1, 2, true, tiles, s, prof, tail));
         MG_TRY(cycle_rec<T>(P, G, l + 1, 0, false, tiles, s, prof, tail));
     }
+    if (leg) return leg_up<T>(P, g, tiles[(size_t)l], l == 0, cur, s, prof);
     const bool fuse = P.nu2 > 0;
     if (!fuse) MG_TRY(launch_prolong<T>(dim, P.op(), g.d, g.ninst, g.n, cur, s));
     for (int i = 0; i < P.nu2; ++i) {
@@ -259,6 +308,10 @@ hipError_t vcycle(const Problem& P, const std::vector<Group>& G, bool zero_top, 
     for (int l = 0; l < stop; ++l) {
         const Group& g = G[(size_t)l];
         const bool zero = l == 0 ? zero_top : true;
+        if (leg_ok(P, g.n)) {
+            MG_TRY(leg_down<T>(P, g, tiles[(size_t)l], l == 0, zero, l == 0 && first_done, sel[(size_t)l], s, prof));
+            continue;
+        }
         // the last sweep may carry the residual and restriction (a plain red-first sweep)
         const bool skip1 = l == 0 && first_done;
         // sweeps 1 and 2 from the zero iterate in one launch (result in u)
@@ -304,6 +357,10 @@ hipError_t vcycle(const Problem& P, const std::vector<Group>& G, bool zero_top, 
     for (int l = stop - 1; l >= 0; --l) {
         const Group& g = G[(size_t)l];
         int cur = sel[(size_t)l];
+        if (leg_ok(P, g.n)) {
+            MG_TRY(leg_up<T>(P, g, tiles[(size_t)l], l == 0, cur, s, prof));
+            continue;
+        }
         const bool fuse = P.nu2 > 0;  // the first post-sweep adds P uc while loading
         if (!fuse) MG_TRY(launch_prolong<T>(dim, P.op(), g.d, g.ninst, g.n, cur, s));
         int i0 = 0;
