@@ -171,7 +171,8 @@ int mg_num_levels(const mg_ctx* ctx);
  * post-smoothing sweeps in one launch (mg_level_smooth2_correct, 2D; *zchunk
  * 0 when the level runs them apart); 2D red-black levels up to 8193 nodes an
  * edge run each leg of a cycle, up to two sweeps with the restriction or the
- * correction, in one launch without these): tile rows
+ * correction, in one launch without these, and large 3D ones run sweeps two to
+ * a launch): tile rows
  * *by, z-chunk *zchunk (3D planes per workgroup), for 3D
  * marching kernels *prefetch = planes of u loaded ahead (1 or 2), *waves =
  * wavefronts per workgroup (4; 1 or 8 for 3D smoothing and the 3D pass), for
@@ -469,9 +470,10 @@ int mg_server_info(mg_ctx* ctx, size_t* used_bytes, int* active, int* queued);
 /* When on, mg_solve runs without graph capture and brackets two kernels of
  * every refinement step (or cycle) with HIP events on the context's stream:
  * kernel 0, the finest-level smoothing sweeps that read the previous iterate
- * (not the zero-iterate or fused-correction variants, nor those that a 2D
- * level's leg fuses with its restriction or correction); kernel 1, the
+ * (not the zero-iterate or fused-correction variants); kernel 1, the
  * finest-level FP64 refinement pass (mixed precision) or norm pass (FP64).
+ * The finest level's sweeps then run one to a launch where a solve otherwise
+ * fuses two of them or a leg (the fused pair from a zero iterate excepted).
  * Launches of steps past the solve's last step (queued before the stop test
  * was read; they find the stop flag set and do no work) are not counted.
  * mg_prof_read_kernel returns the number of counted launches of one kernel

@@ -383,19 +383,28 @@ hipError_t enqueue_mean(mg_ctx* c, hipStream_t s) {
     return cc_subtract(c->p.dim, c->p.n, nullptr, d, c->cc_mean, s);
 }
 
-// FP64 with the fused norm: the first pre-smoothing sweep of the next cycle
-// (reads the bound u, writes its ping-pong partner, leaving u as it is) and
+// FP64 with the fused norm: the first launch of the next cycle (first_sweeps;
+// reads the bound u, writes its ping-pong partner, leaving u as it is) and
 // the norm of u's residual that it sums, into d_norm.  With 'step' > 0 and
 // measurement on, the sweep is bracketed and tagged (step, kernel 1).
 hipError_t enqueue_nrm_sweep(mg_ctx* c, hipStream_t s, int step = 0, const StopTest* stop = nullptr) {
-    const TileCfg cfg = c->tl64[0].smooth_nrm;
-    const bool leg = leg_first(c->prob, c->p.n);
-    const int nparts = leg ? down2d_tiles(c->prob.op(), c->p.n)
-                           : smooth_tiles(c->p.dim, c->prob.smoother, c->p.n, cfg, c->prob.op());
+    const Problem& P = c->prob;
+    const Tiles& t = c->tl64[0];
+    const GridDesc* d = c->G64[0].d;
+    const int n = c->p.n, op = P.op(), k = first_sweeps(P, t, n, c->prof_on);
     const bool timed = prof_begin(c, step, s);
-    hipError_t e = leg ? launch_down2d<double>(c->prob.op(), c->G64[0].d, 1, c->p.n, 0, c->p.nu1, SWEEP_NORM, s)
-                       : launch_smooth<double>(c->p.dim, c->prob.smoother, c->prob.op(), c->G64[0].d, 1, c->p.n, 0,
-                                         SWEEP_NORM, cfg, s);
+    int nparts;
+    hipError_t e;
+    if (!c->prof_on && leg_ok(P, n) && k == P.nu1) {
+        nparts = down2d_tiles(op, n);
+        e = launch_down2d<double>(op, d, 1, n, 0, k, SWEEP_NORM, s);
+    } else if (k == 2) {
+        nparts = smooth3d_x2_tiles(op, n, t.pair_nrm);
+        e = launch_smooth3d_x2<double>(op, d, 1, n, 0, SWEEP_NORM, t.pair_nrm, s);
+    } else {
+        nparts = smooth_tiles(P.dim, P.smoother, n, t.smooth_nrm, op);
+        e = launch_smooth<double>(P.dim, P.smoother, op, d, 1, n, 0, SWEEP_NORM, t.smooth_nrm, s);
+    }
     if (timed) prof_end(c, step, 1, s);
     if (e != hipSuccess) return e;
     return launch_norm_finalize(c->d_spart, nparts, nparts, 0, 1, c->d_norm, s, stop);
@@ -761,6 +770,45 @@ std::vector<TileCfg> smooth2_candidates(int dim, int n) {
     return cands;
 }
 
+// Launch shapes of two sweeps in one launch (3D): by planes per workgroup, with
+// enough boxes.
+std::vector<TileCfg> pair_candidates(int n, int count) {
+    std::vector<TileCfg> cands;
+    for (int zc : {16, 32, 64, 128}) {
+        const TileCfg t{32, zc, 1, 8};
+        if (n >= 129 && zc <= n && (size_t)smooth3d_x2_tiles(OP_LAP, n, t) * (size_t)count >= kPairBoxes)
+            cands.push_back(t);
+    }
+    return cands;
+}
+
+// Two sweeps of a 3D Laplacian red-black level in one launch, the first with
+// 'flags': kept if it beats the two.  'cap': most partials of SWEEP_NORM.
+template <typename T>
+void tune_pair(const GridDesc* d, int count, int n, int flags, const TuneKey& key, int cap, Tiles& t, hipStream_t s) {
+    TileCfg cfg;
+    if (!tune_lookup(key, &cfg)) {
+        std::vector<TileCfg> cands;
+        for (TileCfg c : pair_candidates(n, count))
+            if (!(flags & SWEEP_NORM) || smooth3d_x2_tiles(OP_LAP, n, c) <= cap) cands.push_back(c);
+        auto run = [&](TileCfg c) { return launch_smooth3d_x2<T>(OP_LAP, d, count, n, 0, flags, c, s); };
+        cfg = {32, 0, 1, 8};
+        if (!cands.empty()) {
+            cfg = pick_order(pick_fastest(cands, cands[0], run, s), run, s);
+            const float t_two = time_launch(run, cfg, s);
+            const float t_sep = time_launch([&](TileCfg) {
+                (void)launch_smooth<T>(3, SM_RBGS, OP_LAP, d, count, n, 0, flags, t.sweep(flags), s);
+                return launch_smooth<T>(3, SM_RBGS, OP_LAP, d, count, n, 1, 0, t.smooth, s);
+            }, cfg, s);
+            if (!(t_two < t_sep)) cfg.zchunk = 0;
+        }
+        tune_store(key, cfg);
+    }
+    if (flags & SWEEP_NORM) t.pair_nrm = cfg;
+    else if (flags & SWEEP_PROLONG) t.pair = t.pair_pro = cfg;
+    else t.pair_zg = cfg;
+}
+
 // Tune one hierarchy (levels of 'elem' bytes).  scratch_u / scratch_f stand in
 // for caller-owned level-0 arrays.
 hipError_t tune_levels(mg_ctx* c, const Levels& L, std::vector<Tiles>& tl, void* scratch_u, void* scratch_f) {
@@ -906,6 +954,25 @@ hipError_t tune_levels(mg_ctx* c, const Levels& L, std::vector<Tiles>& tl, void*
             tl[(size_t)l].smooth_zg2 = cfg;
             if (cfg.zchunk < 0) tl[(size_t)l].smooth_zg2.zchunk = std::getenv("MG_FUSED_SMOOTH2") ? -cfg.zchunk : 0;
         }
+        // 3D: pairs of sweeps in one launch, kept if faster
+        if (dim == 3 && !var && sm == SM_RBGS) {
+            tl[(size_t)l].pair = tl[(size_t)l].pair_zg = tl[(size_t)l].pair_pro = tl[(size_t)l].pair_nrm = {32, 0, 1, 8};
+            auto pair = [&](int fl, int family) {
+                const TuneKey kp{dim, L.elem, n, family, sm, 0, 0, 0};
+                if (L.elem == 8) tune_pair<double>(d, 1, n, fl, kp, c->spart_cap, tl[(size_t)l], s);
+                else if (L.elem == 4) tune_pair<float>(d, 1, n, fl, kp, 0, tl[(size_t)l], s);
+                else tune_pair<half_t>(d, 1, n, fl, kp, 0, tl[(size_t)l], s);
+            };
+            if (c->p.nu2 >= 2) pair(SWEEP_PROLONG, 8);
+            // (32-bit and 16-bit levels have their own launch of two sweeps from zero, zg2)
+            if (c->p.nu1 >= 2 && l > 0 && L.elem == 8) pair(SWEEP_ZERO_GUESS, 9);
+            if (c->p.nu1 >= 2 && l == 0 && L.elem == 8 && c->nrm_fused) {
+                h.npart = c->d_spart;
+                e = hipMemcpyAsync(d, &h, sizeof(GridDesc), hipMemcpyHostToDevice, s);
+                if (e != hipSuccess) break;
+                pair(SWEEP_NORM, 10);
+            }
+        }
         // 2D: the first two post-smoothing sweeps in one launch, kept if faster
         if (dim == 2 && !var && sm == SM_RBGS && L.elem <= 4 && c->p.nu2 >= 2 && !leg) {
             TuneKey kp{dim, L.elem, n, 7, sm, 0, 0, 0};
@@ -999,6 +1066,10 @@ hipError_t tune_group(const Problem& P, const GridDesc* d, int count, int n, Til
         }
         t.smooth_zg2 = cfg;
         if (cfg.zchunk < 0) t.smooth_zg2.zchunk = std::getenv("MG_FUSED_SMOOTH2") ? -cfg.zchunk : 0;
+    }
+    if (smoother == SM_RBGS && dim == 3) {
+        t.pair = t.pair_pro = {32, 0, 1, 8};
+        if (P.nu2 >= 2) tune_pair<float>(d, count, n, SWEEP_PROLONG, {dim, 4, n, 8, smoother, 0, 0, bucket}, 0, t, s);
     }
     if (smoother == SM_RBGS && dim == 2 && !leg) {
         TuneKey kp{dim, 4, n, 7, smoother, 0, 0, bucket};
@@ -1252,9 +1323,13 @@ int mg_setup(const mg_params* p, void* stream, mg_ctx** out) {
         const int sm = c->prob.smoother;
         int cap = smooth_tiles(dim, sm, p->n, c->tl64[0].smooth_nrm, c->prob.op());
         if (dim == 2 && !c->cc) cap = std::max(cap, down2d_tiles(c->prob.op(), p->n));
+        if (pair_ok(c->prob, c->tl64[0], SWEEP_NORM, p->n, 1))
+            cap = std::max(cap, smooth3d_x2_tiles(c->prob.op(), p->n, c->tl64[0].pair_nrm));
         if (c->autotune)
             for (TileCfg t : tune_candidates(dim, p->n - 2, true, 0, 8, c->prob.var))
                 if (t.wv != 1) cap = std::max(cap, smooth_tiles(dim, sm, p->n, t));
+        if (c->autotune && dim == 3 && c->prob.op() == OP_LAP)
+            for (TileCfg t : pair_candidates(p->n, 1)) cap = std::max(cap, smooth3d_x2_tiles(OP_LAP, p->n, t));
         c->spart_cap = cap;
         SETUP_CK(hipMalloc((void**)&c->d_spart, sizeof(double) * (size_t)cap));
         GridDesc& d0 = c->G64[0].h[0];

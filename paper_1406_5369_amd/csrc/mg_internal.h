@@ -167,6 +167,14 @@ int smooth2d_zg2_tiles(int n, int ychunk);
 template <typename T>
 hipError_t launch_smooth2d_pro2(const GridDesc* d, int ninst, int n, int sel, TileCfg cfg, hipStream_t s);
 int smooth2d_pro2_tiles(int n, int ychunk);
+// 3D, red-black, constant operators: two sweeps from input 'sel' (bit 2: black
+// first) in one launch; the iterate goes to the partner.  flags as a sweep's: 0,
+// SWEEP_ZERO_GUESS, SWEEP_PROLONG (the correction first) or SWEEP_NORM (FP64).
+// SWEEP_NORM writes smooth3d_x2_tiles partials.
+template <typename T>
+hipError_t launch_smooth3d_x2(int op, const GridDesc* d, int ninst, int n, int sel, int flags, TileCfg cfg,
+                              hipStream_t s);
+int smooth3d_x2_tiles(int op, int n, TileCfg cfg);
 // 2D, red-black, edges 5 .. kLegMaxN: the last 'ns' (1 or 2) pre-smoothing sweeps
 // of a level (from input 'sel'; flags 0, SWEEP_ZERO_GUESS or SWEEP_NORM), residual
 // and full weighting into fc in one launch, and its correction from uc and first

@@ -3,6 +3,7 @@
 #include "mg_kern.h"
 #include "mg_smooth3d_rc.inl"
 #include "mg_smooth3d_rb.inl"
+#include "mg_smooth3d_x2.inl"
 
 namespace mg {
 namespace {
@@ -541,6 +542,42 @@ hipError_t launch_smooth3d(int sm, int op, const GridDesc* d, int sel, int flags
 }
 
 template hipError_t launch_smooth3d<MG_T>(int, int, const GridDesc*, int, int, TileCfg, dim3, hipStream_t);
+
+template <typename T, int OPV, int FL>
+hipError_t launch_smooth3d_x2_fl(const GridDesc* d, int sel, TileCfg cfg, dim3 grid, hipStream_t s) {
+    const int arg = sweep_arg(sel, cfg);
+    if (cfg.by != 32) return hipErrorInvalidValue;
+    k_smooth3d_x2<T, OPV, 2, 8, FL><<<grid, 64 * 8, 0, s>>>(d, arg, cfg.zchunk);
+    return hipGetLastError();
+}
+template <typename T, int OPV>
+hipError_t launch_smooth3d_x2_op(const GridDesc* d, int sel, int flags, TileCfg cfg, dim3 grid, hipStream_t s) {
+    switch (flags) {
+        case 0: return launch_smooth3d_x2_fl<T, OPV, 0>(d, sel, cfg, grid, s);
+        case SWEEP_ZERO_GUESS:  // smaller types: launch_smooth3d_zg2
+            if constexpr (sizeof(T) == 8) return launch_smooth3d_x2_fl<T, OPV, SWEEP_ZERO_GUESS>(d, sel, cfg, grid, s);
+            return hipErrorInvalidValue;
+        case SWEEP_PROLONG: return launch_smooth3d_x2_fl<T, OPV, SWEEP_PROLONG>(d, sel, cfg, grid, s);
+        case SWEEP_NORM:
+            if constexpr (sizeof(T) == 8) return launch_smooth3d_x2_fl<T, OPV, SWEEP_NORM>(d, sel, cfg, grid, s);
+            return hipErrorInvalidValue;
+        default: return hipErrorInvalidValue;
+    }
+}
+template <typename T>
+hipError_t launch_smooth3d_x2(int op, const GridDesc* d, int ninst, int n, int sel, int flags, TileCfg cfg,
+                              hipStream_t s) {
+    if (n < (op == OP_CC ? 2 : 5) || ninst <= 0 || cfg.zchunk < 1) return hipErrorInvalidValue;
+    if ((flags & SWEEP_NORM) && ninst != 1) return hipErrorInvalidValue;  // one partial row
+    const dim3 grid(smooth3d_x2_tiles(op, n, cfg), ninst);
+    if (op == OP_LAP) return launch_smooth3d_x2_op<T, OP_LAP>(d, sel, flags, cfg, grid, s);
+    if constexpr (sizeof(T) == 8) {
+        if (op == OP_STENCIL) return launch_smooth3d_x2_op<T, OP_STENCIL>(d, sel, flags, cfg, grid, s);
+        if (op == OP_CC) return launch_smooth3d_x2_op<T, OP_CC>(d, sel, flags, cfg, grid, s);
+    }
+    return hipErrorInvalidValue;
+}
+template hipError_t launch_smooth3d_x2<MG_T>(int, const GridDesc*, int, int, int, int, TileCfg, hipStream_t);
 
 template <typename T>
 hipError_t launch_smooth3d_zg2(const GridDesc* d, int ninst, int n, int sel, TileCfg cfg, hipStream_t s) {

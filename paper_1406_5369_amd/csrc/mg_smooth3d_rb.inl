@@ -84,10 +84,12 @@ struct PairTile {
     // plane, the planes below and above; up: the lane's node is in the pair's
     // second row (its third y-neighbour is in pair p + 1).  A cell's neighbour
     // outside the domain takes the cell's own value.
+    // ed: what the first and last pair take for the neighbour outside the tile.
     __device__ __forceinline__ T res(const T (&X)[P], const T (&O)[P], const T (&Ob)[P], const T (&Oa)[P], T f, bool up,
-                                     int z, int p) const {
+                                     int z, int p, T ed) const {
         T w = lane_prev(O[p]), e = lane_next(O[p]);
-        T y = pick(up, O[p + 1 < P ? p + 1 : p], O[p > 0 ? p - 1 : p]);
+        const T hi = O[p + 1 < P ? p + 1 : p], lo = O[p > 0 ? p - 1 : p];
+        T y = pick(up, p + 1 < P ? hi : ed, p > 0 ? lo : ed);
         T b = Ob[p], a = Oa[p];
         if constexpr (CC) {
             w = pick(gx == 0, X[p], w);
@@ -105,6 +107,10 @@ struct PairTile {
             return res_lap3(X[p], w, e, O[p], y, b, a, f, c);
         }
     }
+    __device__ __forceinline__ T res(const T (&X)[P], const T (&O)[P], const T (&Ob)[P], const T (&Oa)[P], T f, bool up,
+                                     int z, int p) const {
+        return res(X, O, Ob, Oa, f, up, z, p, O[p]);
+    }
     // The relaxed value of u at a node of pair p, plane z, with residual r.
     __device__ __forceinline__ T relaxed(T u, T r, bool up, int z, int p) const {
         T k = wd;
@@ -120,30 +126,13 @@ struct PairTile {
     __device__ __forceinline__ bool inner(bool up, int p) const { return coli && (up ? yin(2 * p + 1) : yin(2 * p)); }
 };
 
-// One red-black sweep.  Step kk (plane kk enters): the first colour on plane
-// kk-1, the second on plane kk-2, written out.  FL: 0, SWEEP_ZERO_GUESS,
-// SWEEP_PROLONG (the incoming iterate is u + P uc) or, on cells, SWEEP_NORM
-// (the incoming iterate is u - mean; sums its r^2 over the output cells).
-template <typename ST, int OP, int P, int FL, bool YE>
-struct SweepRB : PairTile<ST, OP, P, YE> {
+// A tile whose incoming planes take the coarse-grid correction P uc (PRO), in
+// order of z.
+template <typename ST, int OP, int P, bool PRO, bool YE>
+struct CorrectedTile : PairTile<ST, OP, P, YE> {
     using Base = PairTile<ST, OP, P, YE>;
     using T = arith_t<ST>;
-    using Base::c, Base::coli, Base::gx, Base::gy, Base::lane, Base::n, Base::pl, Base::rb, Base::yin, Base::y0r;
-    static constexpr int H = 2, TX = BX - 2 * H, TY = 2 * P - 2 * H;
-    static constexpr bool PRO = (FL & SWEEP_PROLONG) != 0, NRM = (FL & SWEEP_NORM) != 0, CC = OP == OP_CC;
-    static constexpr bool ZG = (FL & SWEEP_ZERO_GUESS) != 0;
-    using Storage = ST;
-
-    const MG_GLOBAL ST* __restrict__ uin;
-    MG_GLOBAL ST* __restrict__ uout;
-    const MG_GLOBAL ST* __restrict__ f;
-    int z0, z1;
-    bool s;  // of plane kk
-    T raw[2 * P], rawf[2 * P];             // plane kk+1 of u, plane kk of f (in flight)
-    T A[4][P], B[4][P], fA[4][P], fB[4][P];  // slot = plane mod 4 (dead slots take no registers)
-    T Ao[NRM ? P : 1];                     // first-colour nodes of plane kk-2 before their update
-    T mean;
-    double acc;
+    using Base::CC, Base::coli, Base::gx, Base::n, Base::yin, Base::y0r;
 
     // ---- coarse-grid correction: row 0 has odd y, lane 0 odd x, so pair p
     // needs coarse rows p (with p+1 for its first, odd row) and p+1, counted
@@ -176,13 +165,13 @@ struct SweepRB : PairTile<ST, OP, P, YE> {
         }
     }
     // Cells: both rows of a pair, both lanes of an x pair and planes 2K, 2K+1 have one parent.
-    __device__ __forceinline__ void correct_cells(int kk) {
+    __device__ __forceinline__ void correct_cells(int kk, bool zo, T (&raw)[2 * P]) {
 #pragma unroll
         for (int r = 0; r < 2 * P; ++r) raw[r] = raw[r] + cr[r / 2];
-        if (kk & 1) issue_c((kk + 1) >> 1);
+        if (zo) issue_c((kk + 1) >> 1);
     }
-    __device__ __forceinline__ void correct_entering(int kk) {
-        const bool zo = (kk & 1) != 0, zin = this->zin(kk);
+    __device__ __forceinline__ void correct_entering(int kk, bool zo, T (&raw)[2 * P]) {
+        const bool zin = this->zin(kk);
         T sum[2 * P];
         if (zo) {
             T sn[2 * P];
@@ -205,12 +194,61 @@ struct SweepRB : PairTile<ST, OP, P, YE> {
         }
     }
 
+    // zo: kk is odd
+    __device__ __forceinline__ void correct(int kk, bool zo, T (&raw)[2 * P]) {
+        if constexpr (CC) correct_cells(kk, zo, raw);
+        else correct_entering(kk, zo, raw);
+    }
+    // before plane kk, the march's first
+    __device__ __forceinline__ void correct_start(int kk) {
+        cxb = (unsigned)(min(max(gx, 0), n - 1) >> 1) * (unsigned)sizeof(ST);
+        if constexpr (CC) {
+            issue_c(kk >> 1);
+        } else {
+            T w = (gx & 1) ? T(0.5) : T(1);
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                wx[q] = w;
+                w = T(0.5) * w;
+            }
+            // plane kk needs the coarse plane kk/2 (rounded down) completed, and for odd kk the next one pending
+            issue_c((kk - (kk & 1)) >> 1);
+            coarse_sums(sy);
+            if (kk & 1) issue_c((kk + 1) >> 1);
+        }
+    }
+};
+
+// One red-black sweep.  Step kk (plane kk enters): the first colour on plane
+// kk-1, the second on plane kk-2, written out.  FL: 0, SWEEP_ZERO_GUESS,
+// SWEEP_PROLONG (the incoming iterate is u + P uc) or, on cells, SWEEP_NORM
+// (the incoming iterate is u - mean; sums its r^2 over the output cells).
+template <typename ST, int OP, int P, int FL, bool YE>
+struct SweepRB : CorrectedTile<ST, OP, P, (FL & SWEEP_PROLONG) != 0, YE> {
+    using Base = CorrectedTile<ST, OP, P, (FL & SWEEP_PROLONG) != 0, YE>;
+    using T = arith_t<ST>;
+    using Base::c, Base::coli, Base::gx, Base::gy, Base::lane, Base::n, Base::pl, Base::rb, Base::yin, Base::y0r;
+    static constexpr int H = 2, TX = BX - 2 * H, TY = 2 * P - 2 * H;
+    static constexpr bool PRO = (FL & SWEEP_PROLONG) != 0, NRM = (FL & SWEEP_NORM) != 0, CC = OP == OP_CC;
+    static constexpr bool ZG = (FL & SWEEP_ZERO_GUESS) != 0;
+    using Storage = ST;
+
+    const MG_GLOBAL ST* __restrict__ uin;
+    MG_GLOBAL ST* __restrict__ uout;
+    const MG_GLOBAL ST* __restrict__ f;
+    int z0, z1;
+    bool s;  // of plane kk
+    T raw[2 * P], rawf[2 * P];             // plane kk+1 of u, plane kk of f (in flight)
+    T A[4][P], B[4][P], fA[4][P], fB[4][P];  // slot = plane mod 4 (dead slots take no registers)
+    T Ao[NRM ? P : 1];                     // first-colour nodes of plane kk-2 before their update
+    T mean;
+    double acc;
+
     template <int Q>
     __device__ __forceinline__ void step(int kk) {
         constexpr int Q0 = Q & 3, Q1 = (Q + 3) & 3, Q2 = (Q + 2) & 3, Q3 = (Q + 1) & 3;  // planes kk .. kk-3
         s = !s;
-        if constexpr (PRO && CC) correct_cells(kk);
-        else if constexpr (PRO) correct_entering(kk);
+        if constexpr (PRO) this->correct(kk, (kk & 1) != 0, raw);
         if constexpr (NRM) {
 #pragma unroll
             for (int r = 0; r < 2 * P; ++r) raw[r] = raw[r] - mean;
@@ -270,22 +308,7 @@ struct SweepRB : PairTile<ST, OP, P, YE> {
 #pragma unroll
             for (int p = 0; p < P; ++p) A[3][p] = T(0);
         }
-        if constexpr (PRO && CC) {
-            cxb = (unsigned)(min(max(gx, 0), n - 1) >> 1) * (unsigned)sizeof(ST);
-            issue_c(kk >> 1);
-        } else if constexpr (PRO) {
-            cxb = (unsigned)(min(max(gx, 0), n - 1) >> 1) * (unsigned)sizeof(ST);
-            T w = (gx & 1) ? T(0.5) : T(1);
-#pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                wx[q] = w;
-                w = T(0.5) * w;
-            }
-            // plane kk needs the coarse plane kk/2 (rounded down) completed, and for odd kk the next one pending
-            issue_c((kk - (kk & 1)) >> 1);
-            coarse_sums(sy);
-            if (kk & 1) issue_c((kk + 1) >> 1);
-        }
+        if constexpr (PRO) this->correct_start(kk);
         if constexpr (!ZG) this->template load<0, 2 * P>(uin, kk, raw);
         for (;;) {
             step<0>(kk);

@@ -39,6 +39,13 @@ struct Tiles {
     // sweeps (the coarse-grid correction fused into the first) in one launch
     // (zchunk rows per wavefront; 0 = separate sweeps, the autotuner's choice)
     TileCfg smooth_pro2{12, 0};
+    // 3D red-black, constant operators: two sweeps in one launch, by the flags of
+    // the first (zchunk 0: apart)
+    TileCfg pair{32, 0, 1, 8}, pair_zg{32, 0, 1, 8}, pair_pro{32, 0, 1, 8}, pair_nrm{32, 0, 1, 8};
+    const TileCfg& pair_of(int flags) const {
+        if (flags & SWEEP_NORM) return pair_nrm;
+        return (flags & SWEEP_ZERO_GUESS) ? pair_zg : ((flags & SWEEP_PROLONG) ? pair_pro : pair);
+    }
     const TileCfg& sweep(int flags) const {
         if (flags & SWEEP_NORM) return smooth_nrm;
         return (flags & SWEEP_ZERO_GUESS) ? smooth_zg : ((flags & SWEEP_PROLONG) ? smooth_pro : smooth);
@@ -91,8 +98,13 @@ struct Problem {
 // Whether a level of edge n runs each of its legs with its last two pre- and
 // first two post-smoothing sweeps in one launch (launch_down2d, launch_up2d).
 bool leg_ok(const Problem& P, int n);
-// Whether the first pre-smoothing sweep is in that launch.
-inline bool leg_first(const Problem& P, int n) { return leg_ok(P, n) && P.nu1 <= 2; }
+// Whether two sweeps of a level of 'ninst' grids, the first with 'flags', run
+// as one launch (launch_smooth3d_x2).
+bool pair_ok(const Problem& P, const Tiles& t, int flags, int n, int ninst);
+constexpr size_t kPairBoxes = 200;  // fewest boxes of such a launch
+// Pre-smoothing sweeps in the launch that starts level 0's descending leg with
+// SWEEP_NORM; with a leg its restriction, too.
+int first_sweeps(const Problem& P, const Tiles& t, int n, bool measured);
 
 // Coarse levels of a V-cycle run by the single-workgroup tail kernel:
 // groups[first..L-1], one TailDesc per instance (first = -1: no tail).
@@ -109,9 +121,9 @@ int tail_first_level(int dim, int elem, int op, const std::vector<int>& n, bool 
 
 // V-cycle over groups[0..L-1] (groups[l] holds every instance's level l);
 // zero_top: the iterate at level 0 is known to be zero.  Works in precision T.
-// first_done: level 0's first pre-smoothing sweep has already run (its result
-// is in the ping-pong partner t; the cycle continues from the second sweep),
-// or, with leg_first, its whole descending leg.
+// first_done: level 0's first launch (first_sweeps) has already run; its result
+// is in the ping-pong partner t and the cycle continues from there.
+// With prof_ev (measurement) level 0 runs its sweeps apart.
 template <typename T>
 hipError_t vcycle(const Problem& P, const std::vector<Group>& groups, bool zero_top, const std::vector<Tiles>& tiles,
                   hipStream_t s, hipEvent_t* prof_ev, int* prof_n, int prof_cap, const TailPlan* tail = nullptr,

@@ -57,12 +57,21 @@ Tiles lds_tiles(int dim, int n, int smoother) {
     return t;
 }
 
+// Two sweeps in one launch: long chunks, since a chunk costs eight planes more
+// than it owns (257^3 FP64, with the norm: 165 / 140 / 123 / 110 us with 8 / 16 / 32
+// / 64 planes), but enough of them where grids of a batch make up the chip's load.
+static void default_pairs(Tiles& t, int n, bool zg) {
+    t.pair = t.pair_pro = t.pair_nrm = {32, n <= 129 ? 32 : 64, 1, 8};
+    if (zg) t.pair_zg = t.pair;
+}
+
 Tiles default_tiles(int dim, int elem_bytes, int n, int smoother, int op) {
     if (op == OP_CC) {  // edges down to one cell
         Tiles t;
         if (dim == 2) t.smooth = {n <= 512 ? 8 : 16, 1};
         else t.smooth = {8, std::min(32, std::max(2, n / 16)), 1, 1};
         t.smooth_zg = t.smooth_pro = t.smooth_nrm = t.smooth;
+        if (dim == 3 && smoother == SM_RBGS) default_pairs(t, n, true);
         return t;
     }
     Tiles t = lds_tiles(dim, n, smoother);
@@ -78,6 +87,7 @@ Tiles default_tiles(int dim, int elem_bytes, int n, int smoother, int op) {
         // The two sweeps from zero in one launch: 33^3 5.5 us against 3.9 + 4.5,
         // 65^3 7.2 / 8.7, 129^3 13.4 / 15.9 us.
         if (elem_bytes <= 4 && op == OP_LAP) t.smooth_zg2 = {12, zc};
+        default_pairs(t, n, t.smooth_zg2.zchunk == 0);
     }
     return t;
 }
@@ -182,45 +192,124 @@ bool leg_ok(const Problem& P, int n) {
            n <= kLegMaxN;
 }
 
+// Two sweeps in one launch where its boxes cover most of the chip: a box's march
+// is long (about 1 us a plane when it has the compute unit to itself), and on
+// fewer boxes one-wavefront tiles finish sooner.  129^3 FP32, one grid (72
+// boxes): 38 us against 11.5 + 9; seven grids (504): 49 us against 52 + 48.
+bool pair_ok(const Problem& P, const Tiles& t, int flags, int n, int ninst) {
+    const TileCfg& c = t.pair_of(flags);
+    return P.dim == 3 && P.smoother == SM_RBGS && P.op() != OP_VAR && c.zchunk > 0 &&
+           (size_t)smooth3d_x2_tiles(P.op(), n, c) * (size_t)ninst >= kPairBoxes;
+}
+
+int first_sweeps(const Problem& P, const Tiles& t, int n, bool measured) {
+    if (measured || P.nu1 < 2) return 1;
+    if (leg_ok(P, n)) return P.nu1 == 2 ? 2 : 1;
+    return pair_ok(P, t, SWEEP_NORM, n, 1) ? 2 : 1;
+}
+
 // Post-smoothing select bits: the symmetric red-black smoother relaxes black first.
 inline int post_sel(const Problem& P, int cur) { return cur | (P.sym ? SEL_BLACK_FIRST : 0); }
 
-// The descending leg of a leg_ok level: nu1 - ns plain sweeps, then the launch
-// that also restricts.  first_done as in vcycle.  'top': level 0, whose plain
-// sweeps are measured.  Returns the buffer of the iterate in cur.
+// Launches of a level's ascending leg that change the iterate's buffer.
 template <typename T>
-hipError_t leg_down(const Problem& P, const Group& g, const Tiles& t, bool top, bool zero, bool first_done, int& cur,
-                    hipStream_t s, Prof& prof) {
+int up_launches(const Problem& P, const Tiles& t, int n, int ninst, bool apart) {
+    if (P.nu2 == 0) return 0;
+    int i = 0, k = 0;
+    if ((!apart && leg_ok(P, n)) || post2_ok<T>(P, P.dim, t)) {
+        i = P.nu2 >= 2 ? 2 : 1;
+        k = 1;
+    }
+    for (; i < P.nu2; ++k) i += !apart && i + 1 < P.nu2 && pair_ok(P, t, i == 0 ? SWEEP_PROLONG : 0, n, ninst) ? 2 : 1;
+    return k;
+}
+
+// The descending leg of a level: nu1 sweeps, the residual and its restriction,
+// as few launches as the level's rules give.  top: level 0, whose plain sweeps
+// are measured (and then run apart); first_done as in vcycle.  'cur' is the
+// buffer of the iterate (0 u, 1 t).
+template <typename T>
+hipError_t descend(const Problem& P, const Group& g, const Tiles& t, bool top, bool zero, bool first_done, int& cur,
+                   hipStream_t s, Prof& prof) {
+    const bool apart = top && prof.ev;
     cur = first_done ? 1 : 0;
-    if (first_done && leg_first(P, g.n)) return hipSuccess;
+    int i = first_done ? first_sweeps(P, t, g.n, apart) : 0;
+    const bool leg = !apart && leg_ok(P, g.n);
     const int ns = P.nu1 >= 2 ? 2 : 1;
-    int i = first_done ? 1 : 0;
-    for (; i < P.nu1 - ns; ++i) {
+    if (leg && first_done && i == P.nu1) return hipSuccess;
+    const int last = leg ? P.nu1 - ns : P.nu1;  // the leg's launch takes the others
+    if (!leg && i == 0 && smooth2_ok<T>(P, P.dim, t, zero)) {
+        // sweeps 1 and 2 from the zero iterate, into the buffer that an even
+        // number of launches brings to u
+        int k = up_launches<T>(P, t, g.n, g.ninst, apart);
+        for (int j = 2; j < P.nu1; j += !apart && pair_ok(P, t, 0, g.n, g.ninst) && j + 1 < P.nu1 ? 2 : 1) ++k;
+        cur = k & 1;
+        MG_TRY(launch_smooth2<T>(P.dim, g, t, cur ^ 1, s));
+        i = 2;
+    }
+    bool fused = false;
+    while (i < last) {
         const int flags = (i == 0 && zero) ? SWEEP_ZERO_GUESS : 0;
-        const bool timed = top && flags == 0;
-        if (timed) prof.begin();
-        MG_TRY(launch_smooth<T>(2, P.smoother, P.op(), g.d, g.ninst, g.n, cur, flags, t.sweep(flags), s));
-        if (timed) prof.end();
+        if (!apart && i + 1 < last && pair_ok(P, t, flags, g.n, g.ninst)) {
+            MG_TRY(launch_smooth3d_x2<T>(P.op(), g.d, g.ninst, g.n, cur, flags, t.pair_of(flags), s));
+            i += 2;
+        } else if (!leg && i == P.nu1 - 1 && flags == 0 && fused_restrict_ok<T>(P, P.dim, t)) {
+            // the last sweep carries the residual and restriction
+            MG_TRY(launch_smooth_restrict3d<T>(g.d, g.ninst, g.n, cur, t.fused, s));
+            fused = true;
+            ++i;
+        } else {
+            const bool timed = top && flags == 0;  // plain finest-level sweeps only
+            if (timed) prof.begin();
+            MG_TRY(launch_smooth<T>(P.dim, P.smoother, P.op(), g.d, g.ninst, g.n, cur, flags, t.sweep(flags), s));
+            if (timed) prof.end();
+            ++i;
+        }
         cur ^= 1;
     }
-    MG_TRY(launch_down2d<T>(P.op(), g.d, g.ninst, g.n, cur, ns, (i == 0 && zero) ? SWEEP_ZERO_GUESS : 0, s));
-    cur ^= 1;
+    if (leg) {
+        MG_TRY(launch_down2d<T>(P.op(), g.d, g.ninst, g.n, cur, ns, (i == 0 && zero) ? SWEEP_ZERO_GUESS : 0, s));
+        cur ^= 1;
+        return hipSuccess;
+    }
+    if (P.nu1 == 0 && zero) MG_TRY(launch_zero_u<T>(P.dim, g.d, g.ninst, g.n, s));
+    if (!fused) MG_TRY(launch_restrict<T>(P.dim, P.op(), g.d, g.ninst, g.n, cur, t.restr, s));
     return hipSuccess;
 }
 
-// The ascending leg of a leg_ok level; the iterate ends in u.
+// The ascending leg of a level: the correction and nu2 sweeps; the iterate
+// ends in u.
 template <typename T>
-hipError_t leg_up(const Problem& P, const Group& g, const Tiles& t, bool top, int cur, hipStream_t s, Prof& prof) {
-    const int ns = P.nu2 >= 2 ? 2 : 1;
-    MG_TRY(launch_up2d<T>(P.op(), g.d, g.ninst, g.n, post_sel(P, cur), ns, s));
-    cur ^= 1;
-    for (int i = ns; i < P.nu2; ++i) {
-        if (top) prof.begin();
-        MG_TRY(launch_smooth<T>(2, P.smoother, P.op(), g.d, g.ninst, g.n, post_sel(P, cur), 0, t.sweep(0), s));
-        if (top) prof.end();
+hipError_t ascend(const Problem& P, const Group& g, const Tiles& t, bool top, int cur, hipStream_t s, Prof& prof) {
+    const bool apart = top && prof.ev;
+    int i = 0;
+    if (P.nu2 == 0) {
+        MG_TRY(launch_prolong<T>(P.dim, P.op(), g.d, g.ninst, g.n, cur, s));
+    } else if (!apart && leg_ok(P, g.n)) {
+        i = P.nu2 >= 2 ? 2 : 1;
+        MG_TRY(launch_up2d<T>(P.op(), g.d, g.ninst, g.n, post_sel(P, cur), i, s));
+        cur ^= 1;
+    } else if (cur == 1 && post2_ok<T>(P, P.dim, t)) {
+        MG_TRY(launch_smooth2d_pro2<T>(g.d, g.ninst, g.n, post_sel(P, cur), t.smooth_pro2, s));
+        cur = 0;
+        i = 2;
+    }
+    while (i < P.nu2) {
+        const int flags = i == 0 ? SWEEP_PROLONG : 0;  // the first sweep adds P uc while loading
+        if (!apart && i + 1 < P.nu2 && pair_ok(P, t, flags, g.n, g.ninst)) {
+            MG_TRY(launch_smooth3d_x2<T>(P.op(), g.d, g.ninst, g.n, post_sel(P, cur), flags, t.pair_of(flags), s));
+            i += 2;
+        } else {
+            const bool timed = top && flags == 0;
+            if (timed) prof.begin();
+            MG_TRY(launch_smooth<T>(P.dim, P.smoother, P.op(), g.d, g.ninst, g.n, post_sel(P, cur), flags,
+                                    t.sweep(flags), s));
+            if (timed) prof.end();
+            ++i;
+        }
         cur ^= 1;
     }
-    if (cur == 1) MG_TRY(launch_copy_t_to_u<T>(2, g.d, g.ninst, g.n, s));
+    if (cur == 1) MG_TRY(launch_copy_t_to_u<T>(P.dim, g.d, g.ninst, g.n, s));
     return hipSuccess;
 }
 
@@ -240,28 +329,8 @@ hipError_t cycle_rec(const Problem& P, const std::vector<Group>& G, int l, int k
         return launch_tail<T>(dim, P.smoother, P.op(), tail->d, tail->ninst, P.nu1, P.nu2, P.sym ? 1 : 0, kind, zero,
                               s);
     if (l == L - 1) return coarse_solve<T>(P, g, s);
-    const bool leg = leg_ok(P, g.n);
-    int cur = first_done ? 1 : 0;
-    int i0 = first_done ? 1 : 0;
-    if (leg) {
-        MG_TRY(leg_down<T>(P, g, tiles[(size_t)l], l == 0, zero, first_done, cur, s, prof));
-        i0 = P.nu1;
-    } else if (!first_done && smooth2_ok<T>(P, dim, tiles[(size_t)l], zero)) {
-        // sweeps 1 and 2 from the zero iterate: the result lands in u
-        MG_TRY(launch_smooth2<T>(dim, g, tiles[(size_t)l], 1, s));
-        i0 = 2;
-    }
-    for (int i = i0; i < P.nu1; ++i) {
-        const int flags = (i == 0 && zero) ? SWEEP_ZERO_GUESS : 0;
-        const bool timed = l == 0 && flags == 0;
-        if (timed) prof.begin();
-        MG_TRY(launch_smooth<T>(dim, P.smoother, P.op(), g.d, g.ninst, g.n, cur, flags, tiles[(size_t)l].sweep(flags),
-                                s));
-        if (timed) prof.end();
-        cur ^= 1;
-    }
-    if (P.nu1 == 0 && zero) MG_TRY(launch_zero_u<T>(dim, g.d, g.ninst, g.n, s));
-    if (!leg) MG_TRY(launch_restrict<T>(dim, P.op(), g.d, g.ninst, g.n, cur, tiles[(size_t)l].restr, s));
+    int cur;
+    MG_TRY(descend<T>(P, g, tiles[(size_t)l], l == 0, zero, first_done, cur, s, prof));
     if (kind == 0) {
         MG_TRY(cycle_rec<T>(P, G, l + 1, 0, true, tiles, s, prof, tail));
     } else if (kind == 1) {
@@ -271,20 +340,7 @@ hipError_t cycle_rec(const Problem& P, const std::vector<Group>& G, int l, int k
         MG_TRY(cycle_rec<T>(P, G, l + 1, 2, true, tiles, s, prof, tail));
         MG_TRY(cycle_rec<T>(P, G, l + 1, 0, false, tiles, s, prof, tail));
     }
-    if (leg) return leg_up<T>(P, g, tiles[(size_t)l], l == 0, cur, s, prof);
-    const bool fuse = P.nu2 > 0;
-    if (!fuse) MG_TRY(launch_prolong<T>(dim, P.op(), g.d, g.ninst, g.n, cur, s));
-    for (int i = 0; i < P.nu2; ++i) {
-        const int flags = (i == 0 && fuse) ? SWEEP_PROLONG : 0;
-        const bool timed = l == 0 && flags == 0;
-        if (timed) prof.begin();
-        MG_TRY(launch_smooth<T>(dim, P.smoother, P.op(), g.d, g.ninst, g.n, post_sel(P, cur), flags,
-                                tiles[(size_t)l].sweep(flags), s));
-        if (timed) prof.end();
-        cur ^= 1;
-    }
-    if (cur == 1) MG_TRY(launch_copy_t_to_u<T>(dim, g.d, g.ninst, g.n, s));
-    return hipSuccess;
+    return ascend<T>(P, g, tiles[(size_t)l], l == 0, cur, s, prof);
 }
 
 template <typename T>
@@ -305,46 +361,9 @@ hipError_t vcycle(const Problem& P, const std::vector<Group>& G, bool zero_top, 
     if (stop == 0 && !use_tail) return coarse_solve<T>(P, G[0], s);
     std::vector<int> sel((size_t)L, 0);
     // descending leg: presmoothing, residual, restriction (Algorithm 1)
-    for (int l = 0; l < stop; ++l) {
-        const Group& g = G[(size_t)l];
-        const bool zero = l == 0 ? zero_top : true;
-        if (leg_ok(P, g.n)) {
-            MG_TRY(leg_down<T>(P, g, tiles[(size_t)l], l == 0, zero, l == 0 && first_done, sel[(size_t)l], s, prof));
-            continue;
-        }
-        // the last sweep may carry the residual and restriction (a plain red-first sweep)
-        const bool skip1 = l == 0 && first_done;
-        // sweeps 1 and 2 from the zero iterate in one launch (result in u)
-        const bool two = !skip1 && smooth2_ok<T>(P, dim, tiles[(size_t)l], zero);
-        const bool fuse = fused_restrict_ok<T>(P, dim, tiles[(size_t)l]) && P.nu1 >= (two ? 3 : (zero ? 2 : 1));
-        int cur = skip1 ? 1 : 0;
-        int i0 = skip1 ? 1 : 0;
-        // with the fused post-smoothing pair on this level the two sweeps land
-        // in t, so that the pair (t -> u) leaves the iterate in u
-        const bool post2 = two && P.nu1 == 2 && post2_ok<T>(P, dim, tiles[(size_t)l]);
-        if (two) {
-            MG_TRY(launch_smooth2<T>(dim, g, tiles[(size_t)l], post2 ? 0 : 1, s));
-            i0 = 2;
-            cur = post2 ? 1 : 0;
-        }
-        for (int i = i0; i < P.nu1; ++i) {
-            const int flags = (i == 0 && zero) ? SWEEP_ZERO_GUESS : 0;
-            if (fuse && i == P.nu1 - 1) {
-                MG_TRY(launch_smooth_restrict3d<T>(g.d, g.ninst, g.n, cur, tiles[(size_t)l].fused, s));
-                cur ^= 1;
-                continue;
-            }
-            const bool timed = l == 0 && flags == 0;  // plain finest-level sweeps only
-            if (timed) prof.begin();
-            MG_TRY(launch_smooth<T>(dim, P.smoother, P.op(), g.d, g.ninst, g.n, cur, flags,
-                                    tiles[(size_t)l].sweep(flags), s));
-            if (timed) prof.end();
-            cur ^= 1;
-        }
-        if (P.nu1 == 0 && zero) MG_TRY(launch_zero_u<T>(dim, g.d, g.ninst, g.n, s));
-        if (!fuse) MG_TRY(launch_restrict<T>(dim, P.op(), g.d, g.ninst, g.n, cur, tiles[(size_t)l].restr, s));
-        sel[(size_t)l] = cur;
-    }
+    for (int l = 0; l < stop; ++l)
+        MG_TRY(descend<T>(P, G[(size_t)l], tiles[(size_t)l], l == 0, l == 0 ? zero_top : true, l == 0 && first_done,
+                          sel[(size_t)l], s, prof));
     if (use_tail) {
         // every level from 'stop' to the coarsest in one launch, from a zero guess
         MG_TRY(launch_tail<T>(dim, P.smoother, P.op(), tail->d, tail->ninst, P.nu1, P.nu2, P.sym ? 1 : 0, 0, true,
@@ -354,33 +373,8 @@ hipError_t vcycle(const Problem& P, const std::vector<Group>& G, bool zero_top, 
         MG_TRY(coarse_solve<T>(P, G[(size_t)L - 1], s));
     }
     // ascending leg: interpolation + correction, postsmoothing
-    for (int l = stop - 1; l >= 0; --l) {
-        const Group& g = G[(size_t)l];
-        int cur = sel[(size_t)l];
-        if (leg_ok(P, g.n)) {
-            MG_TRY(leg_up<T>(P, g, tiles[(size_t)l], l == 0, cur, s, prof));
-            continue;
-        }
-        const bool fuse = P.nu2 > 0;  // the first post-sweep adds P uc while loading
-        if (!fuse) MG_TRY(launch_prolong<T>(dim, P.op(), g.d, g.ninst, g.n, cur, s));
-        int i0 = 0;
-        if (cur == 1 && post2_ok<T>(P, dim, tiles[(size_t)l])) {
-            // post-sweeps 1 and 2 (correction in the first), t -> u
-            MG_TRY(launch_smooth2d_pro2<T>(g.d, g.ninst, g.n, post_sel(P, cur), tiles[(size_t)l].smooth_pro2, s));
-            cur = 0;
-            i0 = 2;
-        }
-        for (int i = i0; i < P.nu2; ++i) {
-            const int flags = (i == 0 && fuse) ? SWEEP_PROLONG : 0;
-            const bool timed = l == 0 && flags == 0;
-            if (timed) prof.begin();
-            MG_TRY(launch_smooth<T>(dim, P.smoother, P.op(), g.d, g.ninst, g.n, post_sel(P, cur), flags,
-                                    tiles[(size_t)l].sweep(flags), s));
-            if (timed) prof.end();
-            cur ^= 1;
-        }
-        if (cur == 1) MG_TRY(launch_copy_t_to_u<T>(dim, g.d, g.ninst, g.n, s));
-    }
+    for (int l = stop - 1; l >= 0; --l)
+        MG_TRY(ascend<T>(P, G[(size_t)l], tiles[(size_t)l], l == 0, sel[(size_t)l], s, prof));
     return hipSuccess;
 }
 

@@ -454,6 +454,12 @@ int smooth2_tiles(int n, TileCfg cfg) {
     return cdiv(m, BX - 6) * cdiv(m, cfg.by - 6) * nzchunks(m, cfg.zchunk);
 }
 
+// Tiles of two fused 3D sweeps: (64 - 8) x (by - 8) nodes per workgroup times z-chunks
+int smooth3d_x2_tiles(int op, int n, TileCfg cfg) {
+    const int m = op == OP_CC ? n : n - 2;
+    return cdiv(m, BX - 8) * cdiv(m, cfg.by - 8) * nzchunks(m, cfg.zchunk);
+}
+
 // Tiles of the fused kernel: coarse nodes per workgroup 28 x (BY-7)/2 times zc planes
 int smooth_restrict_tiles(int nf, TileCfg cfg) {
     const int nc = (nf - 1) / 2 + 1, CX = 28, CY = (cfg.by - 7) / 2;
