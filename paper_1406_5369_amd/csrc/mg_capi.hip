@@ -1577,7 +1577,22 @@ static bool valid_cfg(TileCfg c, int dim, int elem, bool var, int family) {
 }
 
 // Temporary device descriptor for a context-free call; the stream is synchronised before release.
-static int with_desc(const GridDesc& h, hipStream_t s, GridDesc** d) {
+static // Face coefficients of a 3D grid with nodal coefficients k, for one launch
+// (else none).
+int level_faces(int dim, int elem, int n, const void* k, hipStream_t s, void** fx) {
+    *fx = nullptr;
+    if (!k || dim != 3) return MG_OK;
+    CK(hipMalloc(fx, 3 * npts(3, n) * (size_t)elem));
+    const hipError_t e = elem == 8 ? launch_faces3d<double>((const double*)k, (double*)*fx, n, s)
+                                   : launch_faces3d<float>((const float*)k, (float*)*fx, n, s);
+    if (e == hipSuccess) return MG_OK;
+    (void)hipStreamSynchronize(s);
+    (void)hipFree(*fx);
+    *fx = nullptr;
+    return dev_status(e);
+}
+
+int with_desc(const GridDesc& h, hipStream_t s, GridDesc** d) {
     CK(hipMalloc((void**)d, sizeof(GridDesc)));
     CK(hipMemcpyAsync(*d, &h, sizeof(GridDesc), hipMemcpyHostToDevice, s));
     return MG_OK;
@@ -1621,19 +1636,11 @@ int mg_level_smooth(int dim, int n, int dtype, int smoother, double omega, const
     h.wd = level_wd(dim, n, omega);
     h.omega = omega;
     void* fxt = nullptr;  // face coefficients of a 3D variable-coefficient grid (freed after the sweep)
-    if (k && dim == 3) {
-        CK(hipMalloc(&fxt, 3 * npts(3, n) * (size_t)elem));
-        const hipError_t ef = elem == 8 ? launch_faces3d<double>((const double*)k, (double*)fxt, n, s)
-                                        : launch_faces3d<float>((const float*)k, (float*)fxt, n, s);
-        if (ef != hipSuccess) {
-            (void)hipStreamSynchronize(s);
-            (void)hipFree(fxt);
-            return dev_status(ef);
-        }
-        h.fx = fxt;
-    }
+    int r = level_faces(dim, elem, n, k, s, &fxt);
+    if (r != MG_OK) return r;
+    h.fx = fxt;
     GridDesc* d = nullptr;
-    int r = with_desc(h, s, &d);
+    r = with_desc(h, s, &d);
     if (r != MG_OK) {
         (void)hipStreamSynchronize(s);
         if (fxt) (void)hipFree(fxt);
@@ -1742,13 +1749,23 @@ int mg_level_residual_restrict(int dim, int n, int dtype, const void* k, const v
     h.fc = fc;
     h.n = n;
     h.c = level_c(n);
-    GridDesc* d = nullptr;
-    int r = with_desc(h, s, &d);
+    void* fxt = nullptr;  // face coefficients of a 3D variable-coefficient grid (freed after the launch)
+    int r = level_faces(dim, elem, n, k, s, &fxt);
     if (r != MG_OK) return r;
+    h.fx = fxt;
+    GridDesc* d = nullptr;
+    r = with_desc(h, s, &d);
+    if (r != MG_OK) {
+        (void)hipStreamSynchronize(s);
+        if (fxt) (void)hipFree(fxt);
+        return r;
+    }
     hipError_t e = elem == 8   ? launch_restrict<double>(dim, k != nullptr, d, 1, n, 0, cfg, s)
                    : elem == 4 ? launch_restrict<float>(dim, k != nullptr, d, 1, n, 0, cfg, s)
                                : launch_restrict<half_t>(dim, false, d, 1, n, 0, cfg, s);
-    return finish_desc(d, s, e);
+    r = finish_desc(d, s, e);  // synchronises the stream
+    if (fxt) (void)hipFree(fxt);
+    return r;
 }
 
 int mg_level_prolong_correct(int dim, int n, int dtype, void* u, const void* ec, void* stream) {

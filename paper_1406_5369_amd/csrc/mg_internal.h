@@ -131,7 +131,6 @@ inline int sweep_arg(int sel, const TileCfg& c) { return (sel & (1 | SEL_BLACK_F
 
 // Number of workgroups in x for a level of n nodes per axis (one instance).
 int smooth_tiles(int dim, int sm, int n, TileCfg cfg, int op = OP_LAP);
-int restrict_tiles(int dim, int nf, TileCfg cfg);
 int smooth_restrict_tiles(int nf, TileCfg cfg);
 int smooth2_tiles(int n, TileCfg cfg);
 int norm_tiles(int dim, int n, TileCfg cfg);

@@ -45,13 +45,10 @@ Tiles lds_tiles(int dim, int n, int smoother) {
     t.smooth = t.smooth_zg = t.smooth_pro = t.smooth_nrm = {by, heuristic_zchunk(3, n, by, H, target), 1,
                                                            by >= 16 ? 8 : 4};
     const int nc = (n - 1) / 2 + 1;
-    const int rb = 16;
-    // restriction tiles: 30 x ((rb-3)/2) coarse nodes per z-chunk of coarse planes
+    // restriction columns: 30 x 4 coarse nodes per chunk of coarse planes
     {
-        const int mc = nc - 2;
-        const int cols = ((mc + 29) / 30) * ((mc + (rb - 3) / 2 - 1) / ((rb - 3) / 2));
-        const int chunks = std::max(1, (target + cols - 1) / std::max(cols, 1));
-        t.restr = {rb, std::max(1, (mc + chunks - 1) / chunks)};
+        const int mc = nc - 2, cols = ((mc + 29) / 30) * ((mc + 3) / 4);
+        t.restr = {16, std::max(2, mc * cols / 2048)};
     }
     t.norm = {by, heuristic_zchunk(3, n, by, 1, target)};
     return t;

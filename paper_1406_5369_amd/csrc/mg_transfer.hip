@@ -89,112 +89,170 @@ __global__ __launch_bounds__(NT) void k_restrict2d(const GridDesc* __restrict__ 
     }
 }
 
-// 3D: marching over fine planes; step m publishes u plane m, computes the
-// residual of plane m-1 and, once planes 2K-1..2K+1 are in the residual ring,
-// the coarse plane K.
+// 3D residual and full weighting: one wavefront marches a 64-wide column of
+// planes, its rows in registers.  Lane = x (coarse column x/2 at the even
+// lanes, 30 of them), the thread holds the 2 CY + 3 rows of u around its CY
+// coarse rows.  Per plane it forms the residual of 2 CY + 1 rows; the sums over
+// x come from the adjacent lanes, those over y from its own rows, and of a
+// plane only the four sums per coarse row that full weighting needs again are
+// kept for the next.  No LDS, no barrier; every residual that a stored coarse
+// node needs lies on inner nodes, so nothing is masked.
+//
+// What bounds it is memory: u's rows are read (2 CY + 3) / 2 CY times, out of
+// the caches.  Variable coefficients read the faces' coefficients (three arrays)
+// where forming them from the nodal ones costs six divisions per node.
+// Measured against an LDS tile with two barriers a plane: 513^3 FP32 293 / 318
+// us (1.15 GB: 185 us at 6.2 TB/s), 257^3 FP64 66 / 96, 129^3 FP64 11.5 / 23,
+// seven grids of 129^3 FP32 25 / 61, variable coefficients 257^3 FP32 81 / 126.
+template <typename T, int OP, int BY>
+__host__ __device__ constexpr int restrict3d_cy() {
+    constexpr bool wide = sizeof(T) <= 4 && OP != OP_VAR;
+    return BY == 8 ? 2 : (OP == OP_VAR ? (sizeof(T) == 8 ? 2 : 3) : (BY == 32 && wide ? 6 : 4));
+}
+
 template <typename ST, int OP, int BY>
-__global__ __launch_bounds__(NT) void k_restrict3d(const GridDesc* __restrict__ descs, int sel, int zchunk) {
-    constexpr bool VAR = OP == OP_VAR;
+struct Restrict3 {
     using T = arith_t<ST>;
-    const GridDesc d = descs[blockIdx.y];
+    static constexpr bool VAR = OP == OP_VAR;
+    static constexpr int CX = 30, CY = restrict3d_cy<ST, OP, BY>();
+    static constexpr int RR = 2 * CY + 1, UR = RR + 2;
+    const MG_GLOBAL ST* __restrict__ u;
+    const MG_GLOBAL ST* __restrict__ f;
+    const MG_GLOBAL T* __restrict__ fx;
+    MG_GLOBAL ST* __restrict__ fc;
+    int n, nc, X, Y0, Z0, Z1;
+    bool colX;
+    T c, sc[7];
+    size_t pl;
+    unsigned rb[UR];                 // byte offset of the lane's node of each row of u (clamped)
+    T U[4][UR], F[2][RR];            // planes rp-1 .. rp+2 of u, rp and rp+1 of f, by plane
+    T kx[VAR ? 2 : 1][RR], ky[VAR ? 2 : 1][RR + 1], kz[VAR ? 4 : 1][RR];
+    T cb[CY], xb[CY], yb[CY], xyb[CY];  // of the last odd plane: R, and its sums over x, y and both
+    T cc[CY], fcs[CY], xyc[CY];         // of the even plane: R, x and y sums, corner sums
+
+    __device__ __forceinline__ void load_u(int z, T (&dst)[UR]) const {
+        const PlaneBuf<ST> b(u + (size_t)min(z, n - 1) * pl, pl);
+#pragma unroll
+        for (int i = 0; i < UR; ++i) dst[i] = (T)b.load(rb[i]);
+    }
+    __device__ __forceinline__ void load_f(int z, T (&dst)[RR]) const {
+        const PlaneBuf<ST> b(f + (size_t)min(z, n - 1) * pl, pl);
+#pragma unroll
+        for (int i = 0; i < RR; ++i) dst[i] = (T)b.load(rb[i + 1]);
+    }
+    template <int R>
+    __device__ __forceinline__ void load_k(int axis, int z, int r0, T (&dst)[R]) const {
+        const PlaneBuf<T> b(fx + ((size_t)axis * n + (size_t)min(z, n - 1)) * pl, pl);
+#pragma unroll
+        for (int i = 0; i < R; ++i) dst[i] = b.load(rb[i + r0]);
+    }
+    // Residual plane rp (odd where Q is even).
+    template <int Q>
+    __device__ __forceinline__ void step(int rp) {
+        constexpr int S0 = Q, S1 = (Q + 1) & 3, S2 = (Q + 2) & 3, S3 = (Q + 3) & 3, H = Q & 1;
+        load_u(rp + 2, U[S3]);
+        load_f(rp + 1, F[H ^ 1]);
+        if constexpr (VAR) {
+            load_k(0, rp + 1, 1, kx[H ^ 1]);
+            load_k(1, rp + 1, 0, ky[H ^ 1]);
+            load_k(2, rp + 1, 1, kz[S2]);
+        }
+        T R[RR], x[RR];
+#pragma unroll
+        for (int i = 0; i < RR; ++i) {
+            const T uC = U[S1][i + 1], w = lane_prev(uC), e = lane_next(uC);
+            if constexpr (VAR) {
+                T ds;
+                R[i] = res_var3f(uC, w, e, U[S1][i], U[S1][i + 2], U[S0][i + 1], U[S2][i + 1], lane_prev(kx[H][i]),
+                                 kx[H][i], ky[H][i], ky[H][i + 1], kz[S0][i], kz[S1][i], F[H][i], c, ds);
+            } else {
+                R[i] = res_const3<OP>(uC, w, e, U[S1][i], U[S1][i + 2], U[S0][i + 1], U[S2][i + 1], F[H][i], c, sc);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < RR; ++i) x[i] = lane_prev(R[i]) + lane_next(R[i]);
+        if constexpr (H == 0) {
+            const int K = (rp - 1) >> 1;  // rp is the plane above coarse plane K
+            const bool out = K >= Z0;
+#pragma unroll
+            for (int j = 0; j < CY; ++j) {
+                const T ca = R[2 * j + 1], xa = x[2 * j + 1], ya = R[2 * j] + R[2 * j + 2], xya = x[2 * j] + x[2 * j + 2];
+                const T faces = fcs[j] + (cb[j] + ca);
+                const T edges = (xyc[j] + (xb[j] + xa)) + (yb[j] + ya);
+                const T corners = xyb[j] + xya;
+                const T v = ((T(0.125) * cc[j] + T(0.0625) * faces) + T(0.03125) * edges) + T(0.015625) * corners;
+                if (out && colX && Y0 + j <= nc - 2) fc[((size_t)K * nc + (Y0 + j)) * nc + X] = (ST)v;
+                cb[j] = ca;
+                xb[j] = xa;
+                yb[j] = ya;
+                xyb[j] = xya;
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < CY; ++j) {
+                cc[j] = R[2 * j + 1];
+                fcs[j] = x[2 * j + 1] + (R[2 * j] + R[2 * j + 2]);
+                xyc[j] = x[2 * j] + x[2 * j + 2];
+            }
+        }
+    }
+    __device__ __forceinline__ void run() {
+        int rp = 2 * Z0 - 1;
+        const int end = 2 * Z1 - 1;
+        load_u(rp - 1, U[0]);
+        load_u(rp, U[1]);
+        load_u(rp + 1, U[2]);
+        load_f(rp, F[0]);
+        if constexpr (VAR) {
+            load_k(0, rp, 1, kx[0]);
+            load_k(1, rp, 0, ky[0]);
+            load_k(2, rp - 1, 1, kz[0]);
+            load_k(2, rp, 1, kz[1]);
+        }
+#pragma unroll
+        for (int j = 0; j < CY; ++j) cb[j] = xb[j] = yb[j] = xyb[j] = cc[j] = fcs[j] = xyc[j] = T(0);
+        for (;;) {
+            step<0>(rp);
+            if (++rp > end) break;
+            step<1>(rp);
+            ++rp;
+            step<2>(rp);
+            if (++rp > end) break;
+            step<3>(rp);
+            ++rp;
+        }
+    }
+};
+
+template <typename ST, int OP, int BY>
+__global__ __launch_bounds__(64) void k_restrict3d(const GridDesc* __restrict__ descs, int sel, int zchunk) {
+    const GridDesc& d = descs[blockIdx.y];
     if (d.done && *gp(d.done)) return;
-    constexpr int CX = (BX - 3) / 2, CY = (BY - 3) / 2, RPT = BY / 4;
-    const int nf = d.n, nc = (nf - 1) / 2 + 1;
-    const int ncx = (nc - 2 + CX - 1) / CX, ncy = (nc - 2 + CY - 1) / CY;
+    using S = Restrict3<ST, OP, BY>;
+    S t;
+    t.n = d.n;
+    t.nc = (t.n - 1) / 2 + 1;
+    const int ncx = (t.nc - 2 + S::CX - 1) / S::CX, ncy = (t.nc - 2 + S::CY - 1) / S::CY;
     const int tile = xcd_tile(blockIdx.x, gridDim.x);
     const int tx = tile % ncx, t2 = tile / ncx, ty = t2 % ncy, tz = t2 / ncy;
-    const int X0 = 1 + tx * CX, Y0 = 1 + ty * CY, Z0 = 1 + tz * zchunk, Z1 = min(Z0 + zchunk, nc - 1);
-    const int fx0 = 2 * X0 - 2, fy0 = 2 * Y0 - 2;
-    const MG_GLOBAL ST* __restrict__ u = gp((const ST*)(sel ? d.t : d.u));
-    const MG_GLOBAL ST* __restrict__ f = gp((const ST*)d.f);
-    const MG_GLOBAL T* __restrict__ kf = gp((const T*)d.k);
-    MG_GLOBAL ST* __restrict__ fc = gp((ST*)d.fc);
-    const T c = (T)d.c;
-    T sc[7];
-    load_stencil<OP>(d, sc);
-    __shared__ T U[3][BY][BX];
-    __shared__ T Rr[3][BY][BX];
-    __shared__ T K[VAR ? 3 : 1][BY][BX];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int gx = fx0 + lane;
-    const bool lres = lane >= 1 && lane <= 2 * CX + 1;
-    const bool colg = gx < nf && lane <= 2 * CX + 2, coli = gx >= 1 && gx <= nf - 2;
-    const size_t pl = (size_t)nf * nf;
-    const int mstart = 2 * Z0 - 2, mend = 2 * Z1;
-    T un[RPT], kn[RPT];
-    T fr[2][RPT];
-    // unconditional loads from clamped addresses, values selected afterwards
-    auto issue_u = [&](int z) {
-        const int zc = min(z, nf - 1), xc = min(gx, nf - 1);
+    const int lane = threadIdx.x, X0 = 1 + tx * S::CX;
+    t.X = X0 + (lane - 2) / 2;
+    t.colX = (lane & 1) == 0 && lane >= 2 && lane < 2 + 2 * S::CX && t.X <= t.nc - 2;
+    t.Y0 = 1 + ty * S::CY;
+    t.Z0 = 1 + tz * zchunk;
+    t.Z1 = min(t.Z0 + zchunk, t.nc - 1);
+    t.u = gp((const ST*)(sel ? d.t : d.u));
+    t.f = gp((const ST*)d.f);
+    t.fx = gp((const typename S::T*)d.fx);
+    t.fc = gp((ST*)d.fc);
+    t.c = (typename S::T)d.c;
+    load_stencil<OP>(d, t.sc);
+    t.pl = (size_t)t.n * t.n;
+    const int xc = min(2 * X0 - 2 + lane, t.n - 1);
 #pragma unroll
-        for (int m = 0; m < RPT; ++m) {
-            const int ly = w + 4 * m, gy = fy0 + ly;
-            const bool ing = colg && gy < nf && ly <= 2 * CY + 2 && z < nf;
-            const size_t p = (size_t)zc * pl + (size_t)min(gy, nf - 1) * nf + xc;
-            const T v = u[p];
-            un[m] = ing ? v : T(0);
-            if constexpr (VAR) {
-                const T kv = kf[p];
-                kn[m] = ing ? kv : T(1);
-            }
-        }
-    };
-    auto issue_f = [&](int z, T (&dst)[RPT]) {
-        const bool zin = z >= 1 && z <= nf - 2;
-        const int zc = min(z, nf - 1), xc = min(gx, nf - 1);
-#pragma unroll
-        for (int m = 0; m < RPT; ++m) {
-            const int ly = w + 4 * m, gy = fy0 + ly;
-            const bool inn = zin && coli && gy >= 1 && gy <= nf - 2 && lres && ly >= 1 && ly <= 2 * CY + 1;
-            const T v = f[(size_t)zc * pl + (size_t)min(gy, nf - 1) * nf + xc];
-            dst[m] = inn ? v : T(0);
-        }
-    };
-    auto step = [&](int mm, T (&fcur)[RPT], T (&fprev)[RPT]) {
-        const int s0 = (mm - mstart) % 3, s1 = (mm - 1 - mstart + 3) % 3, s2 = (mm - 2 - mstart + 6) % 3;
-#pragma unroll
-        for (int m = 0; m < RPT; ++m) {
-            U[s0][w + 4 * m][lane] = un[m];
-            if constexpr (VAR) K[s0][w + 4 * m][lane] = kn[m];
-        }
-        issue_f(mm, fcur);
-        if (mm + 1 <= mend) issue_u(mm + 1);
-        __syncthreads();
-        const int rp = mm - 1;  // residual plane
-        if (rp >= mstart + 1) {
-            const bool zin = rp >= 1 && rp <= nf - 2;
-#pragma unroll
-            for (int m = 0; m < RPT; ++m) {
-                const int ly = w + 4 * m, gy = fy0 + ly;
-                if (lres && ly >= 1 && ly <= 2 * CY + 1) {
-                    const bool inn = zin && coli && gy >= 1 && gy <= nf - 2;
-                    T ds;
-                    Rr[s1][ly][lane] =
-                        inn ? lds_res3<T, OP>(U[s2], U[s1], U[s0], K[s2], K[s1], K[s0], ly, lane, fprev[m], c, ds,
-                                              sc)
-                            : T(0);
-                }
-            }
-        }
-        __syncthreads();
-        if (((rp & 1) == 1) && rp >= 2 * Z0 + 1) {  // rp = 2K+1: planes 2K-1..2K+1 ready
-            const int Kz = (rp - 1) / 2;
-            const int sb = (rp - 2 - mstart + 6) % 3, sc = (rp - 1 - mstart + 3) % 3;  // planes 2K-1, 2K
-            for (int t = threadIdx.x; t < CX * CY; t += NT) {
-                const int X = X0 + t % CX, Y = Y0 + t / CX;
-                if (X <= nc - 2 && Y <= nc - 2)
-                    fc[((size_t)Kz * nc + Y) * nc + X] = (ST)fw3<T>(Rr[sb], Rr[sc], Rr[s1], 2 * (Y - Y0) + 2,
-                                                                   2 * (X - X0) + 2);
-            }
-        }
-    };
-    int mm = mstart;
-    issue_u(mm);
-    for (; mm + 1 <= mend; mm += 2) {
-        step(mm, fr[0], fr[1]);
-        step(mm + 1, fr[1], fr[0]);
-    }
-    if (mm <= mend) step(mm, fr[0], fr[1]);
+    for (int i = 0; i < S::UR; ++i)
+        t.rb[i] = (unsigned)(min(2 * t.Y0 - 2 + i, t.n - 1) * t.n + xc) * (unsigned)sizeof(ST);
+    t.run();
 }
 
 // ---------------------------------------------------------------------------
@@ -479,11 +537,10 @@ hipError_t launch_smooth_restrict3d(const GridDesc* d, int ninst, int nf, int se
     }
 }
 
-int restrict_tiles(int dim, int nf, TileCfg cfg) {
+static int restrict_tiles(int nf, TileCfg cfg) {  // 2D
     const int CX = (BX - 3) / 2, CY = (cfg.by - 3) / 2;
     const int mc = (nf - 1) / 2 + 1 - 2;
-    if (dim == 2) return cdiv(mc, CX) * cdiv(mc, CY);
-    return cdiv(mc, CX) * cdiv(mc, CY) * nzchunks(mc, cfg.zchunk);
+    return cdiv(mc, CX) * cdiv(mc, CY);
 }
 
 int norm_tiles(int dim, int n, TileCfg cfg) {
@@ -496,14 +553,28 @@ int norm_tiles(int dim, int n, TileCfg cfg) {
 }
 
 namespace {
-template <typename T, int OPV>
-hipError_t launch_restrict_op(int dim, const GridDesc* d, int sel, TileCfg cfg, dim3 grid, hipStream_t s) {
-    if (dim == 2) {
-        MG_BY_SWITCH(cfg.by, (k_restrict2d<T, OPV, BY><<<grid, NT, 0, s>>>(d, sel)))
-    } else {
-        MG_BY_SWITCH(cfg.by, (k_restrict3d<T, OPV, BY><<<grid, NT, 0, s>>>(d, sel, cfg.zchunk)))
-    }
+template <typename T, int OPV, int BY>
+hipError_t launch_restrict3d_by(const GridDesc* d, int ninst, int nf, int sel, TileCfg cfg, hipStream_t s) {
+    using S = Restrict3<T, OPV, BY>;
+    const int mc = (nf - 1) / 2 - 1;
+    const dim3 grid(cdiv(mc, S::CX) * cdiv(mc, S::CY) * nzchunks(mc, cfg.zchunk), ninst);
+    k_restrict3d<T, OPV, BY><<<grid, 64, 0, s>>>(d, sel, cfg.zchunk);
     return hipGetLastError();
+}
+template <typename T, int OPV>
+hipError_t launch_restrict_op(int dim, const GridDesc* d, int ninst, int nf, int sel, TileCfg cfg, hipStream_t s) {
+    if (dim == 2) {
+        const dim3 grid(restrict_tiles(nf, cfg), ninst);
+        MG_BY_SWITCH(cfg.by, (k_restrict2d<T, OPV, BY><<<grid, NT, 0, s>>>(d, sel)))
+        return hipGetLastError();
+    }
+    switch (cfg.by) {
+        case 8: return launch_restrict3d_by<T, OPV, 8>(d, ninst, nf, sel, cfg, s);
+        case 16: return launch_restrict3d_by<T, OPV, 16>(d, ninst, nf, sel, cfg, s);
+        case 32:  // taller columns of 32-bit constant operators only
+            return launch_restrict3d_by<T, OPV, (sizeof(T) <= 4 && OPV != OP_VAR) ? 32 : 16>(d, ninst, nf, sel, cfg, s);
+        default: return hipErrorInvalidValue;
+    }
 }
 template <typename T, int OPV>
 hipError_t launch_coarsest_op(int dim, const GridDesc* d, int ninst, hipStream_t s) {
@@ -519,13 +590,12 @@ hipError_t launch_restrict(int dim, int op, const GridDesc* d, int ninst, int nf
                            hipStream_t s) {
     if (op == OP_CC) return cc_launch_restrict(dim, d, ninst, nf, sel, s);
     if (nf < 5 || ninst <= 0) return hipErrorInvalidValue;
-    const dim3 grid(restrict_tiles(dim, nf, cfg), ninst);
-    if (op == OP_LAP) return launch_restrict_op<T, OP_LAP>(dim, d, sel, cfg, grid, s);
+    if (op == OP_LAP) return launch_restrict_op<T, OP_LAP>(dim, d, ninst, nf, sel, cfg, s);
     if constexpr (sizeof(T) >= 4) {
-        if (op == OP_VAR) return launch_restrict_op<T, OP_VAR>(dim, d, sel, cfg, grid, s);
+        if (op == OP_VAR) return launch_restrict_op<T, OP_VAR>(dim, d, ninst, nf, sel, cfg, s);
     }
     if constexpr (sizeof(T) == 8) {
-        if (op == OP_STENCIL) return launch_restrict_op<T, OP_STENCIL>(dim, d, sel, cfg, grid, s);
+        if (op == OP_STENCIL) return launch_restrict_op<T, OP_STENCIL>(dim, d, ninst, nf, sel, cfg, s);
     }
     return hipErrorInvalidValue;
 }
