@@ -269,6 +269,7 @@ struct Engine {
             // each wavefront marching 32 rows (longer chunks leave the smaller
             // grids of a batch too few workgroups)
             if (dim == 2) tiles[(size_t)a].norm = TileCfg{16, 32, 2, 4, 0, 2};
+            else tiles[(size_t)a].norm = ir3d_tiles((1 << a) + 1, false);
         }
         for (int a = 2; a <= max_a; ++a)
             pstride = std::max(pstride, norm_tiles(dim, (1 << a) + 1, tiles[(size_t)a].norm));

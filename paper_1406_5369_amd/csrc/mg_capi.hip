@@ -362,13 +362,20 @@ void prof_end(mg_ctx* c, int step, int kind, hipStream_t s) {
     c->prof_kind.push_back(kind);
 }
 
+// Geometry of the norm pass: that of the refinement pass, which alone has the
+// one-wavefront columns.
+TileCfg norm_cfg(const mg_ctx* c) {
+    return c->top.norm.wv == 1 ? lds_tiles(c->p.dim, c->p.n, c->prob.smoother).norm : c->top.norm;
+}
+
 hipError_t enqueue_norm(mg_ctx* c, hipStream_t s, int step = 0, const StopTest* stop = nullptr) {
     if (c->cc) return cc_norm(c->p.dim, c->d_top, c->p.n, c->d_partial, c->d_norm, s, stop);
     if (c->st) return st_norm(c->p.dim, c->d_top, c->p.n, c->d_partial, c->d_norm, s, stop);
     const bool var = c->prob.var;
-    const int nparts = norm_tiles(c->p.dim, c->p.n, c->top.norm);
+    const TileCfg cfg = norm_cfg(c);
+    const int nparts = norm_tiles(c->p.dim, c->p.n, cfg);
     const bool timed = prof_begin(c, step, s);
-    hipError_t e = launch_norm(c->p.dim, var, c->d_top, 1, c->p.n, 0, c->d_partial, c->pstride, c->top.norm, s);
+    hipError_t e = launch_norm(c->p.dim, var, c->d_top, 1, c->p.n, 0, c->d_partial, c->pstride, cfg, s);
     if (timed) prof_end(c, step, 1, s);
     if (e != hipSuccess) return e;
     return launch_norm_finalize(c->d_partial, c->pstride, nparts, 0, 1, c->d_norm, s, stop);
@@ -1121,6 +1128,9 @@ hipError_t autotune(mg_ctx* c) {
             std::vector<TileCfg> cands;
             for (TileCfg t : tune_candidates(dim, n - 2, true, 2, 8, var))
                 if (mode != 2 || t.xp == 2) cands.push_back(t);  // the binary16 pass has two nodes per lane
+            if (mode == 1 && dim == 3)
+                for (int by : {6, 8})
+                    for (int zc = 8; zc <= 128 && zc <= n; zc *= 2) cands.push_back({by, zc, 1, 1});
             const double* scl = nullptr;
             int maxparts = 1;
             for (TileCfg t : cands) maxparts = std::max(maxparts, norm_tiles(dim, n, t));
@@ -1239,6 +1249,8 @@ int mg_setup(const mg_params* p, void* stream, mg_ctx** out) {
         c->top.norm.xp = 2;
         if (dim == 2) c->top.norm.zchunk = 32;
         else c->top.norm.by = std::min(c->top.norm.by, 4 * c->top.norm.wv);
+    } else if (c->p.precision != MG_PREC_FP64 && dim == 3) {
+        c->top.norm = ir3d_tiles(p->n, c->prob.var);
     }
     const char* at = std::getenv("MG_AUTOTUNE");
     // a constant stencil keeps the heuristic geometry: tuning its levels takes 40 .. 1000 ms at setup (against
@@ -1343,7 +1355,7 @@ int mg_setup(const mg_params* p, void* stream, mg_ctx** out) {
         c->nrm_fused = false;
     c->pstride = c->st   ? st_norm_parts(dim, p->n)
                  : c->cc ? cc_norm_parts(dim, p->n)
-                         : std::max(1, norm_tiles(dim, p->n, c->top.norm));
+                         : std::max({1, norm_tiles(dim, p->n, c->top.norm), norm_tiles(dim, p->n, norm_cfg(c))});
     SETUP_CK(hipMalloc((void**)&c->d_partial, sizeof(double) * (size_t)c->pstride));
     if (is_h16(c->p)) {
         SETUP_CK(hipMalloc((void**)&c->d_pmax, sizeof(double) * (size_t)c->pstride));

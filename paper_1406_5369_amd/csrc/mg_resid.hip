@@ -1,4 +1,6 @@
 // FP64 residual norms, the FP64 refinement pass, device-side solve control and setup kernels.
+#include <type_traits>
+
 #include "mg_kern.h"
 
 namespace mg {
@@ -890,6 +892,145 @@ __global__ __launch_bounds__(64 * WV) void k_ir3d(const IRDesc* __restrict__ des
     resid3d_body<VAR, BY, PD, true, WV>(nullptr, d, sel, FL, part, pstride, zchunk);
 }
 
+// The refinement pass with one wavefront per column: lane = x, the thread holds
+// its BY rows (BY - 2 of them owned) of three planes of the updated iterate and
+// marches along z; neighbours along x come from the adjacent lanes.  No LDS, no
+// barrier.  With coefficients it forms each face once where it is used by both
+// of its rows or planes (3 1/4 divisions per node instead of six).
+// What bounds it is memory (32 bytes a node, 40 with coefficients): 257^3 with
+// coefficients 163 us against 181 for the LDS tile (680 MB: 110 us at 6.2 TB/s);
+// seven grids of 129^3 100 / 127 us.  At 513^3 the tiles of two nodes per lane,
+// whose accesses are 16 bytes wide, stay ahead.
+template <bool VAR, int BY, int FL>
+__global__ __launch_bounds__(64) void k_ir3d_c(const IRDesc* __restrict__ descs, int sel, double* __restrict__ part,
+                                               int pstride, int zchunk) {
+    constexpr bool UPD = (FL & IR_NO_UPDATE) == 0;
+    constexpr int RR = BY - 2, TX = BX - 2;
+    const IRDesc& d = descs[blockIdx.y];
+    if (d.done && *gp(d.done)) return;
+    if (d.par) sel = *gp(d.par);
+    const int n = d.n;
+    const int ntx = (n - 2 + TX - 1) / TX, nty = (n - 2 + RR - 1) / RR;
+    const int tile = xcd_tile(blockIdx.x, gridDim.x);
+    const int tx = tile % ntx, t2 = tile / ntx, ty = t2 % nty, tz = t2 / nty;
+    const int lane = threadIdx.x, gx = tx * TX + lane, gy0 = ty * RR;  // of row 0
+    const int z0 = 1 + tz * zchunk, z1 = min(z0 + zchunk, n - 1);
+    const MG_GLOBAL double* __restrict__ uin = gp((const double*)(sel ? d.u[1] : d.u[0]));
+    MG_GLOBAL double* __restrict__ uout = gp(sel ? d.u[0] : d.u[1]);
+    const MG_GLOBAL float* __restrict__ e = gp((const float*)d.e);
+    const MG_GLOBAL double* __restrict__ f = gp(d.f);
+    const MG_GLOBAL double* __restrict__ kf = gp(d.k);
+    MG_GLOBAL float* __restrict__ r32 = gp((float*)d.r);
+    const double c = d.c;
+    const size_t pl = (size_t)n * n;
+    const bool coli = gx >= 1 && gx <= n - 2, own = coli && lane >= 1 && lane <= BX - 2;
+    unsigned rb[BY];  // byte offset of each row's float (clamped)
+#pragma unroll
+    for (int i = 0; i < BY; ++i) rb[i] = (unsigned)(min(gy0 + i, n - 1) * n + min(gx, n - 1)) * 4u;
+
+    double U[3][BY], un[BY], F[2][RR];  // slot = plane mod 3; u of the plane in flight; f by plane
+    float en[BY];
+    double K[VAR ? 3 : 1][BY], kzl[VAR ? RR : 1];
+    auto issue = [&](int z) {
+        const size_t o = (size_t)min(z, n - 1) * pl;
+        const PlaneBuf<double> bu(uin + o, pl);
+        const PlaneBuf<float> be(e + o, pl);
+#pragma unroll
+        for (int i = 0; i < BY; ++i) {
+            un[i] = bu.load(2u * rb[i]);
+            if constexpr (UPD) en[i] = be.load(rb[i]);
+        }
+    };
+    auto take = [&](int z, double (&dst)[BY]) {
+        const bool zin = z >= 1 && z <= n - 2;
+#pragma unroll
+        for (int i = 0; i < BY; ++i) {
+            double v = un[i];
+            if constexpr (UPD)
+                v = pick(coli && zin && gy0 + i >= 1 && gy0 + i <= n - 2, un[i] + (double)en[i], un[i]);
+            dst[i] = v;
+        }
+    };
+    auto issue_f = [&](int z, double (&dst)[RR]) {
+        const PlaneBuf<double> b(f + (size_t)min(z, n - 1) * pl, pl);
+#pragma unroll
+        for (int i = 0; i < RR; ++i) dst[i] = b.load(2u * rb[i + 1]);
+    };
+    auto issue_k = [&](int z, double (&dst)[BY]) {
+        const PlaneBuf<double> b(kf + (size_t)min(z, n - 1) * pl, pl);
+#pragma unroll
+        for (int i = 0; i < BY; ++i) dst[i] = b.load(2u * rb[i]);
+    };
+    double acc = 0.0;
+    auto step = [&](int z, auto qc) {
+        constexpr int Q = decltype(qc)::value, Sb = Q % 3, Sc = (Q + 1) % 3, Sa = (Q + 2) % 3, H = Q & 1;
+        issue_f(z + 1, F[H ^ 1]);
+        if constexpr (VAR) issue_k(z + 2, K[Sb]);  // the plane below is used no more (its faces are in kzl)
+        const size_t o = (size_t)z * pl;
+        const PlaneBuf<double> bo(uout + o, pl);
+        const PlaneBuf<float> br(r32 + o, pl);
+        double kyl = 0.0;
+        if constexpr (VAR) kyl = kface(K[Sc][0], K[Sc][1]);
+#pragma unroll
+        for (int i = 0; i < RR; ++i) {
+            const double uC = U[Sc][i + 1], uw = lane_prev(uC), ue = lane_next(uC);
+            double r;
+            if constexpr (VAR) {
+                const double kx = kface(K[Sc][i + 1], lane_next(K[Sc][i + 1])), kyh = kface(K[Sc][i + 1], K[Sc][i + 2]);
+                const double kzh = kface(K[Sc][i + 1], K[Sa][i + 1]);
+                double ds;
+                r = res_var3f(uC, uw, ue, U[Sc][i], U[Sc][i + 2], U[Sb][i + 1], U[Sa][i + 1], lane_prev(kx), kx, kyl,
+                              kyh, kzl[i], kzh, F[H][i], c, ds);
+                kyl = kyh;
+                kzl[i] = kzh;
+            } else {
+                r = res_lap3(uC, uw, ue, U[Sc][i], U[Sc][i + 2], U[Sb][i + 1], U[Sa][i + 1], F[H][i], c);
+            }
+            const bool in = own && gy0 + 1 + i <= n - 2;
+            acc += pick(in, r * r, 0.0);
+            if (in) {
+                if constexpr (UPD) bo.store(2u * rb[i + 1], uC);
+                br.store(rb[i + 1], (float)r);
+            }
+        }
+        take(z + 2, U[Sb]);
+        issue(z + 3);
+    };
+    issue_f(z0, F[0]);
+    if constexpr (VAR) {
+        issue_k(z0 - 1, K[0]);
+        issue_k(z0, K[1]);
+        issue_k(z0 + 1, K[2]);
+#pragma unroll
+        for (int i = 0; i < RR; ++i) kzl[i] = kface(K[0][i + 1], K[1][i + 1]);
+    }
+    issue(z0 - 1);
+    take(z0 - 1, U[0]);
+    issue(z0);
+    take(z0, U[1]);
+    issue(z0 + 1);
+    take(z0 + 1, U[2]);
+    issue(z0 + 2);
+    for (int z = z0;;) {
+        step(z, std::integral_constant<int, 0>{});
+        if (++z >= z1) break;
+        step(z, std::integral_constant<int, 1>{});
+        if (++z >= z1) break;
+        step(z, std::integral_constant<int, 2>{});
+        if (++z >= z1) break;
+        step(z, std::integral_constant<int, 3>{});
+        if (++z >= z1) break;
+        step(z, std::integral_constant<int, 4>{});
+        if (++z >= z1) break;
+        step(z, std::integral_constant<int, 5>{});
+        if (++z >= z1) break;
+    }
+    // per-workgroup partial in a fixed order (finalised in block order)
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 64);
+    if (lane == 0) part[(size_t)d.inst * pstride + blockIdx.x] = acc;
+}
+
 // Sum of np partials by one workgroup in a fixed order: thread t takes
 // elements t, t + NT, t + 2 NT, ... into eight interleaved accumulators (eight
 // loads in flight per thread), combined pairwise, then the fixed-order
@@ -1198,6 +1339,13 @@ hipError_t launch_ir_fl(int dim, const IRDesc* d, int sel, double* partial, int 
     if (dim == 2) {
         MG_BY_SWITCH(cfg.by, (k_ir2d<VARV, BY, FL><<<grid, NT, 0, s>>>(d, sel, partial, pstride)))
         return hipSuccess;
+    }
+    if (cfg.wv == 1) {  // one wavefront per column
+        switch (cfg.by) {
+            case 6: k_ir3d_c<VARV, 6, FL><<<grid, 64, 0, s>>>(d, sel, partial, pstride, cfg.zchunk); return hipSuccess;
+            case 8: k_ir3d_c<VARV, 8, FL><<<grid, 64, 0, s>>>(d, sel, partial, pstride, cfg.zchunk); return hipSuccess;
+            default: return hipErrorInvalidValue;
+        }
     }
     const bool p2 = cfg.pd == 2;
     switch (cfg.by) {

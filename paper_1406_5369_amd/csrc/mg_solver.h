@@ -58,6 +58,8 @@ struct Tiles {
 Tiles default_tiles(int dim, int elem_bytes, int n, int smoother, int op);
 // The same with LDS tiles only (no one-wavefront sweeps).
 Tiles lds_tiles(int dim, int n, int smoother);
+// Heuristic geometry of the 3D refinement pass (FP32 corrections).
+TileCfg ir3d_tiles(int n, bool var);
 // Autotune the FP32 sweeps and restriction of one absolute level of a batch:
 // 'count' instances of edge n, descriptors d (device).  Cached per process.
 hipError_t tune_group(const Problem& P, const GridDesc* d, int count, int n, Tiles& t, hipStream_t s);

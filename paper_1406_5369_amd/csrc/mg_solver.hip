@@ -89,6 +89,14 @@ Tiles default_tiles(int dim, int elem_bytes, int n, int smoother, int op) {
     return t;
 }
 
+// One wavefront per column, six owned rows (four with coefficients); chunks as
+// short as leave enough wavefronts.  Seven grids of 129^3: 100 us (105 with 32
+// planes a chunk, LDS tiles 127); six of 65^3: 20 us (25); seven of 33^3: 7.7 us
+// (8.1); 257^3 with coefficients 163 us (181).
+TileCfg ir3d_tiles(int n, bool var) {
+    return {var ? 6 : 8, std::max(2, std::min(32, n / 16)), 1, 1};
+}
+
 template <typename T>
 hipError_t launch_smooth(int dim, int sm, int op, const GridDesc* d, int ninst, int n, int sel, int flags,
                          TileCfg cfg, hipStream_t s) {
