@@ -102,8 +102,12 @@ def sweep_blocks(dim: int, n: int, by: int, zchunk: int) -> int:
 
 def short_name(name: str) -> str:
     name = name.strip().replace("(anonymous namespace)::", "")
-    name = re.sub(r"\([^()]*\)$", "", name)
-    return name.replace("void ", "")
+    name = re.sub(r"\([^()]*\)$", "", name).replace("void ", "")
+    # sweeps by operator (0 Laplacian, 1 nodal coefficients) are listed as without / with
+    # coefficients, and the one-wavefront red-black form, which has no prefetch depths, as depth 1
+    name = re.sub(r"(k_smooth(?:2d|3d|3d_rc)<\w+, \d, )([01])(?=,)",
+                  lambda m: m[1] + ("true" if m[2] == "1" else "false"), name)
+    return re.sub(r"k_smooth3d_rb<(\w+), 0, (\d+), (\d)>", r"k_smooth3d_rc<\1, 0, false, \2, 1, \3>", name)
 
 
 def load(path: str, from_kernel: str | None = None):
