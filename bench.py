@@ -692,8 +692,8 @@ def main(argv=None) -> int:
         # pre-smoothing sweep (reads u and f, writes the other buffer): the
         # event brackets time that sweep
         pass_roof = roof(sweep_kernel(dim, word, nby, npd, var, nwv, flags=4), sweep_blocks(dim, n, nby, nzc),
-                         "finest-level FP64 first pre-smoothing sweep that also sums the residual norm of its "
-                         "incoming iterate", pass_launches, pass_ms, (4 if var else 3) * word * dof,
+                         "finest-level FP64 first pre-smoothing launch (a sweep, on large 3D grids two) that also "
+                         "sums the residual norm of its incoming iterate", pass_launches, pass_ms, (4 if var else 3) * word * dof,
                          traffic_record(args.workload, (nby, nzc, npd, nwv, "n")))
     else:
         pass_roof = roof(pass_kernel(dim, pby, ppd, var, ir, pwv, ppr, word=word),
@@ -709,8 +709,8 @@ def main(argv=None) -> int:
     else:
         roofline, other = sweep_roof, pass_roof
     if not other["launches"]:
-        # no launch of that kernel in the timed solves (2D levels run their
-        # sweeps as the fused pairs): nothing to report
+        # no launch of that kernel in the timed solves (2D levels and large 3D
+        # ones run their sweeps in fused launches): nothing to report
         other = None
     log(f"[bench] finest sweep {sweep_roof['avg_launch_ms'] * 1e3:.1f} us x {launches}: "
         f"{sweep_roof['achieved']:.0f} GB/s; refinement/norm pass {pass_roof['avg_launch_ms'] * 1e3:.1f} us x "

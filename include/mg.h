@@ -472,8 +472,8 @@ int mg_server_info(mg_ctx* ctx, size_t* used_bytes, int* active, int* queued);
  * kernel 0, the finest-level smoothing sweeps that read the previous iterate
  * (not the zero-iterate or fused-correction variants); kernel 1, the
  * finest-level FP64 refinement pass (mixed precision) or norm pass (FP64).
- * The finest level's sweeps then run one to a launch where a solve otherwise
- * fuses two of them or a leg (the fused pair from a zero iterate excepted).
+ * Sweeps that share a launch with another one or with the restriction are not
+ * counted (kernel 1 is then the launch that sums the norm).
  * Launches of steps past the solve's last step (queued before the stop test
  * was read; they find the stop flag set and do no work) are not counted.
  * mg_prof_read_kernel returns the number of counted launches of one kernel

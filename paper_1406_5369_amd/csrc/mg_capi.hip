@@ -398,11 +398,11 @@ hipError_t enqueue_nrm_sweep(mg_ctx* c, hipStream_t s, int step = 0, const StopT
     const Problem& P = c->prob;
     const Tiles& t = c->tl64[0];
     const GridDesc* d = c->G64[0].d;
-    const int n = c->p.n, op = P.op(), k = first_sweeps(P, t, n, c->prof_on);
+    const int n = c->p.n, op = P.op(), k = first_sweeps(P, t, n);
     const bool timed = prof_begin(c, step, s);
     int nparts;
     hipError_t e;
-    if (!c->prof_on && leg_ok(P, n) && k == P.nu1) {
+    if (leg_ok(P, n) && k == P.nu1) {
         nparts = down2d_tiles(op, n);
         e = launch_down2d<double>(op, d, 1, n, 0, k, SWEEP_NORM, s);
     } else if (k == 2) {

@@ -106,7 +106,7 @@ bool pair_ok(const Problem& P, const Tiles& t, int flags, int n, int ninst);
 constexpr size_t kPairBoxes = 200;  // fewest boxes of such a launch
 // Pre-smoothing sweeps in the launch that starts level 0's descending leg with
 // SWEEP_NORM; with a leg its restriction, too.
-int first_sweeps(const Problem& P, const Tiles& t, int n, bool measured);
+int first_sweeps(const Problem& P, const Tiles& t, int n);
 
 // Coarse levels of a V-cycle run by the single-workgroup tail kernel:
 // groups[first..L-1], one TailDesc per instance (first = -1: no tail).
@@ -125,7 +125,6 @@ int tail_first_level(int dim, int elem, int op, const std::vector<int>& n, bool 
 // zero_top: the iterate at level 0 is known to be zero.  Works in precision T.
 // first_done: level 0's first launch (first_sweeps) has already run; its result
 // is in the ping-pong partner t and the cycle continues from there.
-// With prof_ev (measurement) level 0 runs its sweeps apart.
 template <typename T>
 hipError_t vcycle(const Problem& P, const std::vector<Group>& groups, bool zero_top, const std::vector<Tiles>& tiles,
                   hipStream_t s, hipEvent_t* prof_ev, int* prof_n, int prof_cap, const TailPlan* tail = nullptr,

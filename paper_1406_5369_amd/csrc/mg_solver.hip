@@ -207,8 +207,8 @@ bool pair_ok(const Problem& P, const Tiles& t, int flags, int n, int ninst) {
            (size_t)smooth3d_x2_tiles(P.op(), n, c) * (size_t)ninst >= kPairBoxes;
 }
 
-int first_sweeps(const Problem& P, const Tiles& t, int n, bool measured) {
-    if (measured || P.nu1 < 2) return 1;
+int first_sweeps(const Problem& P, const Tiles& t, int n) {
+    if (P.nu1 < 2) return 1;
     if (leg_ok(P, n)) return P.nu1 == 2 ? 2 : 1;
     return pair_ok(P, t, SWEEP_NORM, n, 1) ? 2 : 1;
 }
@@ -218,36 +218,35 @@ inline int post_sel(const Problem& P, int cur) { return cur | (P.sym ? SEL_BLACK
 
 // Launches of a level's ascending leg that change the iterate's buffer.
 template <typename T>
-int up_launches(const Problem& P, const Tiles& t, int n, int ninst, bool apart) {
+int up_launches(const Problem& P, const Tiles& t, int n, int ninst) {
     if (P.nu2 == 0) return 0;
     int i = 0, k = 0;
-    if ((!apart && leg_ok(P, n)) || post2_ok<T>(P, P.dim, t)) {
+    if (leg_ok(P, n) || post2_ok<T>(P, P.dim, t)) {
         i = P.nu2 >= 2 ? 2 : 1;
         k = 1;
     }
-    for (; i < P.nu2; ++k) i += !apart && i + 1 < P.nu2 && pair_ok(P, t, i == 0 ? SWEEP_PROLONG : 0, n, ninst) ? 2 : 1;
+    for (; i < P.nu2; ++k) i += i + 1 < P.nu2 && pair_ok(P, t, i == 0 ? SWEEP_PROLONG : 0, n, ninst) ? 2 : 1;
     return k;
 }
 
 // The descending leg of a level: nu1 sweeps, the residual and its restriction,
 // as few launches as the level's rules give.  top: level 0, whose plain sweeps
-// are measured (and then run apart); first_done as in vcycle.  'cur' is the
-// buffer of the iterate (0 u, 1 t).
+// are measured; first_done as in vcycle.  'cur' is the buffer of the iterate (0
+// u, 1 t).
 template <typename T>
 hipError_t descend(const Problem& P, const Group& g, const Tiles& t, bool top, bool zero, bool first_done, int& cur,
                    hipStream_t s, Prof& prof) {
-    const bool apart = top && prof.ev;
     cur = first_done ? 1 : 0;
-    int i = first_done ? first_sweeps(P, t, g.n, apart) : 0;
-    const bool leg = !apart && leg_ok(P, g.n);
+    int i = first_done ? first_sweeps(P, t, g.n) : 0;
+    const bool leg = leg_ok(P, g.n);
     const int ns = P.nu1 >= 2 ? 2 : 1;
     if (leg && first_done && i == P.nu1) return hipSuccess;
     const int last = leg ? P.nu1 - ns : P.nu1;  // the leg's launch takes the others
     if (!leg && i == 0 && smooth2_ok<T>(P, P.dim, t, zero)) {
         // sweeps 1 and 2 from the zero iterate, into the buffer that an even
         // number of launches brings to u
-        int k = up_launches<T>(P, t, g.n, g.ninst, apart);
-        for (int j = 2; j < P.nu1; j += !apart && pair_ok(P, t, 0, g.n, g.ninst) && j + 1 < P.nu1 ? 2 : 1) ++k;
+        int k = up_launches<T>(P, t, g.n, g.ninst);
+        for (int j = 2; j < P.nu1; j += pair_ok(P, t, 0, g.n, g.ninst) && j + 1 < P.nu1 ? 2 : 1) ++k;
         cur = k & 1;
         MG_TRY(launch_smooth2<T>(P.dim, g, t, cur ^ 1, s));
         i = 2;
@@ -255,7 +254,7 @@ hipError_t descend(const Problem& P, const Group& g, const Tiles& t, bool top, b
     bool fused = false;
     while (i < last) {
         const int flags = (i == 0 && zero) ? SWEEP_ZERO_GUESS : 0;
-        if (!apart && i + 1 < last && pair_ok(P, t, flags, g.n, g.ninst)) {
+        if (i + 1 < last && pair_ok(P, t, flags, g.n, g.ninst)) {
             MG_TRY(launch_smooth3d_x2<T>(P.op(), g.d, g.ninst, g.n, cur, flags, t.pair_of(flags), s));
             i += 2;
         } else if (!leg && i == P.nu1 - 1 && flags == 0 && fused_restrict_ok<T>(P, P.dim, t)) {
@@ -286,11 +285,10 @@ hipError_t descend(const Problem& P, const Group& g, const Tiles& t, bool top, b
 // ends in u.
 template <typename T>
 hipError_t ascend(const Problem& P, const Group& g, const Tiles& t, bool top, int cur, hipStream_t s, Prof& prof) {
-    const bool apart = top && prof.ev;
     int i = 0;
     if (P.nu2 == 0) {
         MG_TRY(launch_prolong<T>(P.dim, P.op(), g.d, g.ninst, g.n, cur, s));
-    } else if (!apart && leg_ok(P, g.n)) {
+    } else if (leg_ok(P, g.n)) {
         i = P.nu2 >= 2 ? 2 : 1;
         MG_TRY(launch_up2d<T>(P.op(), g.d, g.ninst, g.n, post_sel(P, cur), i, s));
         cur ^= 1;
@@ -301,7 +299,7 @@ hipError_t ascend(const Problem& P, const Group& g, const Tiles& t, bool top, in
     }
     while (i < P.nu2) {
         const int flags = i == 0 ? SWEEP_PROLONG : 0;  // the first sweep adds P uc while loading
-        if (!apart && i + 1 < P.nu2 && pair_ok(P, t, flags, g.n, g.ninst)) {
+        if (i + 1 < P.nu2 && pair_ok(P, t, flags, g.n, g.ninst)) {
             MG_TRY(launch_smooth3d_x2<T>(P.op(), g.d, g.ninst, g.n, post_sel(P, cur), flags, t.pair_of(flags), s));
             i += 2;
         } else {

@@ -72,6 +72,8 @@ def pass_kernel(dim: int, by: int, pd: int, var: bool = False, ir: bool = True, 
         return f"mg::k_ir3d_p<{by}, {pd}, 0, {wv}, {e}>" if ir else f"mg::k_norm3d_p<{by}, {pd}, {wv}>"
     if pairs:
         return f"mg::k_ir2d_p<{pd}, 0, {e}>" if ir else f"mg::k_norm2d_p<{pd}>"
+    if ir and wv == 1:  # one wavefront per column
+        return f"mg::k_ir3d_c<{v}, {by}, 0>"
     if ir:
         return f"mg::k_ir2d<{v}, {by}, 0>" if dim == 2 else f"mg::k_ir3d<{v}, {by}, {pd}, 0, {wv}>"
     return f"mg::k_norm2d<{v}, {by}>" if dim == 2 else f"mg::k_norm3d<{v}, {by}, {pd}, {wv}>"
@@ -255,8 +257,8 @@ def traffic(fetch_db: str, write_db: str, bench_json: str) -> dict:
     ir = word == 4
     algo_pass = ((32 if ir else 16) + (8 if var else 0)) * (n - 2) ** dim
     pass_configs = {}
-    for by, wv in ((8, 4), (16, 4), (32, 4), (16, 8), (32, 8)):
-        if dim == 2 and wv != 4:
+    for by, wv in ((8, 4), (16, 4), (32, 4), (16, 8), (32, 8), (6, 1), (8, 1)):
+        if dim == 2 and wv != 4 or wv == 1 and not ir:
             continue
         for pd in pds:
             for zc in zcs:
