@@ -324,6 +324,13 @@ void destroy(mg_ctx* c) {
 // Point the level-0 descriptors at the caller's u and f (only when they change).
 int bind(mg_ctx* c, const void* u, const void* f) {
     if (!u || !f) return MG_EINVAL;
+    // Stencils and cells: by a kernel and on every call, so that mg_vcycle neither
+    // waits nor copies from the host (it may be captured) and a replayed capture,
+    // which binds its own arrays, leaves nothing behind for a later call.
+    if (c->st || c->cc) {
+        CK(launch_bind(c->d_top, c->G64[0].d, const_cast<void*>(u), f, c->stream));
+        return MG_OK;
+    }
     if (u == c->bound_u && f == c->bound_f) return MG_OK;
     c->h_top.u = const_cast<void*>(u);
     c->h_top.f = f;

@@ -1219,6 +1219,12 @@ __global__ void k_fill_int(int* __restrict__ p, int v, int count) {
     if (i < count) p[i] = v;
 }
 
+__global__ void k_bind(GridDesc* a, GridDesc* b, void* u, const void* f) {
+    GridDesc* d = threadIdx.x == 0 ? a : b;
+    d->u = u;
+    d->f = f;
+}
+
 }  // namespace
 
 template <bool VARV, int BY, int PD>
@@ -1491,8 +1497,9 @@ hipError_t launch_fill_int(int* p, int v, int count, hipStream_t s) {
     return hipGetLastError();
 }
 
-
-
-
+hipError_t launch_bind(GridDesc* a, GridDesc* b, void* u, const void* f, hipStream_t s) {
+    k_bind<<<1, 2, 0, s>>>(a, b, u, f);
+    return hipGetLastError();
+}
 
 }  // namespace mg
