@@ -350,7 +350,8 @@ int mg_level_cc_remove_mean(int dim, int n, double* v, double* mean_out, void* s
  * e and r are FP32 arrays; u_out's and r's boundaries are not written.  'by',
  * 'zchunk' pick the tile (0 = default); in 3D 'prefetch' is 1 or 2 planes
  * loaded ahead and 'waves' 4 or 8 wavefronts per workgroup (8 needs
- * by >= 16); 0 = default; 'pairs' != 0 (k NULL) runs the variant with two
+ * by >= 16) or 1: one wavefront per column of by 6 or 8 rows (prefetch 1, no
+ * pairs); 0 = default; 'pairs' != 0 (k NULL) runs the variant with two
  * adjacent nodes per lane (128 nodes per tile row; 3D: by <= 4 * waves, else
  * MG_EINVAL; 2D: each of four wavefronts marches 'zchunk' rows along y, 0 =
  * 32, by ignored).  Synchronises the stream. */

@@ -1586,6 +1586,9 @@ static TileCfg pick_cfg(int dim, int elem, int n, int smoother, int op, int by, 
 static bool valid_cfg(TileCfg c, int dim, int elem, bool var, int family) {
     if (c.xp != 1 && !(c.xp == 2 && family == 2 && !var && (dim == 2 ? c.wv == 4 : c.by <= 4 * c.wv)))
         return false;
+    if (c.wv == 1 && family == 2) {  // 3D refinement pass in FP32, one wavefront per column
+        return dim == 3 && c.xp == 1 && c.pd == 1 && (c.by == 6 || c.by == 8) && c.zchunk >= 1;
+    }
     if (c.wv == 1) {  // 3D sweep, one wavefront per tile
         if (dim != 3 || family != 0 || (c.by != 8 && c.by != 12)) return false;
     } else {
