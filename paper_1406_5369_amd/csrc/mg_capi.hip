@@ -1771,23 +1771,13 @@ int mg_level_residual_restrict(int dim, int n, int dtype, const void* k, const v
     h.fc = fc;
     h.n = n;
     h.c = level_c(n);
-    void* fxt = nullptr;  // face coefficients of a 3D variable-coefficient grid (freed after the launch)
-    int r = level_faces(dim, elem, n, k, s, &fxt);
-    if (r != MG_OK) return r;
-    h.fx = fxt;
     GridDesc* d = nullptr;
-    r = with_desc(h, s, &d);
-    if (r != MG_OK) {
-        (void)hipStreamSynchronize(s);
-        if (fxt) (void)hipFree(fxt);
-        return r;
-    }
-    hipError_t e = elem == 8   ? launch_restrict<double>(dim, k != nullptr, d, 1, n, 0, cfg, s)
-                   : elem == 4 ? launch_restrict<float>(dim, k != nullptr, d, 1, n, 0, cfg, s)
+    int r = with_desc(h, s, &d);
+    if (r != MG_OK) return r;
+    hipError_t e = elem == 8   ? launch_restrict<double>(dim, k != nullptr, d, 1, n, 0, cfg, s, true)
+                   : elem == 4 ? launch_restrict<float>(dim, k != nullptr, d, 1, n, 0, cfg, s, true)
                                : launch_restrict<half_t>(dim, false, d, 1, n, 0, cfg, s);
-    r = finish_desc(d, s, e);  // synchronises the stream
-    if (fxt) (void)hipFree(fxt);
-    return r;
+    return finish_desc(d, s, e);
 }
 
 int mg_level_prolong_correct(int dim, int n, int dtype, void* u, const void* ec, void* stream) {

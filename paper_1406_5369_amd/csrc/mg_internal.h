@@ -191,9 +191,10 @@ int down2d_tiles(int op, int n);
 // cfg.order the block order).
 template <typename T>
 hipError_t launch_smooth_restrict3d(const GridDesc* d, int ninst, int nf, int sel, TileCfg cfg, hipStream_t s);
+// nodal: a 3D grid with coefficients has no face arrays (GridDesc::fx).
 template <typename T>
-hipError_t launch_restrict(int dim, int op, const GridDesc* d, int ninst, int nf, int sel, TileCfg cfg,
-                           hipStream_t s);
+hipError_t launch_restrict(int dim, int op, const GridDesc* d, int ninst, int nf, int sel, TileCfg cfg, hipStream_t s,
+                           bool nodal = false);
 template <typename T>
 hipError_t launch_prolong(int dim, int op, const GridDesc* d, int ninst, int nf, int sel, hipStream_t s);
 // Largest tail edge for a dimension, word size and operator (levels at or

@@ -110,7 +110,12 @@ __host__ __device__ constexpr int restrict3d_cy() {
     return BY == 8 ? 2 : (OP == OP_VAR ? (sizeof(T) == 8 ? 2 : 3) : (BY == 32 && wide ? 6 : 4));
 }
 
-template <typename ST, int OP, int BY>
+// NK: the grid has no face arrays (a single-level call on nodal coefficients):
+// the faces of a plane are formed from its coefficients and the next plane's
+// (three divisions per node; a call at 257^3 FP64, wait included, takes 141 us,
+// with face arrays allocated and formed for the call 660 us, from an LDS tile
+// with six divisions per node 252 us; 513^3 FP32 500 / 1989 / 798 us).
+template <typename ST, int OP, int BY, bool NK>
 struct Restrict3 {
     using T = arith_t<ST>;
     static constexpr bool VAR = OP == OP_VAR;
@@ -118,7 +123,7 @@ struct Restrict3 {
     static constexpr int RR = 2 * CY + 1, UR = RR + 2;
     const MG_GLOBAL ST* __restrict__ u;
     const MG_GLOBAL ST* __restrict__ f;
-    const MG_GLOBAL T* __restrict__ fx;
+    const MG_GLOBAL T* __restrict__ fx;  // face coefficients, or with NK the nodal ones
     MG_GLOBAL ST* __restrict__ fc;
     int n, nc, X, Y0, Z0, Z1;
     bool colX;
@@ -127,6 +132,7 @@ struct Restrict3 {
     unsigned rb[UR];                 // byte offset of the lane's node of each row of u (clamped)
     T U[4][UR], F[2][RR];            // planes rp-1 .. rp+2 of u, rp and rp+1 of f, by plane
     T kx[VAR ? 2 : 1][RR], ky[VAR ? 2 : 1][RR + 1], kz[VAR ? 4 : 1][RR];
+    T kn[NK ? UR : 1];               // NK: coefficients of the plane whose faces come next
     T cb[CY], xb[CY], yb[CY], xyb[CY];  // of the last odd plane: R, and its sums over x, y and both
     T cc[CY], fcs[CY], xyc[CY];         // of the even plane: R, x and y sums, corner sums
 
@@ -146,17 +152,33 @@ struct Restrict3 {
 #pragma unroll
         for (int i = 0; i < R; ++i) dst[i] = b.load(rb[i + r0]);
     }
+    // Faces of plane z: along x and y, and to plane z + 1.
+    __device__ __forceinline__ void faces(int z, T (&x)[RR], T (&y)[RR + 1], T (&t)[RR]) {
+        if constexpr (NK) {
+            T ka[UR];  // of plane z + 1
+            load_k(0, z + 1, 0, ka);
+#pragma unroll
+            for (int i = 0; i <= RR; ++i) y[i] = kface(kn[i], kn[i + 1]);
+#pragma unroll
+            for (int i = 0; i < RR; ++i) {
+                x[i] = kface(kn[i + 1], lane_next(kn[i + 1]));
+                t[i] = kface(kn[i + 1], ka[i + 1]);
+            }
+#pragma unroll
+            for (int i = 0; i < UR; ++i) kn[i] = ka[i];
+        } else {
+            load_k(0, z, 1, x);
+            load_k(1, z, 0, y);
+            load_k(2, z, 1, t);
+        }
+    }
     // Residual plane rp (odd where Q is even).
     template <int Q>
     __device__ __forceinline__ void step(int rp) {
         constexpr int S0 = Q, S1 = (Q + 1) & 3, S2 = (Q + 2) & 3, S3 = (Q + 3) & 3, H = Q & 1;
         load_u(rp + 2, U[S3]);
         load_f(rp + 1, F[H ^ 1]);
-        if constexpr (VAR) {
-            load_k(0, rp + 1, 1, kx[H ^ 1]);
-            load_k(1, rp + 1, 0, ky[H ^ 1]);
-            load_k(2, rp + 1, 1, kz[S2]);
-        }
+        if constexpr (VAR) faces(rp + 1, kx[H ^ 1], ky[H ^ 1], kz[S2]);
         T R[RR], x[RR];
 #pragma unroll
         for (int i = 0; i < RR; ++i) {
@@ -203,11 +225,10 @@ struct Restrict3 {
         load_u(rp, U[1]);
         load_u(rp + 1, U[2]);
         load_f(rp, F[0]);
+        if constexpr (NK) load_k(0, rp - 1, 0, kn);
         if constexpr (VAR) {
-            load_k(0, rp, 1, kx[0]);
-            load_k(1, rp, 0, ky[0]);
-            load_k(2, rp - 1, 1, kz[0]);
-            load_k(2, rp, 1, kz[1]);
+            faces(rp - 1, kx[0], ky[0], kz[0]);  // (of its faces only those to plane rp are used)
+            faces(rp, kx[0], ky[0], kz[1]);
         }
 #pragma unroll
         for (int j = 0; j < CY; ++j) cb[j] = xb[j] = yb[j] = xyb[j] = cc[j] = fcs[j] = xyc[j] = T(0);
@@ -224,11 +245,11 @@ struct Restrict3 {
     }
 };
 
-template <typename ST, int OP, int BY>
+template <typename ST, int OP, int BY, bool NK>
 __global__ __launch_bounds__(64) void k_restrict3d(const GridDesc* __restrict__ descs, int sel, int zchunk) {
     const GridDesc& d = descs[blockIdx.y];
     if (d.done && *gp(d.done)) return;
-    using S = Restrict3<ST, OP, BY>;
+    using S = Restrict3<ST, OP, BY, NK>;
     S t;
     t.n = d.n;
     t.nc = (t.n - 1) / 2 + 1;
@@ -243,7 +264,7 @@ __global__ __launch_bounds__(64) void k_restrict3d(const GridDesc* __restrict__ 
     t.Z1 = min(t.Z0 + zchunk, t.nc - 1);
     t.u = gp((const ST*)(sel ? d.t : d.u));
     t.f = gp((const ST*)d.f);
-    t.fx = gp((const typename S::T*)d.fx);
+    t.fx = gp((const typename S::T*)(NK ? d.k : d.fx));
     t.fc = gp((ST*)d.fc);
     t.c = (typename S::T)d.c;
     load_stencil<OP>(d, t.sc);
@@ -554,25 +575,28 @@ int norm_tiles(int dim, int n, TileCfg cfg) {
 
 namespace {
 template <typename T, int OPV, int BY>
-hipError_t launch_restrict3d_by(const GridDesc* d, int ninst, int nf, int sel, TileCfg cfg, hipStream_t s) {
-    using S = Restrict3<T, OPV, BY>;
+hipError_t launch_restrict3d_by(const GridDesc* d, int ninst, int nf, int sel, TileCfg cfg, bool nodal, hipStream_t s) {
+    using S = Restrict3<T, OPV, BY, false>;
     const int mc = (nf - 1) / 2 - 1;
     const dim3 grid(cdiv(mc, S::CX) * cdiv(mc, S::CY) * nzchunks(mc, cfg.zchunk), ninst);
-    k_restrict3d<T, OPV, BY><<<grid, 64, 0, s>>>(d, sel, cfg.zchunk);
+    if (nodal) k_restrict3d<T, OPV, BY, OPV == OP_VAR><<<grid, 64, 0, s>>>(d, sel, cfg.zchunk);
+    else k_restrict3d<T, OPV, BY, false><<<grid, 64, 0, s>>>(d, sel, cfg.zchunk);
     return hipGetLastError();
 }
 template <typename T, int OPV>
-hipError_t launch_restrict_op(int dim, const GridDesc* d, int ninst, int nf, int sel, TileCfg cfg, hipStream_t s) {
+hipError_t launch_restrict_op(int dim, const GridDesc* d, int ninst, int nf, int sel, TileCfg cfg, bool nodal,
+                              hipStream_t s) {
     if (dim == 2) {
         const dim3 grid(restrict_tiles(nf, cfg), ninst);
         MG_BY_SWITCH(cfg.by, (k_restrict2d<T, OPV, BY><<<grid, NT, 0, s>>>(d, sel)))
         return hipGetLastError();
     }
     switch (cfg.by) {
-        case 8: return launch_restrict3d_by<T, OPV, 8>(d, ninst, nf, sel, cfg, s);
-        case 16: return launch_restrict3d_by<T, OPV, 16>(d, ninst, nf, sel, cfg, s);
+        case 8: return launch_restrict3d_by<T, OPV, 8>(d, ninst, nf, sel, cfg, nodal, s);
+        case 16: return launch_restrict3d_by<T, OPV, 16>(d, ninst, nf, sel, cfg, nodal, s);
         case 32:  // taller columns of 32-bit constant operators only
-            return launch_restrict3d_by<T, OPV, (sizeof(T) <= 4 && OPV != OP_VAR) ? 32 : 16>(d, ninst, nf, sel, cfg, s);
+            return launch_restrict3d_by<T, OPV, (sizeof(T) <= 4 && OPV != OP_VAR) ? 32 : 16>(d, ninst, nf, sel, cfg,
+                                                                                              nodal, s);
         default: return hipErrorInvalidValue;
     }
 }
@@ -586,16 +610,16 @@ hipError_t launch_coarsest_op(int dim, const GridDesc* d, int ninst, hipStream_t
 
 // binary16 storage: Laplacian only; a constant stencil: FP64 only
 template <typename T>
-hipError_t launch_restrict(int dim, int op, const GridDesc* d, int ninst, int nf, int sel, TileCfg cfg,
-                           hipStream_t s) {
+hipError_t launch_restrict(int dim, int op, const GridDesc* d, int ninst, int nf, int sel, TileCfg cfg, hipStream_t s,
+                           bool nodal) {
     if (op == OP_CC) return cc_launch_restrict(dim, d, ninst, nf, sel, s);
     if (nf < 5 || ninst <= 0) return hipErrorInvalidValue;
-    if (op == OP_LAP) return launch_restrict_op<T, OP_LAP>(dim, d, ninst, nf, sel, cfg, s);
+    if (op == OP_LAP) return launch_restrict_op<T, OP_LAP>(dim, d, ninst, nf, sel, cfg, nodal, s);
     if constexpr (sizeof(T) >= 4) {
-        if (op == OP_VAR) return launch_restrict_op<T, OP_VAR>(dim, d, ninst, nf, sel, cfg, s);
+        if (op == OP_VAR) return launch_restrict_op<T, OP_VAR>(dim, d, ninst, nf, sel, cfg, nodal, s);
     }
     if constexpr (sizeof(T) == 8) {
-        if (op == OP_STENCIL) return launch_restrict_op<T, OP_STENCIL>(dim, d, ninst, nf, sel, cfg, s);
+        if (op == OP_STENCIL) return launch_restrict_op<T, OP_STENCIL>(dim, d, ninst, nf, sel, cfg, nodal, s);
     }
     return hipErrorInvalidValue;
 }
@@ -649,7 +673,7 @@ hipError_t launch_copy_bytes(void* dst, const void* src, size_t bytes, hipStream
 }
 
 #define MG_INST(T)                                                                                              \
-    template hipError_t launch_restrict<T>(int, int, const GridDesc*, int, int, int, TileCfg, hipStream_t);    \
+    template hipError_t launch_restrict<T>(int, int, const GridDesc*, int, int, int, TileCfg, hipStream_t, bool);    \
     template hipError_t launch_prolong<T>(int, int, const GridDesc*, int, int, int, hipStream_t);                    \
     template hipError_t launch_coarsest<T>(int, int, const GridDesc*, int, hipStream_t);                       \
     template hipError_t launch_copy_t_to_u<T>(int, const GridDesc*, int, int, hipStream_t);                     \
