@@ -1598,10 +1598,9 @@ static bool valid_cfg(TileCfg c, int dim, int elem, bool var, int family) {
     return c.by <= max_tile_rows(dim, elem, var, family, c.wv) && c.zchunk >= 1 && (c.pd == 1 || c.pd == 2);
 }
 
-// Temporary device descriptor for a context-free call; the stream is synchronised before release.
-static // Face coefficients of a 3D grid with nodal coefficients k, for one launch
+// Face coefficients of a 3D grid with nodal coefficients k, for one launch
 // (else none).
-int level_faces(int dim, int elem, int n, const void* k, hipStream_t s, void** fx) {
+static int level_faces(int dim, int elem, int n, const void* k, hipStream_t s, void** fx) {
     *fx = nullptr;
     if (!k || dim != 3) return MG_OK;
     CK(hipMalloc(fx, 3 * npts(3, n) * (size_t)elem));
@@ -1614,7 +1613,8 @@ int level_faces(int dim, int elem, int n, const void* k, hipStream_t s, void** f
     return dev_status(e);
 }
 
-int with_desc(const GridDesc& h, hipStream_t s, GridDesc** d) {
+// Temporary device descriptor for a context-free call; the stream is synchronised before release.
+static int with_desc(const GridDesc& h, hipStream_t s, GridDesc** d) {
     CK(hipMalloc((void**)d, sizeof(GridDesc)));
     CK(hipMemcpyAsync(*d, &h, sizeof(GridDesc), hipMemcpyHostToDevice, s));
     return MG_OK;
