@@ -84,6 +84,9 @@ struct Group {
     std::vector<GridDesc> h;       // host mirror
 };
 
+// Largest edge whose levels run legs: kLegMaxN, or less with MG_LEG_MAX_EDGE (0: none).
+int leg_max_edge();
+
 struct Problem {
     int dim, smoother, nu1, nu2;  // smoother: SM_RBGS or SM_JACOBI (the kernels' relaxations)
     double omega;
@@ -94,6 +97,7 @@ struct Problem {
     double sc[7] = {0, 0, 0, 0, 0, 0, 0};
     bool cc = false;  // cells with a Neumann boundary (FP64)
     int op() const { return cc ? OP_CC : stencil ? OP_STENCIL : (var ? OP_VAR : OP_LAP); }
+    int leg_max = leg_max_edge();
     int cg_iters = 0;   // conjugate-gradient steps on a coarsest level with n > 3 (0: 4 (n - 1))
 };
 

@@ -192,9 +192,22 @@ bool post2_ok(const Problem& P, int dim, const Tiles& t) {
            t.smooth_pro2.zchunk > 0 && std::getenv("MG_NO_FUSED_POST2") == nullptr;
 }
 
+int leg_max_edge() {
+    const char* e = std::getenv("MG_LEG_MAX_EDGE");
+    return e ? std::min(std::atoi(e), kLegMaxN) : kLegMaxN;
+}
+
+// Legs are taken wherever they run: per V(2,2) cycle and solve step they were
+// faster than sweeps (or pairs of them) and restriction apart on every size, type
+// and sweep count timed (us, apart -> legs).  FP64: 257^2 90 -> 50, 1025^2 161 ->
+// 88, 4097^2 694 -> 370, 8193^2 2297 -> 1191, V(1,1) 4097^2 447 -> 357; FP32: 257^2
+// 86 -> 46, 4097^2 457 -> 313, 8193^2 1385 -> 1028, V(3,3) 4097^2 656 -> 470;
+// binary16: 4097^2 478 -> 290; coefficients FP64: 257^2 143 -> 60, 1025^2 265 ->
+// 116, 2049^2 480 -> 211, 4097^2 1382 -> 621, V(1,1) 841 -> 576, V(3,3) 1916 ->
+// 1135; coefficients FP32: 2049^2 406 -> 201, 4097^2 1063 -> 545.
 bool leg_ok(const Problem& P, int n) {
     return P.dim == 2 && P.smoother == SM_RBGS && P.op() != OP_CC && P.nu1 >= 1 && P.nu2 >= 1 && n >= 5 &&
-           n <= kLegMaxN;
+           n <= P.leg_max;
 }
 
 // Two sweeps in one launch where its boxes cover most of the chip: a box's march
