@@ -305,9 +305,10 @@ hipError_t ascend(const Problem& P, const Group& g, const Tiles& t, bool top, in
         i = P.nu2 >= 2 ? 2 : 1;
         MG_TRY(launch_up2d<T>(P.op(), g.d, g.ninst, g.n, post_sel(P, cur), i, s));
         cur ^= 1;
-    } else if (cur == 1 && post2_ok<T>(P, P.dim, t)) {
+    } else if (post2_ok<T>(P, P.dim, t) && (cur == 1 || (up_launches<T>(P, t, g.n, g.ninst) & 1) == cur)) {
+        // (from u only where the sweeps after it bring the iterate back there)
         MG_TRY(launch_smooth2d_pro2<T>(g.d, g.ninst, g.n, post_sel(P, cur), t.smooth_pro2, s));
-        cur = 0;
+        cur ^= 1;
         i = 2;
     }
     while (i < P.nu2) {

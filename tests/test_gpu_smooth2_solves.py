@@ -62,6 +62,16 @@ def test_sweep_counts_around_the_pairs(edge, smoother, cycle, nu1, nu2, dev_ok, 
     solve(257, 1, smoother, cycle, nu1, nu2, steps=3)
 
 
+# plain finest-level sweeps a step: all but the pair from zero and the pair with the correction
+@pytest.mark.parametrize("nu1,nu2", [(2, 2), (2, 3), (3, 3), (2, 4), (2, 5), (4, 3)])
+def test_pairs_run_whatever_the_sweep_counts(nu1, nu2, dev_ok, monkeypatch):
+    for k, v in dict(FORCED, MG_LEG_MAX_EDGE="0").items():
+        monkeypatch.setenv(k, v)
+    pair, sweeps = solve(257, 1, nu1=nu1, nu2=nu2, steps=3, prof=True)
+    assert pair == [True, True]
+    assert sweeps == 3 * (nu1 - 2 + nu2 - 2)
+
+
 def test_batch_with_the_pairs(dev_ok, monkeypatch):
     import torch
 
