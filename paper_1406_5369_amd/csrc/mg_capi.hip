@@ -636,14 +636,18 @@ constexpr size_t kTuneMinPoints = 1u << 16;
 // Candidate launch geometries.  In 3D, smoothing (family 0) and the norm /
 // refinement pass (family 2) also vary the wavefronts per workgroup (8 for
 // 16- and 32-row tiles); smoothing also runs one wavefront per tile with 8 or
-// 12 rows in registers.
-std::vector<TileCfg> tune_candidates(int dim, int planes, bool with_pd, int family, int elem, bool var) {
+// 12 rows in registers (red-black sweeps of the Laplacian by colour: no prefetch
+// depths).
+std::vector<TileCfg> tune_candidates(int dim, int planes, bool with_pd, int family, int elem, bool var,
+                                     int smoother = SM_JACOBI) {
     std::vector<TileCfg> v;
     const int geo[7][2] = {{8, 4}, {16, 4}, {32, 4}, {16, 8}, {32, 8}, {8, 1}, {12, 1}};
     for (const auto& g : geo) {
         const int by = g[0], wv = g[1];
         if (wv != 4 && (dim == 2 || family == 1 || (family == 2 && wv == 1))) continue;
         if (by > max_tile_rows(dim, elem, var, family, wv)) continue;
+        if (family == 1 && by != restrict_rows(dim, elem, var, by)) continue;
+        const bool pd2 = with_pd && !(wv == 1 && smoother == SM_RBGS && !var);
         if (dim == 2) {
             v.push_back({by, 1, 1, 4});
             if (family == 2 && !var && by == 16) {  // two nodes per lane, marching chunks of rows
@@ -657,7 +661,7 @@ std::vector<TileCfg> tune_candidates(int dim, int planes, bool with_pd, int fami
         for (int zc = 4; zc <= 256; zc *= 2) {
             if (zc > std::max(4, planes)) break;
             v.push_back({by, zc, 1, wv});
-            if (with_pd) v.push_back({by, zc, 2, wv});
+            if (pd2) v.push_back({by, zc, 2, wv});
             if (family == 2 && !var && by <= 4 * wv) {  // two nodes per lane, at most four rows per thread
                 v.push_back({by, zc, 1, wv, 0, 2});
                 if (with_pd) v.push_back({by, zc, 2, wv, 0, 2});
@@ -855,8 +859,10 @@ hipError_t tune_levels(mg_ctx* c, const Levels& L, std::vector<Tiles>& tl, void*
         // coarse-grid correction) load different data and are tuned separately
         const int vflags[3] = {0, SWEEP_ZERO_GUESS, SWEEP_PROLONG};
         TileCfg* vcfg[3] = {&tl[(size_t)l].smooth, &tl[(size_t)l].smooth_zg, &tl[(size_t)l].smooth_pro};
+        const bool leg = leg_ok(c->prob, n);
         for (int v = 0; v < 3; ++v) {
             const int fl = vflags[v];
+            if (leg && !leg_leaves(c->prob, fl)) continue;
             TuneKey ks{dim, L.elem, n, 0, sm, var ? 1 : 0, 10 + v, 0};
             if (!tune_lookup(ks, &cfg)) {
                 auto run = [&](TileCfg t) {
@@ -864,7 +870,7 @@ hipError_t tune_levels(mg_ctx* c, const Levels& L, std::vector<Tiles>& tl, void*
                            : L.elem == 4 ? launch_smooth<float>(dim, sm, var, d, 1, n, 0, fl, t, s)
                                          : launch_smooth<half_t>(dim, sm, var, d, 1, n, 0, fl, t, s);
                 };
-                cfg = pick_fastest(tune_candidates(dim, n - 2, true, 0, L.elem, var), *vcfg[v], run, s);
+                cfg = pick_fastest(tune_candidates(dim, n - 2, true, 0, L.elem, var, sm), *vcfg[v], run, s);
                 cfg = pick_order(cfg, run, s);
                 tune_store(ks, cfg);
             }
@@ -872,7 +878,7 @@ hipError_t tune_levels(mg_ctx* c, const Levels& L, std::vector<Tiles>& tl, void*
         }
         // FP64 finest level: the first pre-smoothing sweep that also sums the
         // incoming iterate's r^2 (LDS tile geometries only)
-        if (l == 0 && L.elem == 8 && c->nrm_fused) {
+        if (l == 0 && L.elem == 8 && c->nrm_fused && !(leg && !leg_leaves(c->prob, SWEEP_NORM))) {
             TuneKey kn{dim, 8, n, 0, sm, var ? 1 : 0, 13, 0};
             if (!tune_lookup(kn, &cfg)) {
                 h.npart = c->d_spart;
@@ -889,7 +895,9 @@ hipError_t tune_levels(mg_ctx* c, const Levels& L, std::vector<Tiles>& tl, void*
             tl[(size_t)l].smooth_nrm = cfg;
         }
         TuneKey kr{dim, L.elem, n, 1, 0, var ? 1 : 0, 0, 0};
-        if (!tune_lookup(kr, &cfg)) {
+        if (leg) {
+            cfg = tl[(size_t)l].restr;
+        } else if (!tune_lookup(kr, &cfg)) {
             std::vector<TileCfg> cands;
             for (TileCfg t : tune_candidates(dim, (n - 1) / 2 - 1, false, 1, L.elem, var))
                 if (t.by >= 8) cands.push_back(t);
@@ -938,7 +946,6 @@ hipError_t tune_levels(mg_ctx* c, const Levels& L, std::vector<Tiles>& tl, void*
         }
         // the first two pre-smoothing sweeps from a zero iterate in one launch,
         // kept if it beats the two sweeps it replaces
-        const bool leg = leg_ok(c->prob, n);
         if (!var && sm == SM_RBGS && L.elem <= 4 && c->p.nu1 >= 2 && !leg) {
             TuneKey k2{dim, L.elem, n, 6, sm, 0, 0, 0};
             if (!tune_lookup(k2, &cfg)) {
@@ -1038,17 +1045,20 @@ hipError_t tune_group(const Problem& P, const GridDesc* d, int count, int n, Til
     TileCfg* vcfg[3] = {&t.smooth, &t.smooth_zg, &t.smooth_pro};
     for (int v = 0; v < 3; ++v) {
         const int fl = vflags[v];
+        if (leg && !leg_leaves(P, fl)) continue;
         TuneKey ks{dim, 4, n, 0, smoother, 0, 10 + v, bucket};
         if (!tune_lookup(ks, &cfg)) {
             auto run = [&](TileCfg c) { return launch_smooth<float>(dim, smoother, false, d, count, n, 0, fl, c, s); };
-            cfg = pick_fastest(tune_candidates(dim, n - 2, true, 0, 4, false), *vcfg[v], run, s);
+            cfg = pick_fastest(tune_candidates(dim, n - 2, true, 0, 4, false, smoother), *vcfg[v], run, s);
             cfg = pick_order(cfg, run, s);
             tune_store(ks, cfg);
         }
         *vcfg[v] = cfg;
     }
     TuneKey kr{dim, 4, n, 1, 0, 0, 0, bucket};
-    if (!tune_lookup(kr, &cfg)) {
+    if (leg) {
+        cfg = t.restr;
+    } else if (!tune_lookup(kr, &cfg)) {
         std::vector<TileCfg> cands;
         for (TileCfg c : tune_candidates(dim, (n - 1) / 2 - 1, false, 1, 4, false))
             if (c.by >= 8) cands.push_back(c);

@@ -39,6 +39,14 @@ inline int max_tile_rows(int dim, int elem, bool var, int family, int wv = 4) {
     return rows_per_thread * wv < 32 ? rows_per_thread * wv : 32;
 }
 
+// Rows whose restriction columns a launch with 'by' rows runs: in 3D taller ones
+// are built for 32-bit constant operators only, with FP64 coefficients the lowest.
+constexpr int restrict_rows(int dim, int elem, bool var, int by) {
+    if (dim == 2) return by;
+    if (elem == 8 && var) return 8;
+    return by == 32 && (elem == 8 || var) ? 16 : by;
+}
+
 enum Smoother { SM_RBGS = 0, SM_JACOBI = 1 };
 
 // Operators of the kernels: on nodes the Laplacian, nodal coefficients, a

@@ -104,6 +104,9 @@ struct Problem {
 // Whether a level of edge n runs each of its legs with its last two pre- and
 // first two post-smoothing sweeps in one launch (launch_down2d, launch_up2d).
 bool leg_ok(const Problem& P, int n);
+// Whether such a level still launches sweeps with 'flags' of their own (its
+// restriction and its first sweep with the correction it never does).
+bool leg_leaves(const Problem& P, int flags);
 // Whether two sweeps of a level of 'ninst' grids, the first with 'flags', run
 // as one launch (launch_smooth3d_x2).
 bool pair_ok(const Problem& P, const Tiles& t, int flags, int n, int ninst);

@@ -72,6 +72,7 @@ Tiles default_tiles(int dim, int elem_bytes, int n, int smoother, int op) {
         return t;
     }
     Tiles t = lds_tiles(dim, n, smoother);
+    t.restr.by = restrict_rows(dim, elem_bytes, op == OP_VAR, t.restr.by);
     if (dim == 3 && smoother == SM_RBGS && op != OP_VAR) {
         // One wavefront per 64 x 8 tile, nodes held by colour: measured against
         // the LDS tiles above, 33^3 4.5 / 6.5 us, 65^3 4.9 / 6.5 us, 129^3 9.0 /
@@ -208,6 +209,11 @@ int leg_max_edge() {
 bool leg_ok(const Problem& P, int n) {
     return P.dim == 2 && P.smoother == SM_RBGS && P.op() != OP_CC && P.nu1 >= 1 && P.nu2 >= 1 && n >= 5 &&
            n <= P.leg_max;
+}
+
+bool leg_leaves(const Problem& P, int flags) {
+    if (flags & SWEEP_PROLONG) return false;
+    return P.nu1 > 2 || (flags == 0 && P.nu2 > 2);
 }
 
 // Two sweeps in one launch where its boxes cover most of the chip: a box's march

@@ -592,11 +592,12 @@ hipError_t launch_restrict_op(int dim, const GridDesc* d, int ninst, int nf, int
         return hipGetLastError();
     }
     switch (cfg.by) {
-        case 8: return launch_restrict3d_by<T, OPV, 8>(d, ninst, nf, sel, cfg, nodal, s);
-        case 16: return launch_restrict3d_by<T, OPV, 16>(d, ninst, nf, sel, cfg, nodal, s);
-        case 32:  // taller columns of 32-bit constant operators only
-            return launch_restrict3d_by<T, OPV, (sizeof(T) <= 4 && OPV != OP_VAR) ? 32 : 16>(d, ninst, nf, sel, cfg,
-                                                                                              nodal, s);
+        case 8: return launch_restrict3d_by<T, OPV, restrict_rows(3, sizeof(T), OPV == OP_VAR, 8)>(
+            d, ninst, nf, sel, cfg, nodal, s);
+        case 16: return launch_restrict3d_by<T, OPV, restrict_rows(3, sizeof(T), OPV == OP_VAR, 16)>(
+            d, ninst, nf, sel, cfg, nodal, s);
+        case 32: return launch_restrict3d_by<T, OPV, restrict_rows(3, sizeof(T), OPV == OP_VAR, 32)>(
+            d, ninst, nf, sel, cfg, nodal, s);
         default: return hipErrorInvalidValue;
     }
 }

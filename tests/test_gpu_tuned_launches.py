@@ -1,0 +1,44 @@
+"""The tuner times launches that a solve makes and no launch twice: 2D levels
+that run whole legs keep the built-in geometry of the sweeps and restrictions they
+never launch, and no reported tile names a second form of the same kernel."""
+
+import pytest
+
+import inputs
+
+pytestmark = pytest.mark.gpu
+
+SMOOTH, RESTRICT, ZERO, CORRECT = 0, 1, 3, 4
+
+
+def tiles(monkeypatch, tuned, families, **par):
+    import torch
+
+    import paper_1406_5369_amd as m
+
+    if par.pop("varcoef", False):
+        par.update(op=m.OP_VARCOEF_NODAL,
+                   k=torch.from_numpy(inputs.varcoef_k(par["n"], 3, dim=par["dim"])).to("cuda"))
+    with monkeypatch.context() as env:
+        if not tuned:
+            env.setenv("MG_AUTOTUNE", "0")
+        with m.Solver(m.Params(**par)) as s:
+            levels = [l for l in range(s.num_levels) if (par["n"] - 1) >> l >= 4]
+            return [m.mg_tile_config(s.ctx, l, f, with_order=True) for l in levels for f in families]
+
+
+@pytest.mark.parametrize("precision,varcoef", [(0, False), (0, True), (1, False), (1, True), (2, False)])
+@pytest.mark.parametrize("nu,families", [(2, (SMOOTH, RESTRICT, ZERO, CORRECT)), (3, (RESTRICT, CORRECT))])
+def test_leg_levels_tune_what_they_launch(precision, varcoef, nu, families, dev_ok, monkeypatch):
+    par = dict(dim=2, n=2049, precision=precision, varcoef=varcoef, nu1=nu, nu2=nu)
+    assert tiles(monkeypatch, True, families, **par) == tiles(monkeypatch, False, families, **par)
+
+
+@pytest.mark.parametrize("precision,varcoef", [(0, False), (0, True), (1, False), (1, True)])
+def test_tiles_name_one_kernel_each(precision, varcoef, dev_ok, monkeypatch):
+    par = dict(dim=3, n=129, precision=precision, varcoef=varcoef)
+    rows = {(0, False): (8, 16), (0, True): (8,), (1, False): (8, 16, 32), (1, True): (8, 16)}[precision, varcoef]
+    for tuned in (True, False):
+        assert all(t[0] in rows for t in tiles(monkeypatch, tuned, (RESTRICT,), **par))
+        for by, _, prefetch, waves, *_ in tiles(monkeypatch, tuned, (SMOOTH, ZERO, CORRECT), **par):
+            assert waves != 1 or varcoef or prefetch == 1  # by colour: no prefetch depths
