@@ -322,15 +322,22 @@ void destroy(mg_ctx* c) {
 }
 
 // Point the level-0 descriptors at the caller's u and f (only when they change).
-int bind(mg_ctx* c, const void* u, const void* f) {
+int* ctl_done(mg_ctx* c) { return c->d_ctrl; }
+int* ctl_steps(mg_ctx* c) { return c->d_ctrl + 1; }
+int* ctl_status(mg_ctx* c) { return c->d_ctrl + 2; }
+
+// The arrays of the calls that follow; 'start': also clear the stop flag a
+// previous solve left set (every kernel honours it).
+int bind(mg_ctx* c, const void* u, const void* f, bool start) {
     if (!u || !f) return MG_EINVAL;
     // Stencils and cells: by a kernel and on every call, so that mg_vcycle neither
     // waits nor copies from the host (it may be captured) and a replayed capture,
     // which binds its own arrays, leaves nothing behind for a later call.
     if (c->st || c->cc) {
-        CK(launch_bind(c->d_top, c->G64[0].d, const_cast<void*>(u), f, c->stream));
+        CK(launch_bind(c->d_top, c->G64[0].d, const_cast<void*>(u), f, start ? ctl_done(c) : nullptr, c->stream));
         return MG_OK;
     }
+    if (start) CK(launch_fill_int(ctl_done(c), 0, 1, c->stream));
     if (u == c->bound_u && f == c->bound_f) return MG_OK;
     c->h_top.u = const_cast<void*>(u);
     c->h_top.f = f;
@@ -350,10 +357,6 @@ int bind(mg_ctx* c, const void* u, const void* f) {
     c->bound_f = f;
     return MG_OK;
 }
-
-int* ctl_done(mg_ctx* c) { return c->d_ctrl; }
-int* ctl_steps(mg_ctx* c) { return c->d_ctrl + 1; }
-int* ctl_status(mg_ctx* c) { return c->d_ctrl + 2; }
 
 // FP64 norm of the bound (u, f) into d_norm (partials + fixed-order finalize).
 // With 'step' > 0 and measurement on, the finest-level pass (not its
@@ -1442,9 +1445,8 @@ int mg_vcycle(mg_ctx* c, double* u, const double* f) {
     if (!c) return MG_EINVAL;
     if (is_batch_handle(c)) return MG_EINVAL;
     if (c->cd) return MG_EINVAL;  // complex-diffusion handles take the mg_cdiff_* calls
-    int r = bind(c, u, f);
+    int r = bind(c, u, f, true);
     if (r != MG_OK) return r;
-    CK(launch_fill_int(ctl_done(c), 0, 1, c->stream));
     if (c->p.precision == MG_PREC_FP64) {
         CK(vcycle<double>(c->prob, c->G64, false, c->tl64, c->stream, nullptr, nullptr, 0, &c->tail64));
     } else {
@@ -1462,7 +1464,7 @@ int mg_residual_norm(mg_ctx* c, const double* u, const double* f, double* out) {
     if (!c || !out) return MG_EINVAL;
     if (is_batch_handle(c)) return MG_EINVAL;
     if (c->cd) return MG_EINVAL;  // complex-diffusion handles take the mg_cdiff_* calls
-    int r = bind(c, u, f);
+    int r = bind(c, u, f, false);
     if (r != MG_OK) return r;
     CK(enqueue_norm(c, c->stream));
     CK(hipMemcpyAsync(c->h_pin, c->d_norm, sizeof(double), hipMemcpyDeviceToHost, c->stream));
@@ -1482,7 +1484,7 @@ int mg_solve(mg_ctx* c, double* u, const double* f, double tol, int max_cycles, 
         CK(cc_remove_mean(c->p.dim, c->p.n, c->ccfh, c->cc_work, c->cc_mean, s));
         f = c->ccfh;
     }
-    int r = bind(c, u, f);
+    int r = bind(c, u, f, true);
     if (r != MG_OK) return r;
     r = ensure_hist(c, max_cycles + 1);
     if (r != MG_OK) return r;
@@ -1490,8 +1492,7 @@ int mg_solve(mg_ctx* c, double* u, const double* f, double tol, int max_cycles, 
     c->prof_n = 0;  // measured launches are tagged per solve
     c->prof_step.clear();
     c->prof_kind.clear();
-    // rho_0 (clear the stop flag a previous solve left set first: every kernel honours it)
-    CK(launch_fill_int(ctl_done(c), 0, 1, s));
+    // rho_0
     if (c->cc) CK(enqueue_mean(c, s));
     if (ir) CK(enqueue_ir_start(c, s));
     else if (c->nrm_fused) CK(enqueue_nrm_sweep(c, s));

@@ -293,8 +293,9 @@ hipError_t launch_inject(int dim, int nf, const TS* src, int nc, TD* dst, hipStr
 template <typename TS, typename TD>
 hipError_t launch_convert(size_t total, const TS* src, TD* dst, hipStream_t s);
 hipError_t launch_fill_int(int* p, int v, int count, hipStream_t s);
-// The iterate and right-hand side of two descriptors of one grid.
-hipError_t launch_bind(GridDesc* a, GridDesc* b, void* u, const void* f, hipStream_t s);
+// The iterate and right-hand side of two descriptors of one grid; 'done', if
+// not null, is cleared.
+hipError_t launch_bind(GridDesc* a, GridDesc* b, void* u, const void* f, int* done, hipStream_t s);
 
 // Plain device copy of 'bytes' bytes (bandwidth calibration kernel).
 hipError_t launch_copy_bytes(void* dst, const void* src, size_t bytes, hipStream_t s);

@@ -1219,7 +1219,8 @@ __global__ void k_fill_int(int* __restrict__ p, int v, int count) {
     if (i < count) p[i] = v;
 }
 
-__global__ void k_bind(GridDesc* a, GridDesc* b, void* u, const void* f) {
+__global__ void k_bind(GridDesc* a, GridDesc* b, void* u, const void* f, int* done) {
+    if (done && threadIdx.x == 0) *done = 0;
     GridDesc* d = threadIdx.x == 0 ? a : b;
     d->u = u;
     d->f = f;
@@ -1497,8 +1498,8 @@ hipError_t launch_fill_int(int* p, int v, int count, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_bind(GridDesc* a, GridDesc* b, void* u, const void* f, hipStream_t s) {
-    k_bind<<<1, 2, 0, s>>>(a, b, u, f);
+hipError_t launch_bind(GridDesc* a, GridDesc* b, void* u, const void* f, int* done, hipStream_t s) {
+    k_bind<<<1, 2, 0, s>>>(a, b, u, f, done);
     return hipGetLastError();
 }
 
