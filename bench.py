@@ -36,10 +36,10 @@ sys.path.insert(0, ROOT)
 
 from paper_1406_5369_amd.profsum import (  # noqa: E402
     kernel_source_hash,
+    launched_sweep,
     pass_blocks,
     pass_kernel,
     sweep_blocks,
-    sweep_kernel,
 )
 
 HBM_PEAK_GBPS = 8000.0  # MI355X HBM3E, datasheet
@@ -76,12 +76,11 @@ def make_rhs(w):
     return inputs.uniform_rhs(w["dim"], w["n"], w["rhs"][1])
 
 
-def traffic_record(workload: str, tiles, key: str = "configs") -> dict | None:
-    """HBM bytes per launch of a finest-level kernel (the sweep, key "configs",
-    or the refinement pass, key "pass_configs", with the given tile geometry)
-    from the committed rocprofv3 counter runs (FETCH_SIZE and WRITE_SIZE, each
-    calibrated on a 1 GiB copy), if they were taken on the current kernel
-    source; else None."""
+def launch_traffic(workload: str, kernel: str, blocks: int) -> int | None:
+    """HBM bytes per launch of a finest-level kernel from the committed
+    rocprofv3 counter runs (FETCH_SIZE and WRITE_SIZE, each calibrated on a
+    1 GiB copy), if they hold it and were taken on the current kernel source;
+    else None."""
     path = os.path.join(ROOT, "profiles", "traffic.json")
     if not os.path.exists(path):
         return None
@@ -92,7 +91,8 @@ def traffic_record(workload: str, tiles, key: str = "configs") -> dict | None:
         return None
     if not rec or rec.get("source_hash") != kernel_source_hash():
         return None
-    return rec.get(key, {}).get(",".join(str(t) for t in tiles))
+    return next((e["bytes_per_launch"] for e in rec.get("launches", ())
+                 if (e["kernel"], e["blocks"]) == (kernel, blocks)), None)
 
 
 def cpu_baseline(w, gpu_steps: int, budget_s: float, min_steps: int = 3):
@@ -667,43 +667,39 @@ def main(argv=None) -> int:
     # refinement pass: FP64 u and f read, e read (float or binary16), FP64 u and r (float / binary16) written
     pass_bytes = (8 + 8 + 8 + 2 * word) if ir else 16
 
-    def roof(kernel, blocks, note, n_launch, total_ms, bytes_per_launch, tr):
+    def roof(kernel, blocks, note, n_launch, total_ms, bytes_per_launch):
         avg_ms = total_ms / max(n_launch, 1)
         achieved = bytes_per_launch / (avg_ms * 1e-3) / 1e9 if n_launch else 0.0
         r = {"bound": "hbm", "kernel": kernel, "blocks": blocks, "note": note, "launches": n_launch,
              "avg_launch_ms": avg_ms, "total_ms": total_ms, "algorithmic_bytes_per_launch": bytes_per_launch,
              "achieved": achieved, "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBPS,
              "copy_ceiling": copy_gbps, "frac_of_copy_ceiling": achieved / copy_gbps, "traffic": None}
-        if tr and tr.get("kernel") == kernel and tr.get("blocks") == blocks:
-            r["traffic"] = tr["bytes_per_launch"]
-            r["traffic_ratio_to_algorithmic"] = tr["ratio_to_algorithmic"]
+        moved = launch_traffic(args.workload, kernel, blocks)
+        if moved:
+            r["traffic"] = moved
+            r["traffic_ratio_to_algorithmic"] = moved / bytes_per_launch
         return r
 
     by, zchunk, pd, wv = mg.mg_tile_config(solver.ctx, 0, 0)
-    kname = sweep_kernel(dim, word, by, pd, var, wv)
-    sweep_roof = roof(kname, sweep_blocks(dim, n, by, zchunk),
+    sweep_roof = roof(launched_sweep(dim, word, by, pd, var, wv), sweep_blocks(dim, n, by, zchunk),
                       "finest-level RBGS sweeps that read the previous iterate (zero-iterate and fused-correction "
-                      "variants excluded)", launches, sweep_ms, (4 if var else 3) * word * dof,
-                      traffic_record(args.workload, (by, zchunk, pd, wv)))
+                      "variants excluded)", launches, sweep_ms, (4 if var else 3) * word * dof)
     pby, pzc, ppd, pwv, _, ppr = mg.mg_tile_config(solver.ctx, 0, 2, with_order=True)
     nby, nzc, npd, nwv = mg.mg_tile_config(solver.ctx, 0, 6)
     if not ir and nzc > 0:
         # FP64 solves sum each cycle's residual norm in the next cycle's first
         # pre-smoothing sweep (reads u and f, writes the other buffer): the
         # event brackets time that sweep
-        pass_roof = roof(sweep_kernel(dim, word, nby, npd, var, nwv, flags=4), sweep_blocks(dim, n, nby, nzc),
+        pass_roof = roof(launched_sweep(dim, word, nby, npd, var, nwv, flags=4), sweep_blocks(dim, n, nby, nzc),
                          "finest-level FP64 first pre-smoothing launch (a sweep, on large 3D grids two) that also "
-                         "sums the residual norm of its incoming iterate", pass_launches, pass_ms, (4 if var else 3) * word * dof,
-                         traffic_record(args.workload, (nby, nzc, npd, nwv, "n")))
+                         "sums the residual norm of its incoming iterate", pass_launches, pass_ms, (4 if var else 3) * word * dof)
     else:
         pass_roof = roof(pass_kernel(dim, pby, ppd, var, ir, pwv, ppr, word=word),
                          pass_blocks(dim, n, pby, pzc, ppr),
                          ("finest-level FP64 refinement pass (u += e, r = f - A u, r to "
                           + ("FP32" if word == 4 else "scaled binary16") + ", norm partials)") if ir
                          else "finest-level FP64 residual-norm pass", pass_launches, pass_ms,
-                         (pass_bytes + (8 if var else 0)) * dof,
-                         traffic_record(args.workload, (pby, pzc, ppd, pwv) + (("p",) if ppr else ()),
-                                        key="pass_configs"))
+                         (pass_bytes + (8 if var else 0)) * dof)
     if pass_roof["total_ms"] > sweep_roof["total_ms"]:
         roofline, other = pass_roof, sweep_roof
     else:

@@ -12,10 +12,10 @@ duration, so that launches of one kernel on different grid levels are told
 apart.  ``--counters`` prints per-dispatch averages of the counters of a
 ``--pmc`` run.  ``--traffic`` turns one ``FETCH_SIZE`` run and one
 ``WRITE_SIZE`` run of the benchmark (started with ``--calibrate-copy``, so
-that each run also holds three 1 GiB device copies) into HBM bytes per launch
-of the benchmark's dominant kernel: each counter is scaled by the factor that
-makes it read 1 GiB for the copy kernel, and the record is tagged with the
-hash of the device sources it was measured on.  It reads only rocprofv3's
+that each run also holds three 1 GiB device copies) into HBM bytes per launch of
+the kernels on the benchmark's finest level: each counter is scaled by the
+factor that makes it read 1 GiB for the copy kernel, and the record is tagged
+with the hash of the device sources it was measured on.  It reads only rocprofv3's
 output files and the benchmark's JSON line.
 """
 
@@ -40,7 +40,7 @@ def kernel_source_hash() -> str:
     """Hash of the device-code sources (kernels and their shared headers)."""
     h = hashlib.sha256()
     for name in sorted(os.listdir(CSRC)):
-        if name.startswith(("mg_smooth", "mg_resid", "mg_transfer", "mg_kern", "mg_internal")):
+        if name.startswith(("mg_smooth", "mg_leg", "mg_resid", "mg_transfer", "mg_kern", "mg_internal")):
             with open(os.path.join(CSRC, name), "rb") as fh:
                 h.update(name.encode())
                 h.update(fh.read())
@@ -58,6 +58,17 @@ def sweep_kernel(dim: int, word: int, by: int, pd: int, var: bool = False, wv: i
     if wv == 1:  # one wavefront per tile, rows in registers
         return f"mg::k_smooth3d_rc<{t}, 0, {v}, {by}, {pd}, {flags}>"
     return f"mg::k_smooth3d<{t}, 0, {v}, {by}, {pd}, {flags}, {wv}>"
+
+
+def launched_sweep(dim: int, word: int, by: int, pd: int, var: bool = False, wv: int = 4, flags: int = 0) -> str:
+    """Name, as short_name lists it, of the kernel that an RBGS sweep with the
+    given geometry launches: on the 3D Laplacian one wavefront per tile holds
+    its nodes by colour (and has no prefetch depths), everything else is
+    sweep_kernel."""
+    if dim == 3 and wv == 1 and not var:
+        t = {2: "_Float16", 4: "float", 8: "double"}[word]
+        return f"mg::k_smooth3d_rb<{t}, 0, {by}, {flags}>"
+    return sweep_kernel(dim, word, by, pd, var, wv, flags)
 
 
 def pass_kernel(dim: int, by: int, pd: int, var: bool = False, ir: bool = True, wv: int = 4, pairs: int = 0,
@@ -105,11 +116,9 @@ def sweep_blocks(dim: int, n: int, by: int, zchunk: int) -> int:
 def short_name(name: str) -> str:
     name = name.strip().replace("(anonymous namespace)::", "")
     name = re.sub(r"\([^()]*\)$", "", name).replace("void ", "")
-    # sweeps by operator (0 Laplacian, 1 nodal coefficients) are listed as without / with
-    # coefficients, and the one-wavefront red-black form, which has no prefetch depths, as depth 1
-    name = re.sub(r"(k_smooth(?:2d|3d|3d_rc)<\w+, \d, )([01])(?=,)",
+    # sweeps by operator (0 Laplacian, 1 nodal coefficients) are listed as without / with coefficients
+    return re.sub(r"(k_smooth(?:2d|3d|3d_rc)<\w+, \d, )([01])(?=,)",
                   lambda m: m[1] + ("true" if m[2] == "1" else "false"), name)
-    return re.sub(r"k_smooth3d_rb<(\w+), 0, (\d+), (\d)>", r"k_smooth3d_rc<\1, 0, false, \2, 1, \3>", name)
 
 
 def load(path: str, from_kernel: str | None = None):
@@ -199,88 +208,43 @@ def _bench_line(path: str) -> dict:
     return json.loads(lines[-1])
 
 
-def _entry(runs, kname: str, blocks: int, algo: float) -> dict | None:
-    """Calibrated bytes per launch of one kernel and grid in both counter runs;
-    dispatches under IDLE_FRAC of the largest reading of their counter (stop
-    flag set, no work) are left out."""
-    ent = {"kernel": kname, "blocks": blocks}
-    total = 0.0
-    for cname, (per, calib_kib, factor) in runs.items():
-        vals = per.get((kname, blocks))
-        if not vals:
-            return None
-        keep = [v for v in vals if v >= IDLE_FRAC * max(vals)]
-        avg = sum(keep) / len(keep)
-        ent[cname] = {"kib_per_dispatch": avg, "dispatches": len(keep), "idle": len(vals) - len(keep),
-                      "factor": factor}
-        total += avg * 1024.0 * factor
-    ent["bytes_per_launch"] = total
-    ent["ratio_to_algorithmic"] = total / algo
-    return ent
-
-
 def traffic(fetch_db: str, write_db: str, bench_json: str) -> dict:
-    """HBM bytes per launch of the benchmark's finest-level sweep and
-    refinement pass, from one FETCH_SIZE and one WRITE_SIZE run (KiB per
-    dispatch), each calibrated on the 1 GiB copies of the same run.  The tile
-    autotuner launches every candidate geometry on the finest level during
-    setup, so the record holds one entry per geometry present in both runs,
-    keyed "by,zchunk,prefetch,waves"."""
+    """HBM bytes per launch on the benchmark's finest level, from one FETCH_SIZE
+    and one WRITE_SIZE run (KiB per dispatch), each calibrated on the 1 GiB
+    copies of the same run: one entry per library kernel and grid of both runs
+    whose launches move at least half of what a finest-level sweep has to (the
+    tuner's candidates among them, so a later run that chooses another finds
+    its own).  Dispatches under IDLE_FRAC of the largest reading of their counter (stop
+    flag set, no work) are left out."""
     b = _bench_line(bench_json)
     cfg = b["config"]
     dim, n = cfg["dim"], cfg["n"]
     word = 4 if "f32" in b["dtype"] else 8
-    var = "varcoef" in cfg["workload"]
-    algo = (4 if var else 3) * word * (n - 2) ** dim
-    runs = {}
+    least = 0.5 * (4 if "varcoef" in cfg["workload"] else 3) * word * (n - 2) ** dim
+    per, factor = {}, {}
     for db, cname in ((fetch_db, "FETCH_SIZE"), (write_db, "WRITE_SIZE")):
-        per = _counter_rows(db, cname)
-        copies = [v for (k, _), vals in per.items() if k == "mg::k_copy_bytes" for v in vals]
+        per[cname] = _counter_rows(db, cname)
+        copies = [v for (k, _), vals in per[cname].items() if k == "mg::k_copy_bytes" for v in vals]
         if not copies:
             raise SystemExit(f"{db}: no k_copy_bytes dispatches (run the benchmark with --calibrate-copy)")
-        calib_kib = max(copies)
-        runs[cname] = (per, calib_kib, COPY_BYTES / (calib_kib * 1024.0))
-    zcs = (4, 8, 16, 32, 64, 128, 256) if dim == 3 else (1,)
-    pds = (1, 2) if dim == 3 else (1,)
-    configs = {}
-    for by, wv in ((8, 4), (16, 4), (32, 4), (16, 8), (32, 8), (8, 1), (12, 1)):
-        if dim == 2 and wv != 4:
+        factor[cname] = COPY_BYTES / (max(copies) * 1024.0)
+    launches = []
+    for kernel, blocks in sorted(set(per["FETCH_SIZE"]) & set(per["WRITE_SIZE"])):
+        if not kernel.startswith("mg::") or kernel == "mg::k_copy_bytes":
             continue
-        for pd in pds:
-            for zc in zcs:
-                ent = _entry(runs, sweep_kernel(dim, word, by, pd, var, wv), sweep_blocks(dim, n, by, zc), algo)
-                if ent:
-                    configs[f"{by},{zc},{pd},{wv}"] = ent
-    if not configs:
-        raise SystemExit("no finest-level sweep dispatches found in both runs")
-    # refinement pass (mixed precision): FP64 u and f read, FP32 e read, FP64 u and FP32 r written
-    ir = word == 4
-    algo_pass = ((32 if ir else 16) + (8 if var else 0)) * (n - 2) ** dim
-    pass_configs = {}
-    for by, wv in ((8, 4), (16, 4), (32, 4), (16, 8), (32, 8), (6, 1), (8, 1)):
-        if dim == 2 and wv != 4 or wv == 1 and not ir:
-            continue
-        for pd in pds:
-            for zc in zcs:
-                for pr in ((0, 1) if dim == 3 and not var else (0,)):
-                    ent = _entry(runs, pass_kernel(dim, by, pd, var, ir, wv, pr), pass_blocks(dim, n, by, zc, pr),
-                                 algo_pass)
-                    if ent:
-                        pass_configs[f"{by},{zc},{pd},{wv}" + (",p" if pr else "")] = ent
-    by, zc, pd, wv = b["extra"]["fine_tiles"]["smooth"][:4]
-    pby, pzc, ppd, pwv = b["extra"]["fine_tiles"]["norm_or_refinement"][:4]
-    ppr = b["extra"]["fine_tiles"]["norm_or_refinement"][5] if len(b["extra"]["fine_tiles"]["norm_or_refinement"]) > 5 else 0
-    return {
-        "workload": cfg["workload"],
-        "source_hash": kernel_source_hash(),
-        "algorithmic_bytes": algo,
-        "algorithmic_bytes_pass": algo_pass,
-        "calibration": {c: {"copy_kib_per_GiB": v[1], "factor": v[2]} for c, v in runs.items()},
-        "bench_tiles": f"{by},{zc},{pd},{wv}",
-        "bench_pass_tiles": f"{pby},{pzc},{ppd},{pwv}" + (",p" if ppr else ""),
-        "configs": configs,
-        "pass_configs": pass_configs,
-    }
+        ent, total = {"kernel": kernel, "blocks": blocks}, 0.0
+        for cname in factor:
+            vals = per[cname][kernel, blocks]
+            keep = [v for v in vals if v >= IDLE_FRAC * max(vals)]
+            avg = sum(keep) / len(keep)
+            ent[cname] = {"kib_per_dispatch": round(avg, 1), "dispatches": len(keep), "idle": len(vals) - len(keep)}
+            total += avg * 1024.0 * factor[cname]
+        if total >= least:
+            launches.append(dict(ent, bytes_per_launch=round(total)))
+    if not launches:
+        raise SystemExit("no finest-level dispatches found in both runs")
+    return {"workload": cfg["workload"], "source_hash": kernel_source_hash(), "calibration_factor": factor,
+            "launches": launches}
 
 
 def main(argv=None) -> int:
@@ -306,8 +270,9 @@ def main(argv=None) -> int:
                     allrec = json.load(fh)
             allrec[rec["workload"]] = rec
             with open(a.out, "w") as fh:
-                json.dump(allrec, fh, indent=1, sort_keys=True)
-                fh.write("\n")
+                # one launch a line
+                text = json.dumps(allrec, indent=1, sort_keys=True)
+                fh.write(re.sub(r"\n {4,}", " ", text) + "\n")
         return 0
     a.trace = a.trace[0]
     if a.counters:
