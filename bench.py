@@ -37,7 +37,7 @@ sys.path.insert(0, ROOT)
 from paper_1406_5369_amd.profsum import (  # noqa: E402
     kernel_source_hash,
     launched_sweep,
-    pass_blocks,
+    norm_launch,
     pass_kernel,
     sweep_blocks,
 )
@@ -685,17 +685,14 @@ def main(argv=None) -> int:
                       "finest-level RBGS sweeps that read the previous iterate (zero-iterate and fused-correction "
                       "variants excluded)", launches, sweep_ms, (4 if var else 3) * word * dof)
     pby, pzc, ppd, pwv, _, ppr = mg.mg_tile_config(solver.ctx, 0, 2, with_order=True)
-    nby, nzc, npd, nwv = mg.mg_tile_config(solver.ctx, 0, 6)
-    if not ir and nzc > 0:
+    summing = mg.mg_norm_launch(solver.ctx)
+    if summing["form"] != "pass":
         # FP64 solves sum each cycle's residual norm in the next cycle's first
-        # pre-smoothing sweep (reads u and f, writes the other buffer): the
-        # event brackets time that sweep
-        pass_roof = roof(launched_sweep(dim, word, nby, npd, var, nwv, flags=4), sweep_blocks(dim, n, nby, nzc),
-                         "finest-level FP64 first pre-smoothing launch (a sweep, on large 3D grids two) that also "
-                         "sums the residual norm of its incoming iterate", pass_launches, pass_ms, (4 if var else 3) * word * dof)
+        # launch on the finest level: the event brackets time that launch
+        name, note, needed = norm_launch(summing, dim, n, var)
+        pass_roof = roof(name, summing["blocks"], note, pass_launches, pass_ms, needed)
     else:
-        pass_roof = roof(pass_kernel(dim, pby, ppd, var, ir, pwv, ppr, word=word),
-                         pass_blocks(dim, n, pby, pzc, ppr),
+        pass_roof = roof(pass_kernel(dim, pby, ppd, var, ir, pwv, ppr, word=word), summing["blocks"],
                          ("finest-level FP64 refinement pass (u += e, r = f - A u, r to "
                           + ("FP32" if word == 4 else "scaled binary16") + ", norm partials)") if ir
                          else "finest-level FP64 residual-norm pass", pass_launches, pass_ms,
@@ -715,6 +712,7 @@ def main(argv=None) -> int:
     extra = {"solves_per_s": args.steps / (t1 - t0), "cycles_per_solve": cycles[-1],
              "ms_per_solve_graph_captured": ms_graph,
              "kernel_source_hash": kernel_source_hash(),
+             "norm_launch": summing,
              "roofline_other_kernel": other,
              "fine_tiles": {fam: mg.mg_tile_config(solver.ctx, 0, i, with_order=True) for i, fam in
                             enumerate(["smooth", "restrict", "norm_or_refinement", "smooth_zero_guess",

@@ -485,6 +485,20 @@ int mg_prof_enable(mg_ctx* ctx, int on);
 int mg_prof_read_kernel(mg_ctx* ctx, int kernel, int* launches, double* total_ms);
 int mg_prof_read(mg_ctx* ctx, int* launches, double* total_ms);
 
+/* What kernel 1 is in this context's solves: the launch that sums the residual
+ * norm of each step (form), the pre-smoothing sweeps it holds (0 for a pass of
+ * its own), its tile rows, z-chunk (2D: 1), planes loaded ahead and wavefronts
+ * as in mg_tile_config, and its workgroups.  MG_EINVAL for a batch, server or
+ * complex-diffusion handle. */
+enum mg_norm_form {
+    MG_NORM_PASS = 0,  /* norm pass, or the refinement pass (mg_tile_config family 2) */
+    MG_NORM_SWEEP = 1, /* FP64: the next cycle's first pre-smoothing sweep (family 6) */
+    MG_NORM_PAIR = 2,  /* FP64, 3D: its first two, in one launch */
+    MG_NORM_LEG = 3    /* FP64, 2D: its descending leg on the finest level, restriction included */
+};
+int mg_norm_launch(const mg_ctx* ctx, int* form, int* sweeps, int* by, int* zchunk, int* prefetch, int* waves,
+                   int* blocks);
+
 /* Plain device-to-device copy kernel of 'bytes' bytes (multiple of 16):
  * calibration of the HBM traffic counters against a known byte count. */
 int mg_copy_kernel(void* dst, const void* src, size_t bytes, void* stream);

@@ -132,6 +132,7 @@ def lib():
             "mg_prof_enable": (i, [p, i]),
             "mg_prof_read": (i, [p, C.POINTER(i), C.POINTER(d)]),
             "mg_prof_read_kernel": (i, [p, i, C.POINTER(i), C.POINTER(d)]),
+            "mg_norm_launch": (i, [p] + [C.POINTER(i)] * 7),
             "mg_copy_kernel": (i, [p, p, sz, p]),
             "mg_batch_setup": (i, [i, p, p, C.POINTER(p)]),
             "mg_batch_solve": (i, [p, p, p, d, i, p, p]),
@@ -595,6 +596,16 @@ def mg_prof_read(ctx: int, kernel: int = 0):
     ms = C.c_double(0.0)
     _check(lib().mg_prof_read_kernel(ctx, kernel, C.byref(n), C.byref(ms)), "mg_prof_read_kernel")
     return n.value, ms.value
+
+
+def mg_norm_launch(ctx: int) -> dict:
+    """What mg_prof_read's kernel 1 is in this context's solves: form ("pass", "sweep", "pair" or "leg"), sweeps,
+    by, zchunk, prefetch, waves and blocks (workgroups)."""
+    v = [C.c_int(0) for _ in range(7)]
+    _check(lib().mg_norm_launch(ctx, *(C.byref(x) for x in v)), "mg_norm_launch")
+    out = dict(zip(("form", "sweeps", "by", "zchunk", "prefetch", "waves", "blocks"), (x.value for x in v)))
+    out["form"] = ("pass", "sweep", "pair", "leg")[out["form"]]
+    return out
 
 
 def mg_copy_kernel(dst, src, stream=None) -> None:

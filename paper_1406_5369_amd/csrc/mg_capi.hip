@@ -1574,6 +1574,45 @@ int mg_prof_read_kernel(mg_ctx* c, int kernel, int* launches, double* total_ms) 
 
 int mg_prof_read(mg_ctx* c, int* launches, double* total_ms) { return mg_prof_read_kernel(c, 0, launches, total_ms); }
 
+int mg_norm_launch(const mg_ctx* c, int* form, int* sweeps, int* by, int* zchunk, int* prefetch, int* waves,
+                   int* blocks) {
+    if (!c || is_batch_handle(c) || c->cd) return MG_EINVAL;
+    if (!form || !sweeps || !by || !zchunk || !prefetch || !waves || !blocks) return MG_EINVAL;
+    const Problem& P = c->prob;
+    const int dim = c->p.dim, n = c->p.n, op = P.op();
+    TileCfg cfg;
+    if (!c->nrm_fused) {
+        *form = MG_NORM_PASS;
+        *sweeps = 0;
+        const bool plain = c->st || c->cc;  // one node per thread
+        cfg = plain ? TileCfg{0, 0, 0, 4} : is_ir(c->p) ? c->top.norm : norm_cfg(c);
+        *blocks = c->st   ? st_norm_parts(dim, n)
+                  : c->cc ? cc_norm_parts(dim, n)
+                          : norm_tiles(dim, n, cfg);
+    } else {
+        const Tiles& t = c->tl64[0];
+        *sweeps = first_sweeps(P, t, n);
+        if (leg_ok(P, n) && *sweeps == P.nu1) {
+            *form = MG_NORM_LEG;
+            cfg = {16 * leg_p(op, n, 1), 1, 1, 8};
+            *blocks = down2d_tiles(op, n);
+        } else if (*sweeps == 2) {
+            *form = MG_NORM_PAIR;
+            cfg = t.pair_nrm;
+            *blocks = smooth3d_x2_tiles(op, n, cfg);
+        } else {
+            *form = MG_NORM_SWEEP;
+            cfg = t.smooth_nrm;
+            *blocks = smooth_tiles(dim, P.smoother, n, cfg, op);
+        }
+    }
+    *by = cfg.by;
+    *zchunk = cfg.zchunk;
+    *prefetch = cfg.pd;
+    *waves = cfg.wv;
+    return MG_OK;
+}
+
 int mg_copy_kernel(void* dst, const void* src, size_t bytes, void* stream) {
     if (!dst || !src || bytes % 16 != 0) return MG_EINVAL;
     CK(launch_copy_bytes(dst, src, bytes, (hipStream_t)stream));

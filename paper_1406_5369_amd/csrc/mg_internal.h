@@ -193,6 +193,7 @@ hipError_t launch_down2d(int op, const GridDesc* d, int ninst, int n, int sel, i
 template <typename T>
 hipError_t launch_up2d(int op, const GridDesc* d, int ninst, int n, int sel, int ns, hipStream_t s);
 int down2d_tiles(int op, int n);
+int leg_p(int op, int n, int ninst);  // row pairs per thread: boxes of 16 leg_p rows
 // 3D Laplacian, FP32 or binary16 storage: the last red-first RBGS pre-smoothing
 // sweep of input 'sel' fused with the residual of its result and full
 // weighting into fc (cfg.by 16 rows, cfg.zchunk coarse planes per workgroup,

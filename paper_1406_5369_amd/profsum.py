@@ -71,6 +71,25 @@ def launched_sweep(dim: int, word: int, by: int, pd: int, var: bool = False, wv:
     return sweep_kernel(dim, word, by, pd, var, wv, flags)
 
 
+def norm_launch(info: dict, dim: int, n: int, var: bool = False):
+    """The launch that sums an FP64 solve's residual norm (mg_norm_launch's
+    answer for a node grid of n per axis, not "pass"): its name, what it is, and
+    the bytes it cannot do without.  Each form reads u and f (and k) and writes
+    the iterate once, however many sweeps it holds; a leg also writes the coarse
+    right-hand side."""
+    op, inner, coarse = int(var), (n - 2) ** dim, ((n - 1) // 2 - 1) ** dim
+    bytes_ = (4 if var else 3) * 8 * inner
+    sweeps = {1: "first pre-smoothing sweep", 2: "first two pre-smoothing sweeps in one launch"}[info["sweeps"]]
+    note = f"finest-level FP64 {sweeps}, which also sums the residual norm of its incoming iterate"
+    if info["form"] == "leg":
+        note = (f"finest-level FP64 descending leg (pre-smoothing sweeps: {info['sweeps']}; residual, full weighting), "
+                "which also sums the residual norm of its incoming iterate")
+        return f"mg::k_down2d<double, {op}, 4, {info['by'] // 16}>", note, bytes_ + 8 * coarse
+    if info["form"] == "pair":
+        return f"mg::k_smooth3d_x2<double, {op}, 2, {info['waves']}, 4>", note, bytes_
+    return launched_sweep(dim, 8, info["by"], info["prefetch"], var, info["waves"], 4), note, bytes_
+
+
 def pass_kernel(dim: int, by: int, pd: int, var: bool = False, ir: bool = True, wv: int = 4, pairs: int = 0,
                 word: int = 4) -> str:
     """Demangled name of the finest-level FP64 refinement pass (updating, as

@@ -1,4 +1,6 @@
-"""Sweeps by colour are listed under their own name, and HBM traffic by kernel and grid."""
+"""Names, workgroups and bytes of the launches that sum an FP64 solve's norm, as
+they stand in the kernel traces of whole solves (profiles/k_solves_fused_legs_pairs.md),
+and the listing of the sweeps by colour under their own name."""
 
 import json
 import sqlite3
@@ -6,6 +8,28 @@ import sqlite3
 import pytest
 
 from paper_1406_5369_amd import profsum
+
+
+def info(form, sweeps, by, waves=8, prefetch=1):
+    return dict(form=form, sweeps=sweeps, by=by, zchunk=64, prefetch=prefetch, waves=waves, blocks=1)
+
+
+def test_leg():
+    name, _, needed = profsum.norm_launch(info("leg", 2, 32), 2, 129)
+    assert name == "mg::k_down2d<double, 0, 4, 2>"
+    # u, f and the iterate on 127^2 inner nodes, the right-hand side on 63^2 coarse ones
+    assert needed == 8 * (3 * 127**2 + 63**2)
+    assert profsum.norm_launch(info("leg", 1, 64), 2, 4097)[0] == "mg::k_down2d<double, 0, 4, 4>"
+    name, _, needed = profsum.norm_launch(info("leg", 2, 32), 2, 129, var=True)
+    assert name == "mg::k_down2d<double, 1, 4, 2>" and needed == 8 * (4 * 127**2 + 63**2)
+
+
+def test_pair_and_sweep():
+    name, note, needed = profsum.norm_launch(info("pair", 2, 32), 3, 257)
+    assert name == "mg::k_smooth3d_x2<double, 0, 2, 8, 4>" and needed == 24 * 255**3 and "two" in note
+    name, _, needed = profsum.norm_launch(info("sweep", 1, 16, prefetch=2), 3, 65)
+    assert name == "mg::k_smooth3d<double, 0, false, 16, 2, 4, 8>" and needed == 24 * 63**3
+    assert profsum.norm_launch(info("sweep", 1, 32, waves=4), 2, 129)[0] == "mg::k_smooth2d<double, 0, false, 32, 4>"
 
 
 def test_sweeps_by_colour_keep_their_name():
