@@ -936,7 +936,7 @@ __global__ __launch_bounds__(NT) void k_cd_resblk(const Cx* __restrict__ u_, con
 // and below) down to one cell in one launch, one workgroup, all fields in LDS.
 // Launched apart these levels took 50 launches of 2 - 4 us each in 2D (2 - 4
 // us is what an empty launch and a few dependent divisions cost).  Here a step
-// ends with a barrier, or, for levels of at most 16^2 / 4^3 cells, which the
+// ends with a barrier, or, for levels of at most 8^2 / 4^3 cells, which the
 // first wavefront runs alone, with none.  Per cell the expressions are those
 // of the tiled sweeps (boundary faces through mirror ghosts) and of the
 // residual and transfer kernels; each sweep and residual forms q of the

@@ -58,9 +58,10 @@ enum Op { OP_LAP = 0, OP_VAR = 1, OP_STENCIL = 2, OP_CC = 3 };
 enum SweepFlags {
     SWEEP_ZERO_GUESS = 1,  // the incoming iterate is identically zero: read nothing
     SWEEP_PROLONG = 2,     // incoming iterate is u + P uc (coarse-grid correction fused into the load)
-    SWEEP_NORM = 4,        // FP64 Laplacian / coefficient-field sweeps of an LDS tile geometry: also sum
-                           // r^2 = (f - A u)^2 of the incoming iterate over the tile's output nodes
-                           // into npart[blockIdx.x] (one partial per workgroup)
+    SWEEP_NORM = 4,        // FP64: also sum r^2 = (f - A u)^2 of the incoming iterate (cells: of u - mean)
+                           // over the tile's output nodes into npart[blockIdx.x] (one partial per
+                           // workgroup): LDS sweeps, two 3D sweeps in one launch, descending legs, and
+                           // on cells the sweeps by colour and Jacobi
 };
 
 // One grid at one level, as the kernels see it.  All pointers are device
@@ -74,7 +75,7 @@ struct GridDesc {
     const void* k;    // nodal diffusion coefficient, or null for the Laplacian
     const void* fx;   // 3D with k: face coefficients in the arithmetic type, three arrays of n^3
                       // values (+x, +y, +z face of every node; 1 where the face leaves the grid),
-                      // read by the LDS sweeps; null otherwise
+                      // read by the LDS sweeps and the restriction; null otherwise
     void* uc;         // next coarser level's u (prolongation source), or null
     void* fc;         // next coarser level's f (restriction target), or null
     const int* done;  // per-instance stop flag (non-zero: skip), or null

@@ -22,13 +22,20 @@
 //   full weighting and interpolation: see the restriction and interp helpers.
 //
 // Data layout: one dense array per field, x fastest, idx = (k*n + j)*n + i.
-// Workgroups are 256 threads (four wave64); a workgroup owns an x-y tile and,
-// in 3D, marches along z through a chunk of planes, keeping a ring of three
-// planes in LDS (halo included) so each HBM value is fetched about once per
-// sweep.  Red-black Gauss-Seidel is fused: the red half-sweep is computed on
-// the tile plus a one-node ring (from a two-node ring of old values), the
-// black half-sweep on the tile, and the result is written out-of-place to the
-// ping-pong buffer, so tiles never read values another tile has updated.
+// A workgroup owns an x-y tile and, in 3D, marches along z through a chunk of
+// planes, so that each HBM value is fetched about once per sweep.  Lane = x.
+// The tile is held in one of two ways:
+//   - in LDS with its halo (a ring of three planes in 3D), 256 or 512 threads:
+//     2D sweeps, 3D Jacobi sweeps and those with coefficients, norm and
+//     refinement passes of two nodes per lane;
+//   - in registers, the rows of a column per thread, x-neighbours from the
+//     adjacent lanes: one wavefront (3D sweeps by colour, restriction, the
+//     refinement pass in columns) or several stacked in y that exchange their
+//     edge rows through LDS (legs in 2D, two 3D sweeps in one launch).
+// Red-black Gauss-Seidel is fused: each half-sweep is computed on one ring less
+// than the one before it, from a box of old values, and the result is written
+// out-of-place to the ping-pong buffer, so tiles never read values another tile
+// has updated.
 #pragma once
 
 #include "mg_internal.h"
@@ -178,22 +185,6 @@ __device__ __forceinline__ T lds_res2(const T (*A)[BX], const T (*K)[BX], int ly
     }
 }
 
-// 3D: planes Ab (below, z-1), Ac (centre), Aa (above, z+1).
-template <typename T, int OP>
-__device__ __forceinline__ T lds_res3(const T (*Ab)[BX], const T (*Ac)[BX], const T (*Aa)[BX], const T (*Kb)[BX],
-                                      const T (*Kc)[BX], const T (*Ka)[BX], int ly, int lx, T f, T c, T& dsum,
-                                      const T* s = nullptr) {
-    if constexpr (OP == OP_VAR) {
-        return res_var3(Ac[ly][lx], Ac[ly][lx - 1], Ac[ly][lx + 1], Ac[ly - 1][lx], Ac[ly + 1][lx], Ab[ly][lx],
-                        Aa[ly][lx], Kc[ly][lx], Kc[ly][lx - 1], Kc[ly][lx + 1], Kc[ly - 1][lx], Kc[ly + 1][lx],
-                        Kb[ly][lx], Ka[ly][lx], f, c, dsum);
-    } else {
-        dsum = T(0);
-        return res_const3<OP>(Ac[ly][lx], Ac[ly][lx - 1], Ac[ly][lx + 1], Ac[ly - 1][lx], Ac[ly + 1][lx], Ab[ly][lx],
-                              Aa[ly][lx], f, c, s);
-    }
-}
-
 // Relaxation of Section 2.4: u + omega * diag^-1 * r.
 template <typename T, bool VAR>
 __device__ __forceinline__ T relax(T uC, T r, T dsum, T c, T wd, T om) {
@@ -214,23 +205,6 @@ __device__ __forceinline__ T interp2(P e, int nc, int i, int j) {
     if (oi && !oj) return T(0.5) * (q[0] + q[1]);
     if (!oi && oj) return T(0.5) * (q[0] + q[nc]);
     return T(0.25) * ((q[0] + q[1]) + (q[nc] + q[nc + 1]));
-}
-
-// Trilinear interpolation at fine node (i, j, k); the odd axes are taken in
-// x, y, z order (s0 first, s1 second, s2 third).
-template <typename T, typename P>
-__device__ __forceinline__ T interp3(P e, int nc, int i, int j, int k) {
-    const size_t sy = (size_t)nc, sz = (size_t)nc * nc;
-    const auto q = e + (size_t)(k >> 1) * sz + (size_t)(j >> 1) * sy + (i >> 1);
-    size_t s[3];
-    int m = 0;
-    if (i & 1) s[m++] = 1;
-    if (j & 1) s[m++] = sy;
-    if (k & 1) s[m++] = sz;
-    if (m == 0) return q[0];
-    if (m == 1) return T(0.5) * (q[0] + q[s[0]]);
-    if (m == 2) return T(0.25) * ((q[0] + q[s[0]]) + (q[s[1]] + q[s[0] + s[1]]));
-    return T(0.125) * (((q[0] + q[1]) + (q[sy] + q[1 + sy])) + ((q[sz] + q[1 + sz]) + (q[sy + sz] + q[1 + sy + sz])));
 }
 
 // Map the dispatch-order block id to a tile id such that the blocks that land
