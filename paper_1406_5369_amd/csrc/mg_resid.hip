@@ -897,8 +897,10 @@ __global__ __launch_bounds__(64 * WV) void k_ir3d(const IRDesc* __restrict__ des
 // marches along z; neighbours along x come from the adjacent lanes.  No LDS, no
 // barrier.  With coefficients it forms each face once where it is used by both
 // of its rows or planes (3 1/4 divisions per node instead of six).
-// What bounds it is memory (32 bytes a node, 40 with coefficients): 257^3 with
-// coefficients 163 us against 181 for the LDS tile (680 MB: 110 us at 6.2 TB/s);
+// What bounds it is memory (32 bytes a node, 40 with coefficients) and, with
+// coefficients, the divisions' latency at one wavefront a SIMD: 257^3 with
+// coefficients 163 us against 181 for the LDS tile (723 MB at 4.4 TB/s, 663 MB
+// needed: 107 us at 6.2 TB/s);
 // seven grids of 129^3 100 / 127 us.  At 513^3 the tiles of two nodes per lane,
 // whose accesses are 16 bytes wide, stay ahead.
 template <bool VAR, int BY, int FL>

@@ -19,13 +19,16 @@ namespace {
 // barrier.
 //
 // Two sweeps apart read u and f and write u twice; here once.  What bounds this
-// kernel is vector-ALU issue: 40 .. 50 operations per row and plane for the four
-// half-sweeps, 1.5 times over for the rings, at 2 .. 4 wavefronts per SIMD (the
-// ring of planes is 100 .. 216 registers).  So the steps have no branches but
-// the output's, and the plane's parity is known where a step is compiled.
+// kernel on large grids is memory: at 513^3 FP32 it moves 2.96 GB (1.67 needed;
+// halo rows and planes miss L2) at 5.9 TB/s, next to vector-ALU issue for half of
+// the time (40 .. 50 operations per row and plane for the four half-sweeps, 1.5
+// times over for the rings).  On fewer boxes it is the 2 .. 4 wavefronts per
+// SIMD (the ring of planes is 100 .. 216 registers), too few to cover either:
+// 257^3 FP64 4.5 TB/s, issue 0.4.  So the steps have no branches but the
+// output's, and the plane's parity is known where a step is compiled.
 // Measured: 513^3 FP32 correction and two sweeps 489 us against 452 + 379 apart
-// (1.65 GB it cannot do without: 270 us at 6.2 TB/s); 257^3 FP64 with the norm
-// 110 us against 113 + 93, with the correction 108 against 115 + 93 (66 us).
+// (270 us at 6.2 TB/s for the bytes needed); 257^3 FP64 with the norm 110 us
+// against 113 + 93, with the correction 108 against 115 + 93 (66 us).
 // Boxes of 64 rows (four pairs per thread): 520 us at 513^3; loading two planes
 // ahead: 511 us.
 //

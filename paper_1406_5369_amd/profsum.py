@@ -37,13 +37,13 @@ BX = 64               # tile width of the sweep kernels
 
 
 def kernel_source_hash() -> str:
-    """Hash of the device-code sources (kernels and their shared headers)."""
+    """Hash of the device-code sources (kernels and their shared headers),
+    comments and blanks left out."""
     h = hashlib.sha256()
     for name in sorted(os.listdir(CSRC)):
         if name.startswith(("mg_smooth", "mg_leg", "mg_resid", "mg_transfer", "mg_kern", "mg_internal")):
-            with open(os.path.join(CSRC, name), "rb") as fh:
-                h.update(name.encode())
-                h.update(fh.read())
+            with open(os.path.join(CSRC, name)) as fh:
+                h.update(" ".join([name, *re.sub(r"//[^\n]*", "", fh.read()).split()]).encode())
     return h.hexdigest()[:16]
 
 
@@ -251,15 +251,16 @@ def traffic(fetch_db: str, write_db: str, bench_json: str) -> dict:
     for kernel, blocks in sorted(set(per["FETCH_SIZE"]) & set(per["WRITE_SIZE"])):
         if not kernel.startswith("mg::") or kernel == "mg::k_copy_bytes":
             continue
-        ent, total = {"kernel": kernel, "blocks": blocks}, 0.0
+        moved, seen = {}, {}
         for cname in factor:
             vals = per[cname][kernel, blocks]
             keep = [v for v in vals if v >= IDLE_FRAC * max(vals)]
-            avg = sum(keep) / len(keep)
-            ent[cname] = {"kib_per_dispatch": round(avg, 1), "dispatches": len(keep), "idle": len(vals) - len(keep)}
-            total += avg * 1024.0 * factor[cname]
+            moved[cname] = sum(keep) / len(keep) * 1024.0 * factor[cname]
+            seen[cname] = len(keep)
+        total = sum(moved.values())
         if total >= least:
-            launches.append(dict(ent, bytes_per_launch=round(total)))
+            launches.append({"kernel": kernel, "blocks": blocks, "bytes_per_launch": round(total),
+                             "read": round(moved["FETCH_SIZE"]), "dispatches": min(seen.values())})
     if not launches:
         raise SystemExit("no finest-level dispatches found in both runs")
     return {"workload": cfg["workload"], "source_hash": kernel_source_hash(), "calibration_factor": factor,
@@ -290,8 +291,7 @@ def main(argv=None) -> int:
             allrec[rec["workload"]] = rec
             with open(a.out, "w") as fh:
                 # one launch a line
-                text = json.dumps(allrec, indent=1, sort_keys=True)
-                fh.write(re.sub(r"\n {4,}", " ", text) + "\n")
+                fh.write(re.sub(r"\n {4,}|\n {3}(?=})", " ", json.dumps(allrec, indent=1)) + "\n")
         return 0
     a.trace = a.trace[0]
     if a.counters:

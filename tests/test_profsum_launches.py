@@ -60,4 +60,4 @@ def test_traffic_by_kernel_and_grid(tmp_path):
     (e,) = rec["launches"]
     assert (e["kernel"], e["blocks"]) == ("mg::k_smooth3d_x2<float, 0, 2, 8, 2>", 7)
     assert e["bytes_per_launch"] == pytest.approx(1024 * (2.0 * 500000.0 + 400000.0))
-    assert e["FETCH_SIZE"]["dispatches"] == 2 and e["FETCH_SIZE"]["idle"] == 1
+    assert e["read"] == pytest.approx(1024 * 2.0 * 500000.0) and e["dispatches"] == 2
