@@ -1501,6 +1501,11 @@ int mg_solve(mg_ctx* c, double* u, const double* f, double tol, int max_cycles, 
     // that advance them write them there, so the host waits for a chunk and
     // reads, with no copies and no wait before the first chunk (a solve had
     // five copies and four waits, 40 us of the 550 us of ten 129 x 129 cycles).
+    // Not waiting for rho_0 costs a solve whose first residual is zero the launches
+    // of one chunk that find the flag set (129^2 FP64 102 us against 54, 257^3 269
+    // / 135, 513^3 FP32 refinement 778 / 610) and saves every other solve the gap
+    // (17 us of 381 at 129^2, 15 of 3250 at 257^3; a first chunk of one step with
+    // a look at the flag before the rest is queued cost 2 .. 20 us).
     const double* hist = c->h_pin + kPinHist;
     const int* ctl = (const int*)c->h_pin;  // done, steps, status
     CK(launch_solve_init(c->d_norm, c->d_norm0, ctl_done(c), ctl_steps(c), ctl_status(c), c->h_pin + kPinHist,
