@@ -11,8 +11,8 @@ Printed: one JSON line with fine-grid DoF/s (value), the plain FP64 solve of
 the same problem for context, the roofline of the dominant kernel (of the
 finest-level FP32 smoothing sweep and the FP64 refinement pass, the one with
 the larger total time; both timed with HIP events on the solver's stream over
-the timed region, the other reported beside it) and the CPU oracle timed on a
-bounded sample.
+the timed region, the other reported beside it if the solves launch it) and
+the CPU oracle timed on a bounded sample.
 
 The default line also carries, in `extra`, shorter runs of the batched form
 (512 uneven 2D grids, solves/s and DoF/s beside the same grids solved one by
