@@ -1904,6 +1904,7 @@ int mg_level_ir_update(int dim, int n, const double* k, const double* u_in, cons
     TileCfg cfg = pick_cfg(dim, 8, n, 0, OP_LAP, by, zchunk, 2, true);
     if (prefetch) cfg.pd = prefetch;
     if (waves) cfg.wv = waves;
+    if (cfg.wv == 1 && !by) return MG_EINVAL;  // columns are named by their rows
     cfg.xp = pairs ? 2 : 1;
     if (cfg.xp == 2 && dim == 2 && !zchunk) cfg.zchunk = 32;  // rows each wavefront marches
     if (!valid_cfg(cfg, dim, 8, k != nullptr, 2)) return MG_EINVAL;
@@ -2234,6 +2235,7 @@ int mg_level_ir_update_noalloc(int dim, int n, const double* k, const double* u_
     TileCfg cfg = pick_cfg(dim, 8, n, 0, OP_LAP, by, zchunk, 2, true);
     if (prefetch) cfg.pd = prefetch;
     if (waves) cfg.wv = waves;
+    if (cfg.wv == 1 && !by) return MG_EINVAL;  // columns are named by their rows
     cfg.xp = pairs ? 2 : 1;
     if (cfg.xp == 2 && dim == 2 && !zchunk) cfg.zchunk = 32;
     if (!valid_cfg(cfg, dim, 8, k != nullptr, 2)) return MG_EINVAL;

@@ -59,7 +59,7 @@ def test_reported_tile_is_accepted(varcoef, dev_ok, monkeypatch):
     run(n, varcoef, False, by=by, zchunk=zchunk, prefetch=prefetch, waves=waves, pairs=pairs)
 
 
-@pytest.mark.parametrize("tile", [dict(by=12), dict(by=16), dict(by=8, prefetch=2), dict(by=8, pairs=1)])
+@pytest.mark.parametrize("tile", [dict(), dict(by=12), dict(by=16), dict(by=8, prefetch=2), dict(by=8, pairs=1)])
 def test_other_columns_are_refused(tile, dev_ok):
     import paper_1406_5369_amd as m
 
