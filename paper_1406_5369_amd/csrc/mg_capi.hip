@@ -334,7 +334,7 @@ int bind(mg_ctx* c, const void* u, const void* f, bool start) {
     // waits nor copies from the host (it may be captured) and a replayed capture,
     // which binds its own arrays, leaves nothing behind for a later call.
     if (c->st || c->cc) {
-        CK(launch_bind(c->d_top, c->G64[0].d, const_cast<void*>(u), f, start ? ctl_done(c) : nullptr, c->stream));
+        CK(launch_bind(c->d_top, c->G64[0].d, const_cast<void*>(u), f, ctl_done(c), c->stream));
         return MG_OK;
     }
     if (start) CK(launch_fill_int(ctl_done(c), 0, 1, c->stream));
@@ -379,8 +379,8 @@ TileCfg norm_cfg(const mg_ctx* c) {
 }
 
 hipError_t enqueue_norm(mg_ctx* c, hipStream_t s, int step = 0, const StopTest* stop = nullptr) {
-    if (c->cc) return cc_norm(c->p.dim, c->d_top, c->p.n, c->d_partial, c->d_norm, s, stop);
-    if (c->st) return st_norm(c->p.dim, c->d_top, c->p.n, c->d_partial, c->d_norm, s, stop);
+    if (c->cc) return cc_norm(c->p.dim, c->d_top, c->p.n, nullptr, nullptr, c->d_partial, c->d_norm, s, stop);
+    if (c->st) return st_norm(c->p.dim, c->d_top, c->p.n, nullptr, nullptr, c->d_partial, c->d_norm, s, stop);
     const bool var = c->prob.var;
     const TileCfg cfg = norm_cfg(c);
     const int nparts = norm_tiles(c->p.dim, c->p.n, cfg);
@@ -1464,9 +1464,15 @@ int mg_residual_norm(mg_ctx* c, const double* u, const double* f, double* out) {
     if (!c || !out) return MG_EINVAL;
     if (is_batch_handle(c)) return MG_EINVAL;
     if (c->cd) return MG_EINVAL;  // complex-diffusion handles take the mg_cdiff_* calls
-    int r = bind(c, u, f, false);
-    if (r != MG_OK) return r;
-    CK(enqueue_norm(c, c->stream));
+    if (c->st || c->cc) {  // arrays to the kernel, no launch to bind them
+        if (!u || !f) return MG_EINVAL;
+        CK(c->cc ? cc_norm(c->p.dim, c->d_top, c->p.n, u, f, c->d_partial, c->d_norm, c->stream)
+                 : st_norm(c->p.dim, c->d_top, c->p.n, u, f, c->d_partial, c->d_norm, c->stream));
+    } else {
+        const int r = bind(c, u, f, false);
+        if (r != MG_OK) return r;
+        CK(enqueue_norm(c, c->stream));
+    }
     CK(hipMemcpyAsync(c->h_pin, c->d_norm, sizeof(double), hipMemcpyDeviceToHost, c->stream));
     CK(hipStreamSynchronize(c->stream));
     *out = c->h_pin[0];

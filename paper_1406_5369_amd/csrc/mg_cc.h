@@ -29,10 +29,11 @@ hipError_t cc_mean(int dim, int n, const double* v, const GridDesc* d, double* w
 hipError_t cc_subtract(int dim, int n, double* v, const GridDesc* d, const double* mean, hipStream_t s);
 hipError_t cc_remove_mean(int dim, int n, double* v, double* work, double* mean, hipStream_t s);
 size_t cc_work_doubles(int dim, int n);
-// norm[0] = ||f - A u||_2 of the grid d (partials: cc_norm_parts doubles)
+// norm[0] = ||f - A u||_2 of the grid d (partials: cc_norm_parts doubles); u, f:
+// its iterate and right-hand side where null
 int cc_norm_parts(int dim, int n);
-hipError_t cc_norm(int dim, const GridDesc* d, int n, double* part, double* norm, hipStream_t s,
-                   const StopTest* stop = nullptr);
+hipError_t cc_norm(int dim, const GridDesc* d, int n, const double* u, const double* f, double* part, double* norm,
+                   hipStream_t s, const StopTest* stop = nullptr);
 
 // The steps of a cycle on a level given by its descriptor (OP_CC of the
 // launchers in mg_internal.h), and the coarse tail.

@@ -170,10 +170,12 @@ __global__ __launch_bounds__(NT) void k_cc_sub(double* __restrict__ v_, const Gr
 
 // per-block partial sums of r^2 (the residual norm; any summation order)
 template <int DIM>
-__global__ __launch_bounds__(NT) void k_cc_norm(const GridDesc* __restrict__ desc, double* __restrict__ part) {
+__global__ __launch_bounds__(NT) void k_cc_norm(const GridDesc* __restrict__ desc, const double* __restrict__ u_,
+                                                const double* __restrict__ f_, double* __restrict__ part) {
     __shared__ double red4[4];
     const GridDesc& d = *desc;
-    const MG_GLOBAL double* __restrict__ u = gp((const double*)d.u);
+    const MG_GLOBAL double* __restrict__ u = gp(u_ ? u_ : (const double*)d.u);
+    const MG_GLOBAL double* __restrict__ f = gp(f_ ? f_ : (const double*)d.f);
     const int n = d.n;
     const size_t N = DIM == 2 ? (size_t)n * n : (size_t)n * n * n;
     const size_t p = (size_t)blockIdx.x * NT + threadIdx.x;
@@ -181,7 +183,7 @@ __global__ __launch_bounds__(NT) void k_cc_norm(const GridDesc* __restrict__ des
     if (p < N) {
         int i, j, k;
         cc_ijk<DIM>(p, n, i, j, k);
-        const double r = gp((const double*)d.f)[p] - cc_apply<DIM>(u, n, d.c, i, j, k, p);
+        const double r = f[p] - cc_apply<DIM>(u, n, d.c, i, j, k, p);
         acc = r * r;
     }
     const double s = block_sum(acc, red4);
@@ -663,11 +665,11 @@ hipError_t cc_subtract(int dim, int n, double* v, const GridDesc* d, const doubl
 
 int cc_norm_parts(int dim, int n) { return (int)blocks_for(cc_cells(dim, n)); }
 
-hipError_t cc_norm(int dim, const GridDesc* d, int n, double* part, double* norm, hipStream_t s,
-                   const StopTest* stop) {
+hipError_t cc_norm(int dim, const GridDesc* d, int n, const double* u, const double* f, double* part, double* norm,
+                   hipStream_t s, const StopTest* stop) {
     const int nparts = cc_norm_parts(dim, n);
-    if (dim == 2) k_cc_norm<2><<<nparts, NT, 0, s>>>(d, part);
-    else k_cc_norm<3><<<nparts, NT, 0, s>>>(d, part);
+    if (dim == 2) k_cc_norm<2><<<nparts, NT, 0, s>>>(d, u, f, part);
+    else k_cc_norm<3><<<nparts, NT, 0, s>>>(d, u, f, part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_norm_finalize(part, nparts, nparts, 0, 1, norm, s, stop);

@@ -295,8 +295,8 @@ hipError_t launch_inject(int dim, int nf, const TS* src, int nc, TD* dst, hipStr
 template <typename TS, typename TD>
 hipError_t launch_convert(size_t total, const TS* src, TD* dst, hipStream_t s);
 hipError_t launch_fill_int(int* p, int v, int count, hipStream_t s);
-// The iterate and right-hand side of two descriptors of one grid; 'done', if
-// not null, is cleared.
+// The iterate and right-hand side of two descriptors of one grid; 'done' is
+// cleared.
 hipError_t launch_bind(GridDesc* a, GridDesc* b, void* u, const void* f, int* done, hipStream_t s);
 
 // Plain device copy of 'bytes' bytes (bandwidth calibration kernel).

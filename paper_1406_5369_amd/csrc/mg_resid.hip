@@ -1222,7 +1222,7 @@ __global__ void k_fill_int(int* __restrict__ p, int v, int count) {
 }
 
 __global__ void k_bind(GridDesc* a, GridDesc* b, void* u, const void* f, int* done) {
-    if (done && threadIdx.x == 0) *done = 0;
+    if (threadIdx.x == 0) *done = 0;
     GridDesc* d = threadIdx.x == 0 ? a : b;
     d->u = u;
     d->f = f;

@@ -24,9 +24,10 @@ hipError_t st_restrict(int dim, const double* u, const double* f, double* fc, co
 // n = 3: the single unknown u = f / (c s0)
 hipError_t st_coarsest(int dim, double* u, const double* f, const STConst& L, hipStream_t s);
 // norm[0] = ||f - A u||_2 over inner nodes of the grid (device descriptor) of
-// edge n (part: st_norm_parts doubles)
+// edge n (part: st_norm_parts doubles); u, f: its iterate and right-hand side
+// where null
 int st_norm_parts(int dim, int n);
-hipError_t st_norm(int dim, const GridDesc* d, int n, double* part, double* norm, hipStream_t s,
-                   const StopTest* stop = nullptr);
+hipError_t st_norm(int dim, const GridDesc* d, int n, const double* u, const double* f, double* part, double* norm,
+                   hipStream_t s, const StopTest* stop = nullptr);
 
 }  // namespace mg

@@ -106,7 +106,8 @@ __global__ void k_st_coarsest(double* __restrict__ u_, const double* __restrict_
 
 // per-block partial sums of r^2 over inner nodes
 template <int DIM>
-__global__ __launch_bounds__(NT) void k_st_norm(const GridDesc* __restrict__ desc, double* __restrict__ part) {
+__global__ __launch_bounds__(NT) void k_st_norm(const GridDesc* __restrict__ desc, const double* __restrict__ u,
+                                                const double* __restrict__ f, double* __restrict__ part) {
     __shared__ double red4[4];
     const GridDesc& d = *desc;
     STConst L;
@@ -122,7 +123,7 @@ __global__ __launch_bounds__(NT) void k_st_norm(const GridDesc* __restrict__ des
         int i, j, k;
         st_ijk<DIM>(p, n, i, j, k);
         if (st_inner<DIM>(n, i, j, k)) {
-            const double r = st_res<DIM>(gp((const double*)d.u), gp((const double*)d.f), L, p);
+            const double r = st_res<DIM>(gp(u ? u : (const double*)d.u), gp(f ? f : (const double*)d.f), L, p);
             acc = r * r;
         }
     }
@@ -174,11 +175,11 @@ hipError_t st_coarsest(int dim, double* u, const double* f, const STConst& L, hi
 
 int st_norm_parts(int dim, int n) { return (int)nblk(nodes(dim, n)); }
 
-hipError_t st_norm(int dim, const GridDesc* d, int n, double* part, double* norm, hipStream_t s,
-                   const StopTest* stop) {
+hipError_t st_norm(int dim, const GridDesc* d, int n, const double* u, const double* f, double* part, double* norm,
+                   hipStream_t s, const StopTest* stop) {
     const int np = st_norm_parts(dim, n);
-    if (dim == 2) k_st_norm<2><<<np, NT, 0, s>>>(d, part);
-    else k_st_norm<3><<<np, NT, 0, s>>>(d, part);
+    if (dim == 2) k_st_norm<2><<<np, NT, 0, s>>>(d, u, f, part);
+    else k_st_norm<3><<<np, NT, 0, s>>>(d, u, f, part);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_norm_finalize(part, np, np, 0, 1, norm, s, stop);
