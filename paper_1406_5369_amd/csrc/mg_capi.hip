@@ -372,11 +372,9 @@ void prof_end(mg_ctx* c, int step, int kind, hipStream_t s) {
     c->prof_kind.push_back(kind);
 }
 
-// Geometry of the norm pass: that of the refinement pass, which alone has the
-// one-wavefront columns.
-TileCfg norm_cfg(const mg_ctx* c) {
-    return c->top.norm.wv == 1 ? lds_tiles(c->p.dim, c->p.n, c->prob.smoother).norm : c->top.norm;
-}
+// Geometry of the norm pass: that of the refinement pass or, where the pass runs
+// in one-wavefront columns, which the norm has not, the next best.
+TileCfg norm_cfg(const mg_ctx* c) { return c->top.norm.wv == 1 ? c->norm_tile : c->top.norm; }
 
 hipError_t enqueue_norm(mg_ctx* c, hipStream_t s, int step = 0, const StopTest* stop = nullptr) {
     if (c->cc) return cc_norm(c->p.dim, c->d_top, c->p.n, nullptr, nullptr, c->d_partial, c->d_norm, s, stop);
@@ -676,8 +674,10 @@ std::vector<TileCfg> tune_candidates(int dim, int planes, bool with_pd, int fami
 
 // Time every candidate (after warming the GPU up to its working clocks) in three
 // interleaved rounds and keep the fastest by its best round.
+// 'tiles', if not null: the fastest of the candidates that are no one-wavefront columns.
 template <class Launch>
-TileCfg pick_fastest(const std::vector<TileCfg>& cands, TileCfg fallback, Launch&& launch, hipStream_t s) {
+TileCfg pick_fastest(const std::vector<TileCfg>& cands, TileCfg fallback, Launch&& launch, hipStream_t s,
+                     TileCfg* tiles = nullptr) {
     hipEvent_t a = nullptr, b = nullptr;
     if (cands.empty() || hipEventCreate(&a) != hipSuccess || hipEventCreate(&b) != hipSuccess) return fallback;
     std::vector<float> best_ms(cands.size(), 1e30f);
@@ -716,12 +716,17 @@ TileCfg pick_fastest(const std::vector<TileCfg>& cands, TileCfg fallback, Launch
         }
     }
     TileCfg best = fallback;
-    float bt = 1e30f;
-    for (size_t i = 0; i < cands.size(); ++i)
+    float bt = 1e30f, tt = 1e30f;
+    for (size_t i = 0; i < cands.size(); ++i) {
         if (ok[i] && best_ms[i] < bt) {
             bt = best_ms[i];
             best = cands[i];
         }
+        if (tiles && ok[i] && cands[i].wv != 1 && best_ms[i] < tt) {
+            tt = best_ms[i];
+            *tiles = cands[i];
+        }
+    }
     (void)hipEventDestroy(a);
     (void)hipEventDestroy(b);
     return best;
@@ -1142,8 +1147,9 @@ hipError_t autotune(mg_ctx* c) {
     if (e == hipSuccess && N >= kTuneMinPoints) {
         const bool var = c->prob.var;
         const int mode = c->p.precision == MG_PREC_FP64 ? 0 : (is_h16(c->p) ? 2 : 1);
-        TuneKey kn{dim, 8, n, 2, 0, var ? 1 : 0, mode, 0};
+        TuneKey kn{dim, 8, n, 2, 0, var ? 1 : 0, mode, 0}, kt{dim, 8, n, 2, 0, var ? 1 : 0, 4, 0};
         TileCfg cfg;
+        if (mode == 1) (void)tune_lookup(kt, &c->norm_tile);
         if (!tune_lookup(kn, &cfg)) {
             std::vector<TileCfg> cands;
             for (TileCfg t : tune_candidates(dim, n - 2, true, 2, 8, var))
@@ -1193,13 +1199,14 @@ hipError_t autotune(mg_ctx* c) {
                         cfg = pick_fastest(cands, c->top.norm, [&](TileCfg t) {
                             return mode == 2 ? launch_ir_update_f16(dim, d, 1, n, 0, 0, part, maxparts, t, s)
                                              : launch_ir_update(dim, var, d, 1, n, 0, 0, part, maxparts, t, s);
-                        }, s);
+                        }, s, &c->norm_tile);
                     (void)hipStreamSynchronize(s);
                     ffree(d);
                     ffree(tscl);
                     ffree(tmax);
                 }
                 ffree(part);
+                if (e == hipSuccess && mode == 1) tune_store(kt, c->norm_tile);
                 if (e == hipSuccess) tune_store(kn, cfg);
             }
         }
@@ -1265,6 +1272,7 @@ int mg_setup(const mg_params* p, void* stream, mg_ctx** out) {
         c->tl32.push_back(default_tiles(dim, ir_elem(c->p), c->n[(size_t)l], c->prob.smoother, c->prob.op()));
     }
     c->top = c->tl64[0];
+    c->norm_tile = c->top.norm;
     if (is_h16(c->p)) {  // the binary16 refinement pass has two nodes per lane
         c->top.norm.xp = 2;
         if (dim == 2) c->top.norm.zchunk = 32;

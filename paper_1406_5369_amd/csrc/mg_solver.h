@@ -156,6 +156,7 @@ struct mg_ctx {
     std::vector<int> n;
     std::vector<mg::Tiles> tl64, tl32;  // per level launch geometry of each hierarchy
     mg::Tiles top;                      // finest-level FP64 norm / refinement kernels
+    mg::TileCfg norm_tile{16, 128};     // norm pass where the refinement pass runs in columns
     bool autotune = true;
 
     // FP64 hierarchy (precision FP64): level 0 u/f are the caller's.

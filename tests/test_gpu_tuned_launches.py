@@ -42,3 +42,24 @@ def test_tiles_name_one_kernel_each(precision, varcoef, dev_ok, monkeypatch):
         assert all(t[0] in rows for t in tiles(monkeypatch, tuned, (RESTRICT,), **par))
         for by, _, prefetch, waves, *_ in tiles(monkeypatch, tuned, (SMOOTH, ZERO, CORRECT), **par):
             assert waves != 1 or varcoef or prefetch == 1  # by colour: no prefetch depths
+
+
+@pytest.mark.parametrize("n", [65, 129, 257])
+@pytest.mark.parametrize("varcoef", [False, True])
+def test_norm_beside_a_pass_in_columns(n, varcoef, dev_ok):
+    """A tuned 3D refinement context: its pass may run in columns, its norm runs the fastest other tile."""
+    import numpy as np
+    import torch
+
+    import oracle
+    import paper_1406_5369_amd as m
+
+    f, u = inputs.uniform_rhs(3, n, 31), inputs.random_guess(3, n, 32)
+    k = inputs.varcoef_k(n, 33) if varcoef else None
+    par = dict(op=m.OP_VARCOEF_NODAL, k=torch.from_numpy(k).to("cuda")) if varcoef else {}
+    expect = float(np.sqrt((oracle.residual(u, f, k=k)[1:-1, 1:-1, 1:-1] ** 2).sum()))
+    for _ in range(2):  # the second from the cache
+        with m.Solver(m.Params(dim=3, n=n, precision=m.PREC_FP32_IR, **par)) as s:
+            got = s.residual_norm(torch.from_numpy(u).to("cuda"), torch.from_numpy(f).to("cuda"))
+        # two sums of N squares in different orders differ by at most (N - 1) 2^-53 relative each
+        assert got == pytest.approx(expect, rel=max(1e-14, 2.0 * f.size * 2.0**-53))
